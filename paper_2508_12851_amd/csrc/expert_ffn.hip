@@ -15,109 +15,13 @@
 // of this file.  GEMM1 loads the gate rows and the up rows of the same f range
 // into one tile, so silu(gate)*up is a register epilogue and only h is written.
 // Activation rows of GEMM1 are gathered through local_src (no permuted copy of
-// x is materialised).
+// x is materialised).  fp32 layers: expert_ffn_f32.hip.
 #include "grouped_gemm.h"
 #include "prism_internal.h"
 
 namespace prism {
 static bool stream_tiles_apply(const prism_layer_desc& d, int T);
 namespace {
-
-// ---------------------------------------------------------------------------
-// fp32 path (small layers only): one wavefront per output element, the
-// contraction split over lanes and reduced with shuffles.
-// ---------------------------------------------------------------------------
-struct F32Args {
-  const float* x;
-  const void* const* wg; const void* const* wu; const void* const* wd;
-  const void* const* swg; const void* const* swu; const void* const* swd;
-  const int32_t* local_src; const int32_t* local_offsets;
-  float* h; float* y;
-  int T, H, F, E, S, top_k;
-};
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
-// Resolves output row r to (group, token); returns false for rows that hold nothing.
-__device__ __forceinline__ bool resolve_row(const F32Args& p, int r, int& g, int& tok) {
-  const int A = p.T * p.top_k;
-  if (r >= A) {
-    const int s = (r - A) / p.T;
-    g = p.E + s;
-    tok = (r - A) - s * p.T;
-    return true;
-  }
-  if (r >= p.local_offsets[p.E]) return false;
-  int e = 0;
-  while (p.local_offsets[e + 1] <= r) ++e;
-  g = e;
-  tok = p.local_src[r] / p.top_k;
-  return true;
-}
-
-constexpr int kF32ColsPerBlock = 64;
-
-__global__ __launch_bounds__(256) void ffn1_f32_kernel(const F32Args p) {
-  extern __shared__ float s_x[];
-  __shared__ int s_g, s_tok, s_ok;
-  const int r = blockIdx.x;
-  if (threadIdx.x == 0) {
-    int g = 0, tok = 0;
-    s_ok = resolve_row(p, r, g, tok) ? 1 : 0;
-    s_g = g; s_tok = tok;
-  }
-  __syncthreads();
-  if (!s_ok) return;
-  const int g = s_g;
-  for (int i = threadIdx.x; i < p.H; i += blockDim.x) s_x[i] = p.x[(size_t)s_tok * p.H + i];
-  __syncthreads();
-  const float* wg = (const float*)(g < p.E ? p.wg[g] : p.swg[g - p.E]);
-  const float* wu = (const float*)(g < p.E ? p.wu[g] : p.swu[g - p.E]);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int i = wave; i < kF32ColsPerBlock; i += 4) {
-    const int f = blockIdx.y * kF32ColsPerBlock + i;
-    if (f >= p.F) break;
-    float ag = 0.f, au = 0.f;
-    for (int hh = lane; hh < p.H; hh += 64) {
-      const float xv = s_x[hh];
-      ag = fmaf(xv, wg[(size_t)f * p.H + hh], ag);
-      au = fmaf(xv, wu[(size_t)f * p.H + hh], au);
-    }
-    ag = wave_sum(ag);
-    au = wave_sum(au);
-    if (lane == 0) p.h[(size_t)r * p.F + f] = (ag / (1.0f + expf(-ag))) * au;
-  }
-}
-
-__global__ __launch_bounds__(256) void ffn2_f32_kernel(const F32Args p) {
-  extern __shared__ float s_h[];
-  __shared__ int s_g, s_ok;
-  const int r = blockIdx.x;
-  if (threadIdx.x == 0) {
-    int g = 0, tok = 0;
-    s_ok = resolve_row(p, r, g, tok) ? 1 : 0;
-    s_g = g;
-  }
-  __syncthreads();
-  if (!s_ok) return;
-  const int g = s_g;
-  for (int i = threadIdx.x; i < p.F; i += blockDim.x) s_h[i] = p.h[(size_t)r * p.F + i];
-  __syncthreads();
-  const float* wd = (const float*)(g < p.E ? p.wd[g] : p.swd[g - p.E]);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int i = wave; i < kF32ColsPerBlock; i += 4) {
-    const int n = blockIdx.y * kF32ColsPerBlock + i;
-    if (n >= p.H) break;
-    float acc = 0.f;
-    for (int f = lane; f < p.F; f += 64) acc = fmaf(s_h[f], wd[(size_t)n * p.F + f], acc);
-    acc = wave_sum(acc);
-    if (lane == 0) p.y[(size_t)r * p.H + n] = acc;
-  }
-}
 
 // ---------------------------------------------------------------------------
 // bf16 path: two grouped GEMMs on the matrix cores
@@ -377,27 +281,10 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
                                bool schedules_built) {
   if (deferred_splits != nullptr) *deferred_splits = nullptr;
   if (T == 0) return PRISM_OK;
-  const int A = T * d.top_k;
-  const int rows = A + d.n_shared * T;
-  if (d.dtype == PRISM_F32) {
-    if (d.weight_layout != PRISM_WEIGHTS_ROW_MAJOR) return PRISM_ERR_UNSUPPORTED;
-    F32Args a{(const float*)x, w.w_gate, w.w_up, w.w_down, w.shared_w_gate, w.shared_w_up,
-              w.shared_w_down, local_src, local_offsets, (float*)h, (float*)y,
-              T, d.hidden, d.ffn, d.n_experts, d.n_shared, d.top_k};
-    if ((size_t)d.hidden * 4 > 64 * 1024 || (size_t)d.ffn * 4 > 64 * 1024) return PRISM_ERR_UNSUPPORTED;
-    trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
-    hipLaunchKernelGGL(ffn1_f32_kernel, dim3(rows, ceil_div(d.ffn, kF32ColsPerBlock)), dim3(256),
-                       (size_t)d.hidden * 4, st, a);
-    PRISM_CHECK_LAUNCH();
-    trace(stage_events, PRISM_STAGE_FFN_UP, 1, st);
-    trace(stage_events, PRISM_STAGE_FFN_DOWN, 0, st);
-    hipLaunchKernelGGL(ffn2_f32_kernel, dim3(rows, ceil_div(d.hidden, kF32ColsPerBlock)), dim3(256),
-                       (size_t)d.ffn * 4, st, a);
-    PRISM_CHECK_LAUNCH();
-    trace(stage_events, PRISM_STAGE_FFN_DOWN, 1, st);
-    return PRISM_OK;
-  }
+  if (d.dtype == PRISM_F32)
+    return launch_expert_ffn_f32(d, x, w, local_src, local_offsets, T, y, h, st, stage_events);
 
+  const int rows = T * (d.top_k + d.n_shared);
   // bf16: schedules for the two GEMMs, then the GEMMs.  Buffer addressing uses
   // 32-bit byte offsets, so every operand matrix must stay below 4 GiB.
   constexpr size_t kMaxOperandBytes = 0xFFFF0000ull;

@@ -203,6 +203,11 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
                                void* const* stage_events, const int32_t** deferred_splits,
                                bool schedules_built = false);
 
+// The fp32 layers' part of launch_expert_ffn (T > 0).
+prism_status launch_expert_ffn_f32(const prism_layer_desc& d, const void* x, const prism_expert_weights& w,
+                                   const int32_t* local_src, const int32_t* local_offsets, int T, void* y,
+                                   void* h, hipStream_t st, void* const* stage_events);
+
 // True when launch_decode_front_end serves this layer shape and batch.
 bool decode_front_end_applies(const prism_layer_desc& d, int T);
 

@@ -1,0 +1,57 @@
+"""GPU: the fp32 expert FFN at the edges of its tiles (64 rows x 32 / 64 columns, k-tiles of 16, eighths of the
+contraction), against 64-bit arithmetic."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,H,F,rows,S", [
+    (1, 8, 1, [0, 1, 0], 0),                    # one element per row of the down projection
+    (5, 16, 3, [2, 0, 3], 1),                   # rows shorter than a 16-byte load
+    (70, 24, 5, [64, 1, 5], 2),                 # full tile, single row; misaligned rows of W_down
+    (130, 136, 18, [65, 32, 33], 0),            # both halves of a tile and one row more
+    (160, 200, 33, [63, 0, 97], 1),
+    (40, 1024, 2047, [7, 33, 0], 1),            # the longest chains; every weight row at another alignment
+    (300, 264, 130, [129, 128, 43], 0),
+])
+def test_f32_ffn_edges(T, H, F, rows, S):
+    import paper_2508_12851_amd as P
+    rng = np.random.default_rng([T, H, F])
+    E, A = len(rows), T                          # top_k = 1: at most one row per token
+    assert sum(rows) <= A
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    w = [[(rng.standard_normal(s) / np.sqrt(s[1])).astype(np.float32) for s in ((F, H), (F, H), (H, F))]
+         for _ in range(E + S)]
+    src = rng.permutation(A)[:sum(rows)].astype(np.int32)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+
+    def dev(a):
+        return torch.from_numpy(a).cuda()
+
+    desc = P.make_desc(H, F, E, 1, S, "f32")
+    table = P.WeightTable([tuple(map(dev, t)) for t in w[:E]], [tuple(map(dev, t)) for t in w[E:]])
+    y = torch.full((A + S * T, H), -7.0, device="cuda")
+    local_src = torch.full((A,), -1, dtype=torch.int32, device="cuda")
+    local_src[:len(src)] = dev(src)
+    P.prism_expert_ffn(desc, dev(x), table, local_src, dev(off), P.alloc_workspace(desc, T), y=y)
+    y = y.cpu().numpy()
+
+    def ffn(xr, t):
+        g, u, d = (m.astype(np.float64) for m in t)
+        a = xr.astype(np.float64)
+        z = a @ g.T
+        return (z / (1.0 + np.exp(-z)) * (a @ u.T)) @ d.T
+
+    # Each sum passes at most 4 + 2 + K/128 + 3 < 32 roundings of 2^-24; they are independent, so the
+    # relative 2-norm of a sum's error stays below sqrt(32) * 2^-24 = 3.4e-7; gate, up and down add up.
+    def check(got, ref):
+        if ref.size:
+            assert np.linalg.norm(got - ref) <= 1e-6 * np.linalg.norm(ref)
+
+    for e in range(E):
+        check(y[off[e]:off[e + 1]], ffn(x[src[off[e]:off[e + 1]]], w[e]))
+    assert (y[off[E]:A] == -7.0).all()           # rows without an assignment are not written
+    for s in range(S):
+        check(y[A + s * T:A + (s + 1) * T], ffn(x, w[E + s]))
