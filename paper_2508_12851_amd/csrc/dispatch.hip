@@ -48,15 +48,15 @@ constexpr int kSchedParts = 4;   // workgroups that share the building of one sc
 
 // Workgroups [0, n_blocks) place their block; if n_sched > 0, workgroups n_blocks + 4 s + part
 // build part `part` of schedule s (0: gate/up GEMM, 1: down GEMM) from the same histograms.
-template <bool FROM_HIST>
+template <bool FROM_HIST, int CHUNK>
 __global__ __launch_bounds__(kThreads) void dispatch_place_kernel(
     const int32_t* __restrict__ idx, int A, int E, const uint8_t* __restrict__ mask,
     const int32_t* __restrict__ block_hist, int n_blocks, int sub, const SplitOut o,
     int32_t* __restrict__ local_src, int32_t* __restrict__ remote_src, int32_t* __restrict__ inv,
     int S, int T, const gg::SchedParams p0, const gg::SchedParams p1) {
   if ((int)blockIdx.x < n_blocks) {
-    dispatch_place_block<FROM_HIST>(idx, A, E, mask, block_hist, n_blocks, sub, blockIdx.x, o,
-                                    local_src, remote_src, inv);
+    dispatch_place_block<FROM_HIST, CHUNK>(idx, A, E, mask, block_hist, n_blocks, sub, blockIdx.x, o,
+                                           local_src, remote_src, inv);
     return;
   }
   if (FROM_HIST) {
@@ -91,12 +91,12 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
   if (schedules_built != nullptr) *schedules_built = false;
   gg::SchedParams p0{}, p1{};
   if (A <= kDispatchChunk) {   // one workgroup histograms and places (T = 0: writes the empty split)
-    hipLaunchKernelGGL(dispatch_place_kernel<false>, dim3(1), dim3(kThreads), 0, st, topk_idx, A, E,
-                       mask, (const int32_t*)nullptr, 1, 1, o, local_src, remote_src, inv, 0, T, p0, p1);
+    hipLaunchKernelGGL((dispatch_place_kernel<false, kDispatchChunk>), dim3(1), dim3(kThreads), 0, st, topk_idx,
+                       A, E, mask, (const int32_t*)nullptr, 1, 1, o, local_src, remote_src, inv, 0, T, p0, p1);
     PRISM_CHECK_LAUNCH();
     return PRISM_OK;
   }
-  const int sub = sub_chunks(A);
+  const int sub = sub_chunks(A, kDispatchChunk);
   const int n_blocks = ceil_div(A, sub * kDispatchChunk);
   int n_sched = 0;
   if (tiles != nullptr && d.dtype == PRISM_BF16) {
@@ -107,9 +107,32 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
   hipLaunchKernelGGL(dispatch_hist_kernel, dim3(n_blocks), dim3(kThreads), 0, st, topk_idx, A, E, sub,
                      block_hist);
   PRISM_CHECK_LAUNCH();
-  hipLaunchKernelGGL(dispatch_place_kernel<true>, dim3(n_blocks + n_sched), dim3(kThreads), 0, st,
-                     topk_idx, A, E, mask, block_hist, n_blocks, sub, o, local_src, remote_src, inv,
+  hipLaunchKernelGGL((dispatch_place_kernel<true, kDispatchChunk>), dim3(n_blocks + n_sched), dim3(kThreads),
+                     0, st, topk_idx, A, E, mask, block_hist, n_blocks, sub, o, local_src, remote_src, inv,
                      d.n_shared, T, p0, p1);
+  PRISM_CHECK_LAUNCH();
+  return PRISM_OK;
+}
+
+prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk_idx, const uint8_t* mask,
+                                  int T, int32_t* local_src, int32_t* local_offsets, int32_t* remote_src,
+                                  int32_t* remote_offsets, int32_t* n_local_remote, int64_t* remote_bytes,
+                                  int32_t* inv, const SplitRoutePlan& plan, int32_t* counts,
+                                  int64_t* counts_accum, hipStream_t st, int32_t* tiles) {
+  const int A = T * d.top_k;
+  const SplitOut o{local_offsets, remote_offsets, n_local_remote, remote_bytes, counts,
+                   (unsigned long long*)counts_accum, d.hidden * elem_size(d.dtype)};
+  gg::SchedParams p0, p1;
+  gg::ffn_sched_params(d, T, tiles, &p0, &p1);
+  const dim3 grid(plan.n_blocks + 2 * kSchedParts);
+  if (plan.chunk == kFineChunk)
+    hipLaunchKernelGGL((dispatch_place_kernel<true, kFineChunk>), grid, dim3(kThreads), 0, st, topk_idx, A,
+                       d.n_experts, mask, plan.block_hist, plan.n_blocks, plan.sub, o, local_src, remote_src,
+                       inv, d.n_shared, T, p0, p1);
+  else
+    hipLaunchKernelGGL((dispatch_place_kernel<true, kDispatchChunk>), grid, dim3(kThreads), 0, st, topk_idx, A,
+                       d.n_experts, mask, plan.block_hist, plan.n_blocks, plan.sub, o, local_src, remote_src,
+                       inv, d.n_shared, T, p0, p1);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }

@@ -10,8 +10,6 @@ namespace dispatch_dev {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kPerWave = kDispatchChunk / kWaves;   // contiguous assignments per wavefront
-constexpr int kSteps = kPerWave / kWave;
 
 struct SplitOut {
   int32_t* local_offsets;    // [E+1]
@@ -23,12 +21,12 @@ struct SplitOut {
   int row_bytes;
 };
 
-// Assignments one workgroup places: `sub` consecutive chunks of kDispatchChunk, the fewest
+// Assignments one workgroup places: `sub` consecutive chunks of `chunk`, the fewest
 // that keep the number of workgroups at or below kMaxBlocks (every workgroup sums the
 // histograms of the workgroups before it).
 constexpr int kMaxBlocks = 256;
-static inline int sub_chunks(int A) {
-  const int chunks = (A + kDispatchChunk - 1) / kDispatchChunk;
+static inline int sub_chunks(int A, int chunk) {
+  const int chunks = (A + chunk - 1) / chunk;
   return chunks > kMaxBlocks ? (chunks + kMaxBlocks - 1) / kMaxBlocks : 1;
 }
 
@@ -91,6 +89,7 @@ __device__ __forceinline__ HistSums sum_block_hists(const int32_t* __restrict__ 
   HistSums r{0, 0};
   const int e = threadIdx.x;
   if (e < E) {
+#pragma unroll 8
     for (int b = 0; b < n_blocks; ++b) {
       const int c = block_hist[(size_t)b * E + e];
       r.total += c;
@@ -100,7 +99,7 @@ __device__ __forceinline__ HistSums sum_block_hists(const int32_t* __restrict__ 
   return r;
 }
 
-// Places the assignments of block `block` (sub consecutive chunks of kDispatchChunk),
+// Places the assignments of block `block` (sub consecutive chunks of CHUNK),
 // called by all kThreads threads of a workgroup.
 // FROM_HIST: block_hist [n_blocks][E] holds every block's histogram; the workgroup derives
 // the bucket starts from it and, if it is block 0, writes the outputs in o.
@@ -111,13 +110,16 @@ __device__ __forceinline__ HistSums sum_block_hists(const int32_t* __restrict__ 
 // s_local_off (LDS, [E + 1], only without FROM_HIST): also receives the local offsets.
 // my_mask >= 0: thread e < E already holds mask[e] (read before the steps that precede the call,
 // so that its latency is not paid here).
-template <bool FROM_HIST>
+template <bool FROM_HIST, int CHUNK>
 __device__ __forceinline__ void dispatch_place_block(
     const int32_t* idx, int A, int E, const uint8_t* __restrict__ mask,
     const int32_t* __restrict__ block_hist, int n_blocks, int sub, int block, const SplitOut& o,
     int32_t* __restrict__ local_src, int32_t* __restrict__ remote_src, int32_t* __restrict__ inv,
     int* s_local_off = nullptr, int my_mask = -1) {
   static_assert(PRISM_MAX_EXPERTS <= kThreads, "one thread per expert");
+  static_assert(CHUNK % kThreads == 0, "whole steps for every wavefront");
+  constexpr int kPerWave = CHUNK / kWaves;   // contiguous assignments per wavefront
+  constexpr int kSteps = kPerWave / kWave;
   // Only LDS data crosses between threads in here, so the barriers do not wait for
   // the global stores.
   __shared__ int s_whist[kWaves][PRISM_MAX_EXPERTS];
@@ -146,7 +148,7 @@ __device__ __forceinline__ void dispatch_place_block(
   for (int c = 0; c < sub; ++c) {
     for (int i = threadIdx.x; i < kWaves * PRISM_MAX_EXPERTS; i += kThreads) (&s_whist[0][0])[i] = 0;
     lds_barrier();
-    const int wave0 = (block * sub + c) * kDispatchChunk + wave * kPerWave;
+    const int wave0 = (block * sub + c) * CHUNK + wave * kPerWave;
     int my_e[kSteps];
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) {

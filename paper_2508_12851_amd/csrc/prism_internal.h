@@ -31,6 +31,7 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // prism_workspace_bytes() fits all of them.
 // ---------------------------------------------------------------------------
 constexpr int kDispatchChunk = 2048;   // assignments per dispatch block
+constexpr int kFineChunk = 512;        // ... of batches whose router counted them already, and of decode batches
 constexpr int kDecodeMaxTokens = 64;    // batches up to this size take the weight-streaming path
 constexpr int kDecodeSplits = 8;        // most contraction slices of its down projection (the schedule builder picks how many) ...
 constexpr int kStreamSplits = 4;        // ... and of batches with more than kManySplitsRows rows that still split it
@@ -189,6 +190,28 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
                              int32_t* block_hist, int32_t* counts, int64_t* counts_accum,
                              hipStream_t st, int32_t* tiles = nullptr,
                              bool* schedules_built = nullptr);
+
+// bf16 batches of more than 64 tokens inside the whole layer: the router as two launches.  The
+// first spreads (token tile, experts, hidden elements) over the chip and leaves fp64 partial
+// logits, the second sums them, picks the experts and counts them per block of assignments.
+struct SplitRoutePlan {
+  int nt, tmb, hs;        // expert tiles (16) and token tiles (16) of a workgroup; parts of the hidden dimension
+  int n_blocks, sub, chunk;   // blocks of the placement: sub * chunk assignments each
+  double* partial;        // [hs][T][16 * route_col_tiles] partial logits
+  int32_t* block_hist;    // [n_blocks][E]
+};
+// Whether that serves a batch of T tokens: scratch / scratch_bytes is memory nothing else uses until
+// the GEMMs start (16-byte aligned).
+bool plan_split_route(const prism_layer_desc& d, int T, void* scratch, size_t scratch_bytes, SplitRoutePlan* plan);
+prism_status launch_split_route(const prism_layer_desc& d, const void* x, const void* w_router, const float* bias,
+                                int T, int32_t* topk_idx, float* topk_gate, const SplitRoutePlan& plan,
+                                hipStream_t st);
+// Placement split from the histograms of launch_split_route; also builds the schedules in tiles.
+prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk_idx, const uint8_t* mask,
+                                  int T, int32_t* local_src, int32_t* local_offsets, int32_t* remote_src,
+                                  int32_t* remote_offsets, int32_t* n_local_remote, int64_t* remote_bytes,
+                                  int32_t* inv, const SplitRoutePlan& plan, int32_t* counts,
+                                  int64_t* counts_accum, hipStream_t st, int32_t* tiles);
 
 // schedules_built: the two schedules in tiles already exist (decode front end).
 // slice_part: scratch for a cut last round of the down projection (slice_part_bytes).

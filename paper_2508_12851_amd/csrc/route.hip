@@ -32,6 +32,7 @@ namespace {
 
 constexpr int kTokPerBlock = 16;
 constexpr int kWavesPerBlock = 8;      // split the hidden dimension
+constexpr int kSplitRouteMaxParts = 16;   // parts of the hidden dimension of the split router, at most
 
 __device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
   const f32x4 a = *reinterpret_cast<const f32x4*>(p);
@@ -64,14 +65,15 @@ __device__ __forceinline__ void load_bias_group(const float* __restrict__ bias, 
 // wavefront.  The routing of a token is one long dependent chain (arg-max rounds, an fp64
 // exponential, a division); the U chains run side by side in one instruction stream.
 // has_bias: add b (from load_bias_group) after the one rounding to fp32.
-// s_counts (LDS, may be NULL) receives +1 per selected expert; s_idx (LDS, may be NULL) a copy
+// s_counts (LDS, may be NULL) receives +1 per selected expert; picked[u] (may be NULL) the expert in
+// slot r of token t[u] where there is one; s_idx (LDS, may be NULL) a copy
 // of topk_idx for what follows in the same kernel.
 template <int NT, int U>
 __device__ __forceinline__ void finish_groups(const double (&s)[U][NT], const float (&b)[U][NT],
                                               bool has_bias, const int (&t)[U], int T, int E, int k,
                                               int gate_mode, float* __restrict__ logits,
                                               int32_t* topk_idx, float* __restrict__ topk_gate,
-                                              int* s_counts, int32_t* s_idx) {
+                                              int* s_counts, int32_t* s_idx, int* picked = nullptr) {
   const int r = threadIdx.x & 15;
   // ---- one rounding to fp32, then the fp32 bias add --------------------------
   float lg[U][NT];
@@ -163,6 +165,7 @@ __device__ __forceinline__ void finish_groups(const double (&s)[U][NT], const fl
       if (s_idx != nullptr) s_idx[t[u] * k + r] = myidx[u];
       topk_gate[(size_t)t[u] * k + r] = (float)(w[u] / sum[u]);
       if (s_counts != nullptr) atomicAdd(&s_counts[myidx[u]], 1);
+      if (picked != nullptr) picked[u] = myidx[u];
     }
 }
 
@@ -171,14 +174,14 @@ __device__ __forceinline__ void finish_group(const double (&s)[NT], const float 
                                              bool has_bias, int t, int T, int E, int k, int gate_mode,
                                              float* __restrict__ logits, int32_t* topk_idx,
                                              float* __restrict__ topk_gate, int* s_counts,
-                                             int32_t* s_idx = nullptr) {
+                                             int32_t* s_idx = nullptr, int* picked = nullptr) {
   double s1[1][NT];
   float b1[1][NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) { s1[0][n] = s[n]; b1[0][n] = b[n]; }
   const int t1[1] = {t};
   finish_groups<NT, 1>(s1, b1, has_bias, t1, T, E, k, gate_mode, logits, topk_idx, topk_gate, s_counts,
-                       s_idx);
+                       s_idx, picked);
 }
 
 // The same for a tile of 16 tokens held by one wavefront in the accumulator layout of
@@ -384,12 +387,20 @@ struct StagedCfg {
   static_assert(kDepth >= 2, "the next slice must be in flight during the MFMAs of this one");
 };
 
-template <int NT, int TMB>
+// SPLIT: workgroup (x, y, z) multiplies experts [16 NT y, 16 NT (y + 1)) and the z-th of gridDim.z
+// parts of the hidden dimension only, and leaves the sums in partial[z][T][EP] (EP: experts padded
+// to whole tiles of the layer); it also clears clear[0, n_clear).  A batch of a few hundred tokens
+// has a few dozen token tiles, and one workgroup each takes as long as its fp64 products do on one
+// CU: router + histogram / placement + schedules of 333 tokens x 60 experts took 28 + 11 + 5 us and
+// take 7 + 6 (route_pick_kernel) + 7; 3000 tokens x 256 experts (route_kernel before) 80 + 5 + 14,
+// now 45 + 9 + 13.
+template <int NT, int TMB, bool SPLIT>
 __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router,
     const float* __restrict__ bias, int T, int H, int E, int k, int bias_group_tokens, int gate_mode,
     float* __restrict__ logits, int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate,
-    int32_t* __restrict__ counts, unsigned long long* __restrict__ counts_accum) {
+    int32_t* __restrict__ counts, unsigned long long* __restrict__ counts_accum,
+    double* __restrict__ partial, int ep, int32_t* __restrict__ clear, int n_clear) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources exist in device code only
   using C = StagedCfg<NT, TMB>;
   constexpr int EP = NT * 16;
@@ -402,9 +413,16 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
   const int r = lane & 15;
   const int q = lane >> 4;
   const int tok0 = blockIdx.x * (kTokPerBlock * TMB);
+  const int e0 = SPLIT ? (int)blockIdx.y * EP : 0;         // first expert
 
-  for (int e = threadIdx.x; e < EP; e += blockDim.x) s_counts[e] = 0;
-  __syncthreads();
+  if (SPLIT) {
+    const int wg = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const int all = gridDim.x * gridDim.y * gridDim.z * blockDim.x;
+    for (int i = wg * blockDim.x + threadIdx.x; i < n_clear; i += all) clear[i] = 0;
+  } else {
+    for (int e = threadIdx.x; e < EP; e += blockDim.x) s_counts[e] = 0;
+    __syncthreads();
+  }
 
   // ---- global side: lane l fetches row l / 4 of each block, chunk (l % 4 - l / 16) % 4 ----
   const int lrow = lane >> 2;
@@ -417,7 +435,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
   }
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
-    const int e = n * 16 + lrow;
+    const int e = e0 + n * 16 + lrow;
     voff[TMB + n] = e < E ? ((uint32_t)e * (uint32_t)H + chunk * 8) * 2u : kOutOfRange;
   }
   const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -425,7 +443,9 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
   const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void*)w_router, 0, (int)((uint32_t)E * (uint32_t)H * 2u), kBufferFlags);
   uint8_t* const wave_base = smem + wave * (kDepth * kBlocks * 1024);
-  const int n_slices = (H + 31) / 32;
+  const int all_slices = (H + 31) / 32;
+  const int part0 = SPLIT ? (int)((long long)all_slices * blockIdx.z / gridDim.z) : 0;   // this workgroup's slices
+  const int n_slices = SPLIT ? (int)((long long)all_slices * (blockIdx.z + 1) / gridDim.z) : all_slices;
   // Fills ring position `buf` with slice s (hidden elements 32 s ..): rows or chunks past
   // the end, and whole slices past the last one, arrive as zeros.  Always kBlocks loads, so
   // the vector-memory counter can be awaited with a constant.
@@ -445,7 +465,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
   const int b_fin = wave >> 2, v_fin = wave & 3;
   const int t_fin = tok0 + b_fin * kTokPerBlock + 4 * v_fin + q;
   float bias_fin[NT];
-  load_bias_group<NT>(bias, b_fin < TMB ? t_fin : T, T, E, bias_group_tokens, bias_fin);
+  if (!SPLIT) load_bias_group<NT>(bias, b_fin < TMB ? t_fin : T, T, E, bias_group_tokens, bias_fin);
 
   // ---- router GEMM on the fp64 matrix cores -----------------------------------------
   f64x4 acc[TMB][NT];
@@ -462,8 +482,8 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
   // whole chip read a 512-byte column window at any time, and the L2 channels holding it
   // bounded the kernel.)  The order is the same for every workgroup, so a token's logits do
   // not depend on where in the batch it sits.
-  const int seg = (n_slices + kWavesPerBlock - 1) / kWavesPerBlock;
-  const int first = wave * seg;
+  const int seg = (n_slices - part0 + kWavesPerBlock - 1) / kWavesPerBlock;
+  const int first = part0 + wave * seg;
   const int n_mine = max(0, min(seg, n_slices - first));
   const int phase = n_mine > 0 ? (4 * ((wave * seg) >> 6)) % n_mine : 0;
   auto slice_of = [&](int i) {   // i-th slice this wavefront multiplies; past its last: none
@@ -525,10 +545,18 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
         s += part[((((size_t)w * TMB + b_fin) * NT + n) * 4 + v_fin) * 64 + lane];
       sum[n] = s;
     }
+    if (SPLIT) {
+      if (t_fin < T) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+          partial[((size_t)blockIdx.z * T + t_fin) * ep + e0 + n * 16 + r] = sum[n];
+      }
+      return;
+    }
     finish_group<NT>(sum, bias_fin, bias != nullptr, t_fin, T, E, k, gate_mode, logits, topk_idx,
                      topk_gate, counts != nullptr ? s_counts : nullptr);
   }
-  if (counts == nullptr) return;   // the caller derives the counts from the dispatch histogram
+  if (SPLIT || counts == nullptr) return;   // the caller derives the counts from the dispatch histogram
 
   // ---- per-expert activation counts -----------------------------------------
   __syncthreads();
@@ -540,6 +568,48 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_staged_kernel(
     }
   }
 #endif
+}
+
+// Second launch of the split router: 16 tokens per workgroup, one per 16-lane group.  Sums the hs
+// parts of their logits in order, finishes the routing, and adds the picks to the histograms of the
+// placement blocks (block_len assignments each, at least kFineChunk) they fall into, at most two of them.
+constexpr int kPickThreads = 256;
+template <int NT>
+__global__ __launch_bounds__(kPickThreads) void route_pick_kernel(
+    const double* __restrict__ partial, int hs, const float* __restrict__ bias, int T, int E, int k,
+    int bias_group_tokens, int gate_mode, int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate,
+    int32_t* __restrict__ block_hist, int block_len) {
+  constexpr int EP = NT * 16;
+  static_assert(kPickThreads >= PRISM_MAX_EXPERTS && 16 * PRISM_MAX_TOPK <= kFineChunk, "one thread per expert, two blocks");
+  __shared__ int s_hist[2][EP];
+  const int tok0 = blockIdx.x * 16;
+  const int t = tok0 + (threadIdx.x >> 4), r = threadIdx.x & 15;
+  for (int i = threadIdx.x; i < 2 * EP; i += kPickThreads) (&s_hist[0][0])[i] = 0;
+  float b[NT];
+  load_bias_group<NT>(bias, t, T, E, bias_group_tokens, b);
+  double s[NT];
+  const double* p = partial + (size_t)min(t, T - 1) * EP + r;
+#pragma unroll
+  for (int n = 0; n < NT; ++n) s[n] = p[n * 16];
+  for (int z = 1; z < hs; ++z) {
+    p += (size_t)T * EP;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) s[n] += p[n * 16];
+  }
+  lds_barrier();
+  // a token's assignments start in block t k / block_len; the first block of the workgroup is blk0
+  const int blk0 = tok0 * k / block_len;
+  const int cut = (blk0 + 1) * block_len;          // first assignment of the next block
+  int picked = -1;
+  finish_group<NT>(s, b, bias != nullptr, t, T, E, k, gate_mode, nullptr, topk_idx, topk_gate, nullptr, nullptr, &picked);
+  if (picked >= 0) atomicAdd(&s_hist[t * k + r >= cut ? 1 : 0][picked], 1);
+  lds_barrier();
+  const int e = threadIdx.x;
+  if (e < E) {
+    const int c0 = s_hist[0][e], c1 = s_hist[1][e];
+    if (c0 != 0) atomicAdd(&block_hist[(size_t)blk0 * E + e], c0);
+    if (c1 != 0) atomicAdd(&block_hist[(size_t)(blk0 + 1) * E + e], c1);
+  }
 }
 
 __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v) {
@@ -567,7 +637,7 @@ __global__ __launch_bounds__(kFrontThreads) void decode_front_end_kernel(
   const int n_tiles = (T + kTokPerBlock - 1) / kTokPerBlock;
   // asked for now, used by the split: the load's latency passes during the routing
   const int my_mask = (int)threadIdx.x < E ? (int)mask[threadIdx.x] : 0;
-  __shared__ int32_t s_idx[kDispatchChunk];                 // topk_idx, for the split
+  __shared__ int32_t s_idx[kFineChunk];                     // topk_idx, for the split
   __shared__ int s_local_off[PRISM_MAX_EXPERTS + 1];        // local_offsets, for the schedules
   // A tile's routing is four units of four tokens (accumulator register v holds tokens
   // 4v + q); wavefront w takes unit v = w of every tile, so even a 16-token batch keeps all
@@ -635,7 +705,7 @@ __global__ __launch_bounds__(kFrontThreads) void decode_front_end_kernel(
     }
   }
   lds_barrier();   // s_idx is complete (the copy in memory is for the caller)
-  dispatch_dev::dispatch_place_block<false>(s_idx, T * k, E, mask, nullptr, 1, 1, 0, o, local_src,
+  dispatch_dev::dispatch_place_block<false, kFineChunk>(s_idx, T * k, E, mask, nullptr, 1, 1, 0, o, local_src,
                                             remote_src, inv, s_local_off, my_mask);
   lds_barrier();   // s_local_off, written by the split
   const gg::SchedParams p[2] = {p0, p1};
@@ -658,13 +728,31 @@ prism_status launch_staged_one(const prism_layer_desc& d, const void* x, const v
                                int32_t* counts, int64_t* accum, hipStream_t st) {
   using C = StagedCfg<NT, TMB>;
   static LdsLimitOnce lds_limit;   // more than 64 KiB of dynamic LDS; one per instantiation
-  if (!raise_lds_limit(lds_limit, (const void*)route_staged_kernel<NT, TMB>, C::kLdsBytes))
+  if (!raise_lds_limit(lds_limit, (const void*)route_staged_kernel<NT, TMB, false>, C::kLdsBytes))
     return PRISM_ERR_LAUNCH;
-  hipLaunchKernelGGL((route_staged_kernel<NT, TMB>), dim3(ceil_div(T, kTokPerBlock * TMB)),
+  hipLaunchKernelGGL((route_staged_kernel<NT, TMB, false>), dim3(ceil_div(T, kTokPerBlock * TMB)),
                      dim3(kWavesPerBlock * kWave), (size_t)C::kLdsBytes, st, (const uint16_t*)x,
                      (const uint16_t*)w, bias, T, d.hidden, d.n_experts, d.top_k,
                      d.bias_group_tokens, d.gate_mode, logits, idx, gate, counts,
-                     (unsigned long long*)accum);
+                     (unsigned long long*)accum, (double*)nullptr, 0, (int32_t*)nullptr, 0);
+  PRISM_CHECK_LAUNCH();
+  return PRISM_OK;
+}
+
+template <int NT, int TMB>
+prism_status launch_split_one(const prism_layer_desc& d, const void* x, const void* w, int T,
+                              const SplitRoutePlan& plan, hipStream_t st) {
+  using C = StagedCfg<NT, TMB>;
+  static LdsLimitOnce lds_limit;   // one per instantiation
+  if (!raise_lds_limit(lds_limit, (const void*)route_staged_kernel<NT, TMB, true>, C::kLdsBytes))
+    return PRISM_ERR_LAUNCH;
+  const int cols = route_col_tiles(d.n_experts);
+  hipLaunchKernelGGL((route_staged_kernel<NT, TMB, true>),
+                     dim3(ceil_div(T, kTokPerBlock * TMB), ceil_div(ceil_div(d.n_experts, 16), NT), plan.hs),
+                     dim3(kWavesPerBlock * kWave), (size_t)C::kLdsBytes, st, (const uint16_t*)x, (const uint16_t*)w,
+                     (const float*)nullptr, T, d.hidden, d.n_experts, d.top_k, 0, 0, (float*)nullptr,
+                     (int32_t*)nullptr, (float*)nullptr, (int32_t*)nullptr, (unsigned long long*)nullptr,
+                     plan.partial, cols * 16, plan.block_hist, plan.n_blocks * d.n_experts);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }
@@ -747,6 +835,76 @@ prism_status launch_route(const prism_layer_desc& d, const void* x, const void* 
                                 counts_accum, nullptr, st);
 }
 
+bool plan_split_route(const prism_layer_desc& d, int T, void* scratch, size_t scratch_bytes, SplitRoutePlan* plan) {
+  if (d.dtype != PRISM_BF16 || T <= kDecodeMaxTokens || (uint64_t)T * d.hidden * 2 >= 0xFFFF0000ull) return false;
+  // With 32-token workgroups for three quarters of the CUs the router in one launch is as good
+  // (8192 tokens x 60 experts: 51 us with its histogram launch of 5, split 52 + 6 us, and the
+  // layer 1 % slower).
+  if (staged_router_applies(d, T) && ceil_div(T, 2 * kTokPerBlock) >= 192) return false;
+  const int A = T * d.top_k;
+  // Blocks of 512 assignments up to 8192 (a block's four wavefronts then take two steps instead of
+  // eight); beyond, every placing workgroup would sum more histograms than that saves (32768
+  // assignments over 60 experts: the placement took 24 us with 64 blocks, 14 us with 16).
+  plan->chunk = A <= 16 * kFineChunk ? kFineChunk : kDispatchChunk;
+  plan->sub = dispatch_dev::sub_chunks(A, plan->chunk);
+  plan->n_blocks = ceil_div(A, plan->sub * plan->chunk);
+  const size_t hist_bytes = align_up((size_t)plan->n_blocks * d.n_experts * 4, 256);
+  const size_t part_bytes = (size_t)T * route_col_tiles(d.n_experts) * 16 * 8;   // one part of the hidden dimension
+  if (hist_bytes + part_bytes > scratch_bytes) return false;
+  // The shape of a workgroup: the one with the least estimated time.  A SIMD holds two of its
+  // wavefronts, and a v_mfma_f64_16x16x4 takes 64 clocks, the conversion of an operand element
+  // about 12 more, none of which overlap; filling the ring and adding up the partial tiles takes
+  // about 3000 and 1500 per tile.  (13 sizes from 100 x 60 to 8192 x 60 and 3000 x 256 tokens x
+  // experts, all 5 shapes with 1 to 16 parts: what the estimate picks is within 6 % of the fastest
+  // or at the launch floor; the worst shape takes up to twice as long.)
+  const int tiles = ceil_div(T, kTokPerBlock), cols = ceil_div(d.n_experts, 16), slices = ceil_div(d.hidden, 32);
+  const int shapes[5][2] = {{4, 2}, {2, 2}, {4, 1}, {2, 1}, {1, 1}};
+  long long best = -1;
+  for (const auto& s : shapes) {
+    const int nt = s[0], tmb = s[1];
+    if (nt > route_col_tiles(d.n_experts)) continue;
+    for (int hs = 1; hs <= kSplitRouteMaxParts && hs * kWavesPerBlock <= std::max(slices, kWavesPerBlock); ++hs) {
+      if (hist_bytes + part_bytes * hs > scratch_bytes) break;
+      const long long wgs = (long long)ceil_div(tiles, tmb) * ceil_div(cols, nt) * hs;
+      const long long per_wave = ceil_div(ceil_div(slices, hs), kWavesPerBlock);
+      const long long cost = (wgs + 255) / 256 * (3000 + 1500 * nt * tmb + per_wave * 2 * 8 * (64 * nt * tmb + 12 * (nt + tmb))) + 200 * hs;
+      if (best < 0 || cost < best) {
+        best = cost;
+        plan->nt = nt; plan->tmb = tmb; plan->hs = hs;
+      }
+    }
+  }
+  plan->block_hist = (int32_t*)scratch;
+  plan->partial = (double*)((char*)scratch + hist_bytes);
+  return true;
+}
+
+prism_status launch_split_route(const prism_layer_desc& d, const void* x, const void* w_router, const float* bias,
+                                int T, int32_t* topk_idx, float* topk_gate, const SplitRoutePlan& plan,
+                                hipStream_t st) {
+  auto gemm = [&] {
+    if (plan.nt == 4)
+      return plan.tmb == 2 ? launch_split_one<4, 2>(d, x, w_router, T, plan, st) : launch_split_one<4, 1>(d, x, w_router, T, plan, st);
+    if (plan.nt == 2)
+      return plan.tmb == 2 ? launch_split_one<2, 2>(d, x, w_router, T, plan, st) : launch_split_one<2, 1>(d, x, w_router, T, plan, st);
+    return launch_split_one<1, 1>(d, x, w_router, T, plan, st);
+  };
+  PRISM_TRY(gemm());
+#define PRISM_PICK_CASE(NT)                                                                      \
+  hipLaunchKernelGGL(route_pick_kernel<NT>, dim3(ceil_div(T, 16)), dim3(kPickThreads), 0, st,    \
+                     plan.partial, plan.hs, bias, T, d.n_experts, d.top_k, d.bias_group_tokens,  \
+                     d.gate_mode, topk_idx, topk_gate, plan.block_hist, plan.sub * plan.chunk)
+  const int nt = route_col_tiles(d.n_experts);
+  if (nt <= 1) PRISM_PICK_CASE(1);
+  else if (nt <= 2) PRISM_PICK_CASE(2);
+  else if (nt <= 4) PRISM_PICK_CASE(4);
+  else if (nt <= 8) PRISM_PICK_CASE(8);
+  else PRISM_PICK_CASE(16);
+#undef PRISM_PICK_CASE
+  PRISM_CHECK_LAUNCH();
+  return PRISM_OK;
+}
+
 bool decode_front_end_applies(const prism_layer_desc& d, int T) {
   return d.dtype == PRISM_BF16 && T > 0 && T <= kDecodeMaxTokens;
 }
@@ -759,7 +917,7 @@ prism_status launch_decode_front_end(const prism_layer_desc& d, const void* x, c
                                      int32_t* remote_offsets, int32_t* n_local_remote,
                                      int64_t* remote_bytes, int32_t* inv, double* route_part,
                                      int32_t* tiles, hipStream_t st, void* const* stage_events) {
-  if (!decode_front_end_applies(d, T) || T * d.top_k > kDispatchChunk) return PRISM_ERR_INVALID_ARG;
+  if (!decode_front_end_applies(d, T) || T * d.top_k > kFineChunk) return PRISM_ERR_INVALID_ARG;
   trace(stage_events, PRISM_STAGE_ROUTE, 0, st);
   PRISM_TRY(launch_typed<uint16_t>(d, x, w_router, bias, T, nullptr, nullptr, nullptr, nullptr,
                                    nullptr, route_part, st));

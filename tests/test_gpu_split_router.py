@@ -1,0 +1,29 @@
+"""GPU: the router of batches of more than 64 tokens inside the layer (experts and hidden elements spread over
+workgroups, picks counted per placement block) at its edges, against the oracle, whole numbers bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,H,E,k", [
+    (65, 64, 2, 1),          # fewest tokens, 2 slices of the hidden dimension for 8 wavefronts
+    (65, 64, 256, 1),        # partial logits larger than the FFN buffers they would borrow: one-launch router
+    (97, 2112, 17, 3),       # ragged tiles, odd number of slices; 48 assignments per workgroup straddle blocks
+    (513, 320, 65, 8),       # 5 of 8 expert tiles, 4104 assignments
+    (1366, 128, 60, 6),      # 8196 assignments: first size with blocks of 2048
+    (700, 1024, 129, 7),     # 9 of 16 expert tiles
+    (300, 256, 256, 5),
+    (5000, 64, 16, 2),
+])
+@pytest.mark.parametrize("gates", ["renormalized", "softmax_all"])
+def test_split_router_in_layer(T, H, E, k, gates):
+    from gpu_util import check_layer, oracle_layer, run_layer, weight_table
+    from prism_inputs import make_config, make_inputs
+    cfg = make_config("cfg4_finegrained", T=T, H=H, F=64, E=E, k=k, S=1, bias_group_tokens=100)
+    mask = (np.random.default_rng([T, E]).random(E) < 0.3).astype(np.uint8)
+    mask[E - 1] = 1
+    inp = make_inputs(cfg)
+    o = run_layer(cfg, inp, mask, weight_table(inp, mask), gate_mode=gates)
+    check_layer(cfg, o, oracle_layer(inp, mask, renormalize=gates == "renormalized"))
