@@ -59,7 +59,12 @@ constexpr int kReduceInts = 8;       // ints per entry of the list of sliced ite
 //
 // Work order.  A group's row tiles are split into equal parts of at most kRectRows.  All
 // items -- groups in order, then row parts, then the column tiles of a row part, the row tiles
-// of a column running fastest -- form one sequence, and XCD x gets the x-th eighth of it.  So
+// of a column running fastest -- form one sequence, of which every XCD gets an eighth: the x-th
+// eighth of the routed items and then as many of the shared experts' items as make its share of
+// all items even.  (The two kinds are not equally fast: a shared expert's row tiles are full and
+// take their weights from the L2, most routed experts have one partly filled tile and take theirs
+// from HBM.  Eighths of one sequence left whole XCDs with one kind: 8192 tokens, 36 of 60 experts
+// and 4 shared ones: gate/up 608 -> 594 us, down 345 -> 320 us.)  So
 // the 32 workgroups resident on an XCD work at any time on a rectangle of about 8 row tiles x
 // 4 column tiles -- 8 activation tiles and 4 weight tiles for 32 items instead of one of each
 // per item -- which is what the XCD's L2 can share among them, and the eight lists have the
@@ -140,6 +145,7 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
                                                       int n_parts = 1) {
   __shared__ int s_rows[kMaxGroups], s_row0[kMaxGroups];
   __shared__ int s_start[NS][kMaxGroups + 1];            // first row tile of group g
+  __shared__ unsigned s_routed[NS][kXcds + 1], s_all[NS][kXcds + 1];   // see "Work order": items before XCD x's
   const int G = E + S;
   // p[s] for a thread-dependent s, without indexing the parameter array at run time
   // (that would put it in scratch memory)
@@ -164,19 +170,29 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
   if ((int)(threadIdx.x >> 6) < NS) {
     const int s = threadIdx.x >> 6;
     const SchedParams ps = pick(s);
-    int run = 0;
+    int run = 0, routed_tiles = 0;
     for (int g0 = 0; g0 < G; g0 += 64) {
       const int g = g0 + lane;
       const int rows = g < G ? s_rows[g] : 0;
       const int tiles = (rows + ps.BM - 1) / ps.BM;
       const int incl = wave_inclusive_scan(tiles);
       if (g < G) s_start[s][g] = run + incl - tiles;
+      if (E - g0 >= 1 && E - g0 <= 64) routed_tiles = run + __builtin_amdgcn_readlane(incl, E - g0 - 1);
       run += __builtin_amdgcn_readlane(incl, 63);
     }
     const int rows_total = s_row0[E - 1] + s_rows[E - 1] + S * T;   // all rows of all groups
     if (lane == 0) s_start[s][G] = run;
     const unsigned total = (unsigned)run * (unsigned)ps.n_ntiles;
     const unsigned per_xcd = (total + kXcds - 1) / kXcds;
+    // items dealt to the XCDs before XCD x: routed ones, and all of them (fewer than 8 shared items
+    // are counted as routed ones, so that no XCD's share of either is negative)
+    unsigned routed_items = (unsigned)routed_tiles * (unsigned)ps.n_ntiles;
+    if (total - routed_items < kXcds) routed_items = total;
+    auto eighths = [&](unsigned items, int x) { return (unsigned)((unsigned long long)items * (unsigned)x / kXcds); };
+    if (lane <= kXcds) {
+      s_all[s][lane] = eighths(total, lane);
+      s_routed[s][lane] = eighths(routed_items, lane);
+    }
     if (part == 0) {
       if (lane == 0) {
         ps.sched[0] = run;
@@ -187,8 +203,8 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
         unsigned count;
         if (ps.interleave)   // items x, x + 8, ...
           count = total > x ? (total - x + kXcds - 1) / kXcds : 0;
-        else                 // every list holds per_xcd items, the last non-empty one the remainder
-          count = total > x * per_xcd ? min(per_xcd, total - x * per_xcd) : 0;
+        else
+          count = eighths(total, lane + 1) - eighths(total, lane);
         const Slicing sl = slicing_of((int)count, ps.slice_kt);
         ps.sched[4 + x] = (int)count - sl.items;
         ps.sched[20 + x] = sl.items * sl.slices;
@@ -231,7 +247,7 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
       return lo;
     };
     const unsigned n_items = (unsigned)n_mtiles * (unsigned)n_ntiles;
-    const unsigned per_xcd = (n_items + kXcds - 1) / kXcds;
+    const unsigned n_routed = s_routed[s][kXcds];
     if (interleave) {
       // no lists: the kernel derives item seq = tile * n_ntiles + column tile from its position
       // (XCD x takes seq = x, x + 8, ...) and reads the row tile's line of this table
@@ -255,11 +271,20 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
       // column by column), earlier rows of its column
       const unsigned seq = (unsigned)(s_start[s][g] + rp.first) * (unsigned)n_ntiles +
                            (unsigned)(nt * rp.len + (mi - rp.first));
-      const unsigned x = seq / per_xcd;
-      const unsigned pos = seq - x * per_xcd;
+      unsigned x = 0, pos;
+      if (seq < n_routed) {
+#pragma unroll
+        for (int b = 1; b < kXcds; ++b) x += s_routed[s][b] <= seq;
+        pos = seq - s_routed[s][x];
+      } else {
+        const unsigned sh = seq - n_routed;     // XCD b starts with shared item s_all[b] - s_routed[b]
+#pragma unroll
+        for (int b = 1; b < kXcds; ++b) x += s_all[s][b] - s_routed[s][b] <= sh;
+        pos = s_routed[s][x + 1] - s_routed[s][x] + sh - (s_all[s][x] - s_routed[s][x]);
+      }
       const int4 head = int4{g, s_row0[g] + mi * BM, min(BM, s_rows[g] - mi * BM), g < E ? -1 : mi * BM};
       int4* list = reinterpret_cast<int4*>(p[s].sched + kSchedHeader + (size_t)x * capacity * kItemInts);
-      const unsigned in_list = n_items > x * per_xcd ? min(per_xcd, n_items - x * per_xcd) : 0u;
+      const unsigned in_list = s_all[s][x + 1] - s_all[s][x];
       const Slicing sl = slicing_of((int)in_list, p[s].slice_kt);
       const int first_sliced = (int)in_list - sl.items;
       if ((int)pos < first_sliced || sl.slices == 0) {
@@ -287,7 +312,7 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
       for (int r = part * blockDim.x + threadIdx.x; r < kXcds * (kSliceSlots / 2); r += n_parts * blockDim.x) {
         const unsigned x = (unsigned)r / (kSliceSlots / 2);
         const int li = r % (kSliceSlots / 2);
-        const unsigned in_list = n_items > x * per_xcd ? min(per_xcd, n_items - x * per_xcd) : 0u;
+        const unsigned in_list = s_all[s][x + 1] - s_all[s][x];
         const Slicing sl = slicing_of((int)in_list, p[s].slice_kt);
         if (li >= sl.items || sl.slices == 0)
           reinterpret_cast<int4*>(p[s].sched + sched_reduce_offset(capacity))[(size_t)r * (kReduceInts / 4) + 1] =
