@@ -21,6 +21,7 @@
 
 namespace prism {
 static bool stream_tiles_apply(const prism_layer_desc& d, int T);
+static bool few_rows_per_expert(const prism_layer_desc& d, int T);
 namespace {
 
 // ---------------------------------------------------------------------------
@@ -36,14 +37,14 @@ template <int BM_, int BN_, int BK_, int STAGES_> struct TileCfg {
 constexpr float kSplitRoundBytes = 14 * 8192.f;
 
 // What the schedule builders need to know about a path's two GEMMs (C1: gate/up, C2: down).
-template <typename C1, typename C2, bool SPLIT_DOWN>
+template <typename C1, typename C2, bool SPLIT_DOWN, bool ROTATE>
 FfnShapes shapes_of(const prism_layer_desc& d, int T) {
   FfnShapes f{};
   f.bm1 = C1::BM;
   f.nt1 = ceil_div(d.ffn, C1::BN / 2);     // GEMM1 tile: BN/2 gate rows + BN/2 up rows
   f.bm2 = C2::BM;
   f.nt2 = ceil_div(d.hidden, C2::BN);
-  f.interleave = SPLIT_DOWN;               // the paths that stream the weights once
+  f.interleave = ROTATE;
   // prefill tiles: the down projection's last round may be cut along its contraction
   f.slice_kt2 = !SPLIT_DOWN && C2::BM == 256 && down_slicing_applies(d, T) ? d.ffn / C2::BK : 0;
   if (SPLIT_DOWN) {
@@ -133,14 +134,13 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const int32_t* __restri
   }
 }
 
-template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B = false>
+template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B, bool ROTATE>
 prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_expert_weights& w,
                           const int32_t* local_src, const int32_t* local_offsets, int T, void* y,
                           void* h, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
                           void* const* stage_events, const int32_t** deferred_splits,
                           bool schedules_built) {
   using gg::GemmArgs;
-  constexpr bool kRotate = SPLIT_DOWN;   // the decode path: no weight tile is shared between items
   const int A = T * d.top_k;
   const int rows = A + d.n_shared * T;
   // the k-tile ring of a workgroup must not be longer than its contraction slice
@@ -149,7 +149,7 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   int32_t* sched2 = tiles + tile_table_ints(d, T);
   // The schedules (built here, or by the caller's dispatch) follow ffn_schedule_shapes(), which
   // must describe the kernels this instantiation launches.
-  const FfnShapes f = shapes_of<C1, C2, SPLIT_DOWN>(d, T);
+  const FfnShapes f = shapes_of<C1, C2, SPLIT_DOWN, ROTATE>(d, T);
   const FfnShapes told = ffn_schedule_shapes(d, T);
   if (f.bm1 != told.bm1 || f.nt1 != told.nt1 || f.bm2 != told.bm2 || f.nt2 != told.nt2 ||
       f.interleave != told.interleave || f.slice_kt2 != told.slice_kt2 || f.split_kt2 != told.split_kt2 ||
@@ -159,8 +159,8 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   // the down projection's last round of items may be cut along the contraction (prefill only)
   const int slice_kt = slice_part != nullptr ? f.slice_kt2 : 0;
   if (slice_kt != f.slice_kt2) return PRISM_ERR_INVALID_ARG;   // the schedule would hold slice entries
-  static_assert(SPLIT_DOWN || (C2::BM == kSliceTile && C2::BN == kSliceTile && C2::BK == 32),
-                "sum_slices_kernel assumes the prefill tile");
+  constexpr bool kCanSlice = !SPLIT_DOWN && C2::BM == kSliceTile;   // as shapes_of
+  static_assert(!kCanSlice || (C2::BN == kSliceTile && C2::BK == 32), "sum_slices_kernel assumes the prefill tile");
   if (!schedules_built) PRISM_TRY(gg::launch_build_schedules(d, local_offsets, T, tiles, st));
 
   GemmArgs g1{};
@@ -174,7 +174,7 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   g1.K = d.hidden; g1.N = d.ffn; g1.top_k = d.top_k; g1.E = d.n_experts;
   g1.b_tiled = d.weight_layout == PRISM_WEIGHTS_TILED;
   trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
-  PRISM_TRY((gg::launch_gemm<C1::BM, C1::BN, 2, 2, C1::BK, C1::STAGES, true, false, kRotate, STREAM_B>(
+  PRISM_TRY((gg::launch_gemm<C1::BM, C1::BN, 2, 2, C1::BK, C1::STAGES, true, false, ROTATE, STREAM_B>(
       g1, gg::sched_capacity(d, T, C1::BM, nt1), st)));
   trace(stage_events, PRISM_STAGE_FFN_UP, 1, st);
 
@@ -191,9 +191,9 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   // SPLIT_DOWN: the number of contraction slices is in the schedule's header (schedule.h, "Splits")
   const int32_t* n_splits = sched2 + 2;
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 0, st);
-  PRISM_TRY((gg::launch_gemm<C2::BM, C2::BN, 2, 2, C2::BK, C2::STAGES, false, SPLIT_DOWN, kRotate, STREAM_B>(
+  PRISM_TRY((gg::launch_gemm<C2::BM, C2::BN, 2, 2, C2::BK, C2::STAGES, false, SPLIT_DOWN, ROTATE, STREAM_B>(
       g2, gg::sched_capacity(d, T, C2::BM, nt2), st)));
-  if constexpr (!SPLIT_DOWN) {
+  if constexpr (kCanSlice) {
     if (slice_kt > 0)   // the cut last round: one slice entry per workgroup, fp32 partial tiles
       PRISM_TRY((gg::launch_gemm<C2::BM, C2::BN, 2, 2, C2::BK, C2::STAGES, false, false, false, false, true>(
           g2, gg::sched_capacity(d, T, C2::BM, nt2), st)));
@@ -216,11 +216,12 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
 }
 
 // One tile path of the bf16 FFN: tile shapes of the two GEMMs, whether the down projection is
-// split along its contraction, whether the weight loads are marked non-temporal.
-template <typename C1_, typename C2_, bool SPLIT_DOWN_, bool STREAM_B_> struct Path {
+// split along its contraction, whether the weight loads are marked non-temporal, whether the items
+// are dealt to the XCDs one by one with rotated contractions (grouped_gemm.h, ROTATE).
+template <typename C1_, typename C2_, bool SPLIT_DOWN_, bool STREAM_B_, bool ROTATE_> struct Path {
   using C1 = C1_;
   using C2 = C2_;
-  static constexpr bool kSplitDown = SPLIT_DOWN_, kStreamB = STREAM_B_;
+  static constexpr bool kSplitDown = SPLIT_DOWN_, kStreamB = STREAM_B_, kRotate = ROTATE_;
 };
 
 // Calls fn(Path<...>{}) with the path that serves a bf16 batch of T tokens of layer d.
@@ -239,36 +240,51 @@ auto select_path(const prism_layer_desc& d, int T, Fn&& fn) {
     // An expert has one row tile here, so every weight element is read by exactly one
     // workgroup, once: the weight loads are marked non-temporal (see STREAM_B).
     if (d.weight_layout == PRISM_WEIGHTS_TILED && d.hidden >= 256 && d.ffn >= 1024)
-      return fn(Path<TileCfg<64, 128, 32, 8>, TileCfg<64, 128, 32, 8>, true, true>{});
+      return fn(Path<TileCfg<64, 128, 32, 8>, TileCfg<64, 128, 32, 8>, true, true, true>{});
     if (d.hidden >= 192 && d.ffn >= 192)
-      return fn(Path<TileCfg<64, 128, 64, 4>, TileCfg<64, 128, 64, 4>, true, true>{});
-    return fn(Path<TileCfg<64, 128, 32, 3>, TileCfg<64, 128, 32, 3>, true, true>{});
+      return fn(Path<TileCfg<64, 128, 64, 4>, TileCfg<64, 128, 64, 4>, true, true, true>{});
+    return fn(Path<TileCfg<64, 128, 32, 3>, TileCfg<64, 128, 32, 3>, true, true, true>{});
   }
   // Batches of a few hundred tokens of a wide layer are still bound by streaming the weights
   // once, but an expert now has up to a few hundred rows; the down projection splits its
-  // contraction as for decode batches.
-  // Up to 256 tokens: 128 x 128 tiles with 64-wide k-tiles, weight loads non-temporal.  Up to
-  // 128 tokens an expert has a single row tile (a token picks an expert at most once), so the
-  // weights are read once and stream; between 129 and 256 the few experts with more than 128
-  // rows read theirs twice, which still beats the wider tiles of the next case (4096 x 14336
-  // layer, 5 of 8 experts hosted: 0.386 against 0.418 ms at 128 tokens, 0.381 against 0.413 at
-  // 129, 0.450 against 0.470 at 192, 0.470 against 0.480 at 256; at 320 they lose, 0.555 against
-  // 0.536).
-  if (stream_tiles_apply(d, T) && T <= kMidMaxTokens)
-    return fn(Path<TileCfg<128, 128, 64, 4>, TileCfg<128, 128, 64, 4>, true, true>{});
-  // Beyond, most experts have several row tiles, which share weight tiles through the L2 (the
-  // non-temporal hint costs 8-13 % there).  Tiles twice as wide in weight rows (256) as in
-  // activation rows (128) bring twice the HBM bytes per k-tile for the same waits and barriers,
-  // and the padding rows of a half-empty 256-row tile would cost their loads and MFMAs like
-  // real ones (256 x 128 tiles: 0.590 against 0.546 ms at 352 tokens; the 256 x 256 prefill
-  // tiles: their down projection has too few items to fill the machine).
-  if (stream_tiles_apply(d, T))
-    return fn(Path<TileCfg<128, 256, 32, 6>, TileCfg<128, 256, 32, 6>, true, false>{});
+  // contraction as for decode batches.  Tiles of 128 activation rows x 256 weight rows bring twice
+  // the HBM bytes per k-tile for the same waits and barriers as 128 x 128, and 64-wide k-tiles take
+  // whole 128-byte lines of the activations (and of row-major weights), which 32-wide ones ask the
+  // L2 for twice.  The row tiles of an expert stand next to each other in an XCD's list, so the
+  // second one finds the weight tile in the L2.  4096 x 14336 layer, 5 of 8 experts hosted, tiled
+  // weights, against 128 x 128 x 64 tiles dealt item by item (up to 256 tokens) and 128 x 256 x 32
+  // ones beyond: 328 -> 317 us at 110 tokens, 344 -> 335 at 160, 417 -> 375 at 230, 502 -> 419 at
+  // 352; against prefill tiles 529 -> 445 at 400, 554 -> 502 at 512.  A padded row tile of 256
+  // costs its loads and MFMAs like a full one: prefill tiles with the cut last round are
+  // even at 1024 tokens (between 512 and there: not split here, see kStreamMaxTokens).
+  // Up to 256 tokens most experts have one row tile and the weight loads are marked non-temporal
+  // (341 against 360 us at 180 tokens, 375 against 375 at 230, 424 against 411 at 300).
+  if (stream_tiles_apply(d, T)) {
+    using Tile = TileCfg<128, 256, 64, 3>;
+    if (T <= kMidMaxTokens) return fn(Path<Tile, Tile, true, true, false>{});
+    return fn(Path<Tile, Tile, true, false, false>{});
+  }
+  // Many narrow experts with few rows each (rows per expert: what an even spread of the picks over
+  // all experts would give).  256-row tiles are mostly padding there, and the narrow layers have
+  // items enough without a split.  Time of both GEMMs against the 256 x 256 tiles:
+  //   gate/up 128 x 256, down 128 x 128, 64-wide k-tiles: 60 experts, 4 picks, 4 shared, 333 tokens
+  //   (22 rows) 172 -> 148 us, 600 tokens 221 -> 179; 256 experts, 8 picks, 800 tokens 173 -> 158,
+  //   4096 (128 rows) 343 -> 325; 64 experts, 6 picks, 1500 tokens (141 rows) 273 -> 264; beyond,
+  //   the full tiles win (60 experts at 2500 tokens, 167 rows: 390 against 411).
+  //   64 x 128, weights non-temporal, up to 16 rows (an expert has one tile, its weights are read
+  //   once): 64 experts, 80 tokens 138 -> 107 us; 256 experts, 100 tokens 108 -> 81, 400 tokens
+  //   147 -> 116 (126 in the tiles above).  Shared experts take all tokens and read their weights
+  //   once per 64 rows: with 4 of them at 200 tokens the larger tiles are ahead, 128 against 140.
+  if (few_rows_per_expert(d, T)) {
+    if ((long long)T * d.top_k <= 16LL * d.n_experts && (long long)T * d.n_shared <= 512)
+      return fn(Path<TileCfg<64, 128, 64, 4>, TileCfg<64, 128, 64, 4>, false, true, false>{});
+    return fn(Path<TileCfg<128, 256, 64, 3>, TileCfg<128, 128, 64, 4>, false, false, false>{});
+  }
   // Prefill batch: 256 x 256 tiles (GEMM1: 128 gate + 128 up weight rows).  Very short
   // contractions (H or F of 64) get the shallowest ring.
   if (d.hidden >= 128 && d.ffn >= 128)
-    return fn(Path<TileCfg<256, 256, 32, 4>, TileCfg<256, 256, 32, 4>, false, false>{});
-  return fn(Path<TileCfg<256, 256, 32, 3>, TileCfg<256, 256, 32, 3>, false, false>{});
+    return fn(Path<TileCfg<256, 256, 32, 4>, TileCfg<256, 256, 32, 4>, false, false, false>{});
+  return fn(Path<TileCfg<256, 256, 32, 3>, TileCfg<256, 256, 32, 3>, false, false, false>{});
 }
 
 }  // namespace
@@ -293,29 +309,33 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
     return PRISM_ERR_UNSUPPORTED;
   return select_path(d, T, [&](auto path) {
     using P = decltype(path);
-    return run_bf16_ffn<typename P::C1, typename P::C2, P::kSplitDown, P::kStreamB>(
+    return run_bf16_ffn<typename P::C1, typename P::C2, P::kSplitDown, P::kStreamB, P::kRotate>(
         d, x, w, local_src, local_offsets, T, y, h, tiles, part, slice_part, st, stage_events, deferred_splits,
         schedules_built);
   });
 }
 
-// Batches between the decode and the prefill sizes of layers wide enough for the 6-stage ring,
-// if the down projection in prefill tiles would have too few items for the machine: column
-// tiles x row tiles, the latter estimated from what the host knows (half of the experts
-// hosted, rows spread evenly).  Layers of many small experts have enough items at any batch
-// size and run as fast or faster in prefill tiles (measured at E = 60 / 64 with 4 / 2 shared
-// experts: within 3 % up to 256 tokens, 5-18 % faster from 384).
+// Batches between the decode and the prefill sizes whose down projection in prefill tiles would
+// have too few items for the machine: column tiles x row tiles, the latter estimated from what the
+// host knows (half of the experts hosted, rows spread evenly).  Layers of many small experts have
+// enough items at any batch size.
 static bool stream_tiles_apply(const prism_layer_desc& d, int T) {
-  const int t_max = slicing_shape(d) ? kStreamMaxTokensSliced : kStreamMaxTokens;
-  if (T <= kDecodeMaxTokens || T > t_max || d.hidden < 256 || d.ffn < 1024) return false;
+  if (T <= kDecodeMaxTokens || T > kStreamMaxTokens || d.hidden < 256 || d.ffn < 1024) return false;
   const int row_tiles = ceil_div(T * d.top_k, 256) + d.n_experts / 2 + d.n_shared * ceil_div(T, 256);
   return row_tiles * ceil_div(d.hidden, 256) <= 128;
+}
+
+// The line at 144 rows per expert is measured on narrow layers (select_path); layers whose down
+// projection may cut its last round keep the prefill tiles, which the cut fills better.
+static bool few_rows_per_expert(const prism_layer_desc& d, int T) {
+  if (T <= kDecodeMaxTokens || d.hidden < 192 || d.ffn < 192 || slicing_shape(d)) return false;
+  return (long long)T * d.top_k <= 144LL * d.n_experts;
 }
 
 FfnShapes ffn_schedule_shapes(const prism_layer_desc& d, int T) {
   return select_path(d, T, [&](auto path) {
     using P = decltype(path);
-    return shapes_of<typename P::C1, typename P::C2, P::kSplitDown>(d, T);
+    return shapes_of<typename P::C1, typename P::C2, P::kSplitDown, P::kRotate>(d, T);
   });
 }
 

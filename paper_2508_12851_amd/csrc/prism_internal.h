@@ -37,7 +37,7 @@ constexpr int kDecodeSplits = 8;        // most contraction slices of its down p
 constexpr int kStreamSplits = 4;        // ... and of batches with more than kManySplitsRows rows that still split it
 constexpr int kManySplitsRows = 256;    // (every slice is one more fp32 copy of all rows)
 constexpr int kStreamMaxTokens = 512;   // wide bf16 layers: batches up to this size also split the down projection (expert_ffn.hip)
-constexpr int kMidMaxTokens = 256;      // ... and up to this size they run in 128 x 128 tiles (expert_ffn.hip)
+constexpr int kMidMaxTokens = 256;      // ... and up to this size with non-temporal weight loads (expert_ffn.hip)
 constexpr int kMinTileM = 64;           // smallest row tile of the grouped GEMM (bounds table sizes)
 constexpr int kRouteTokTile = 16;       // tokens per router tile
 constexpr int kRouteMaxHSplit = 16;     // hidden-dimension slices of the decode router
@@ -85,9 +85,8 @@ static inline size_t tile_table_ints(const prism_layer_desc& d, int T) {
 // (about 40 us); with fewer than 128 k-tiles (the gate/up GEMM of the same layers included, whose
 // contraction is H) it was measured to lose.
 constexpr int kSliceMinFfn = 4096;
-// With the cut available, prefill tiles beat the 128 x 256 streaming tiles of the mid-size batches
-// earlier (4096 x 14336 layer, 5 of 8 experts hosted: 0.503 against 0.492 ms at 320 tokens, 0.537
-// against 0.556 at 384, 0.564 against 0.629 at 512).
+// Batches beyond this size may take prefill tiles (layers with too many row tiles for the streaming
+// path, expert_ffn.hip); no smaller one needs the partial tiles.
 constexpr int kStreamMaxTokensSliced = 352;
 static inline bool slicing_shape(const prism_layer_desc& d) {
   return d.dtype == PRISM_BF16 && d.ffn >= kSliceMinFfn && d.hidden >= 128;

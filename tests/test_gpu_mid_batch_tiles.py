@@ -1,0 +1,36 @@
+"""GPU: batches between decode and prefill at the lines of the rules that choose their tiles (rows per expert, rows
+of the shared experts, token limits of the split down projection) and at the edges of those tiles, against the oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,H,F,E,k,S,hosted", [
+    (65, 256, 1024, 4, 2, 0, 3),       # split down projection: fewest tokens, shortest contractions
+    (256, 320, 1088, 4, 2, 1, 4),      # ragged columns, last size with non-temporal weights
+    (257, 320, 1088, 4, 4, 0, 4),      # every expert 257 rows: a third row tile of one row
+    (512, 256, 1024, 8, 2, 1, 5),      # last split size
+    (513, 256, 1024, 8, 2, 1, 5),
+    (360, 256, 4096, 8, 2, 0, 5),      # a contraction long enough for the cut, not cut any more
+    (384, 192, 192, 48, 2, 0, 40),     # 16 rows per expert, shortest ring
+    (385, 192, 192, 48, 2, 0, 40),     # one pick over it
+    (128, 192, 704, 32, 4, 4, 20),     # 512 shared rows
+    (129, 192, 704, 32, 4, 4, 20),     # 516
+    (1152, 320, 448, 24, 3, 0, 24),    # 144 rows per expert
+    (1153, 320, 448, 24, 3, 1, 24),
+    (128, 192, 320, 2, 2, 1, 2),       # full 128-row tiles
+    (129, 192, 320, 2, 2, 1, 1),       # and one row more
+    (70, 128, 192, 64, 2, 0, 64),      # contraction below the rings': prefill tiles
+])
+def test_mid_batch_tiles(T, H, F, E, k, S, hosted):
+    from gpu_util import check_layer, oracle_layer, run_layer, weight_table
+    from prism_inputs import make_config, make_inputs
+    cfg = make_config("cfg4_finegrained", T=T, H=H, F=F, E=E, k=k, S=S, bias_group_tokens=0)
+    mask = np.zeros(E, np.uint8)
+    mask[np.random.default_rng([T, E]).permutation(E)[:hosted]] = 1
+    inp = make_inputs(cfg)
+    ref = oracle_layer(inp, mask)
+    for layout in ("row_major", "tiled"):
+        check_layer(cfg, run_layer(cfg, inp, mask, weight_table(inp, mask, tiled=layout == "tiled"),
+                                   weight_layout=layout), ref)
