@@ -33,9 +33,9 @@ static prism_status check_workspace(const prism_layer_desc& d, int T, void* ws, 
                                     Workspace* out) {
   PRISM_RETURN_IF(ws == nullptr, PRISM_ERR_INVALID_ARG);
   PRISM_RETURN_IF(((uintptr_t)ws & 255u) != 0, PRISM_ERR_INVALID_ARG);
-  const Workspace probe = carve(d, T, nullptr);
-  PRISM_RETURN_IF(ws_bytes < probe.total, PRISM_ERR_WORKSPACE_TOO_SMALL);
-  *out = carve(d, T, ws);
+  const bool tiled_h = ws_bytes >= carve(d, T, nullptr).total;
+  PRISM_RETURN_IF(ws_bytes < carve(d, T, nullptr, tiled_h).total, PRISM_ERR_WORKSPACE_TOO_SMALL);
+  *out = carve(d, T, ws, tiled_h);
   return PRISM_OK;
 }
 
@@ -146,7 +146,7 @@ prism_status prism_expert_ffn(const prism_layer_desc* desc, const void* x,
   if (T > 0) PRISM_RETURN_IF(x == nullptr || local_src == nullptr || y == nullptr, PRISM_ERR_INVALID_ARG);
   Workspace ws;
   PRISM_TRY(check_workspace(*desc, T, workspace, workspace_bytes, &ws));
-  return launch_expert_ffn(*desc, x, *weights, local_src, local_offsets, T, y, ws.h, ws.tiles,
+  return launch_expert_ffn(*desc, x, *weights, local_src, local_offsets, T, y, ws.h, ws.h_tiled, ws.tiles,
                            ws.part, ws.slice_part, (hipStream_t)stream, nullptr, nullptr);
 }
 
@@ -263,7 +263,7 @@ prism_status prism_moe_layer_traced(const prism_layer_desc* desc, const void* x,
                                       ws.local_offsets, remote_src, remote_offsets, n_local_remote,
                                       remote_bytes, ws.inv, ws.route_part, ws.tiles, st, ev));
     PRISM_TRY(launch_expert_ffn(*desc, x, *weights, ws.local_src, ws.local_offsets, T, ws.y, ws.h,
-                                ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, true));
+                                ws.h_tiled, ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, true));
   } else if (SplitRoutePlan plan;
              // h and y lie side by side and are written by the GEMMs only
              plan_split_route(*desc, T, ws.h, (size_t)((char*)ws.part - (char*)ws.h), &plan)) {
@@ -276,7 +276,7 @@ prism_status prism_moe_layer_traced(const prism_layer_desc* desc, const void* x,
                                    counts_accum, st, ws.tiles));
     trace(ev, PRISM_STAGE_DISPATCH, 1, st);
     PRISM_TRY(launch_expert_ffn(*desc, x, *weights, ws.local_src, ws.local_offsets, T, ws.y, ws.h,
-                                ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, true));
+                                ws.h_tiled, ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, true));
   } else {
     trace(ev, PRISM_STAGE_ROUTE, 0, st);
     // the activation counts come out of the dispatch histogram, not out of the router
@@ -290,7 +290,7 @@ prism_status prism_moe_layer_traced(const prism_layer_desc* desc, const void* x,
                               ws.block_hist, counts, counts_accum, st, ws.tiles, &schedules_built));
     trace(ev, PRISM_STAGE_DISPATCH, 1, st);
     PRISM_TRY(launch_expert_ffn(*desc, x, *weights, ws.local_src, ws.local_offsets, T, ws.y, ws.h,
-                                ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, schedules_built));
+                                ws.h_tiled, ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, schedules_built));
   }
   trace(ev, PRISM_STAGE_COMBINE, 0, st);
   PRISM_TRY(launch_combine(*desc, ws.y, ws.inv, topk_gate, T, out, st, ws.part, n_splits));
@@ -340,7 +340,7 @@ prism_status prism_moe_layer_static(const prism_layer_desc* desc, const void* x,
   PRISM_ENTER();
   PRISM_TRY(validate_desc(desc, T, true));
   // the same layout the caller's workspace would have; it has to fit the fixed array
-  PRISM_RETURN_IF(carve(*desc, T, nullptr).total > kStaticScratchBytes, PRISM_ERR_WORKSPACE_TOO_SMALL);
+  PRISM_RETURN_IF(carve(*desc, T, nullptr, false).total > kStaticScratchBytes, PRISM_ERR_WORKSPACE_TOO_SMALL);
   void* ws = nullptr;
   PRISM_TRY(static_scratch(&ws));
   return prism_moe_layer_traced(desc, x, w_router, router_bias, weights, local_mask, T, out, topk_idx,

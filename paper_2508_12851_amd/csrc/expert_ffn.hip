@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const int32_t* __restri
 template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B, bool ROTATE>
 prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_expert_weights& w,
                           const int32_t* local_src, const int32_t* local_offsets, int T, void* y,
-                          void* h, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
+                          void* h, bool h_tiled, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
                           void* const* stage_events, const int32_t** deferred_splits,
                           bool schedules_built) {
   using gg::GemmArgs;
@@ -173,6 +173,7 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   g1.b_bytes = (uint32_t)((size_t)d.ffn * d.hidden * 2);
   g1.K = d.hidden; g1.N = d.ffn; g1.top_k = d.top_k; g1.E = d.n_experts;
   g1.b_tiled = d.weight_layout == PRISM_WEIGHTS_TILED;
+  g1.h_tiled = h_tiled;
   trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
   PRISM_TRY((gg::launch_gemm<C1::BM, C1::BN, 2, 2, C1::BK, C1::STAGES, true, false, ROTATE, STREAM_B>(
       g1, gg::sched_capacity(d, T, C1::BM, nt1), st)));
@@ -184,10 +185,11 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   g2.C = (uint16_t*)y;
   g2.Cpart = SPLIT_DOWN ? part : slice_part; g2.c_rows = rows;
   g2.sched = sched2; g2.local_src = local_src;
-  g2.a_bytes = (uint32_t)((size_t)rows * d.ffn * 2);
+  g2.a_bytes = (uint32_t)((h_tiled ? align_up(rows, 16) : (size_t)rows) * d.ffn * 2);
   g2.b_bytes = (uint32_t)((size_t)d.ffn * d.hidden * 2);
   g2.K = d.ffn; g2.N = d.hidden; g2.top_k = d.top_k; g2.E = d.n_experts;
   g2.b_tiled = d.weight_layout == PRISM_WEIGHTS_TILED;
+  g2.h_tiled = h_tiled;
   // SPLIT_DOWN: the number of contraction slices is in the schedule's header (schedule.h, "Splits")
   const int32_t* n_splits = sched2 + 2;
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 0, st);
@@ -292,7 +294,7 @@ auto select_path(const prism_layer_desc& d, int T, Fn&& fn) {
 prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
                                const prism_expert_weights& w, const int32_t* local_src,
                                const int32_t* local_offsets, int T, void* y, void* h,
-                               int32_t* tiles, float* part, float* slice_part, hipStream_t st,
+                               bool h_tiled, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
                                void* const* stage_events, const int32_t** deferred_splits,
                                bool schedules_built) {
   if (deferred_splits != nullptr) *deferred_splits = nullptr;
@@ -307,10 +309,11 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
   if ((size_t)T * d.hidden * 2 >= kMaxOperandBytes || (size_t)rows * d.ffn * 2 >= kMaxOperandBytes ||
       (size_t)d.ffn * d.hidden * 2 >= kMaxOperandBytes)
     return PRISM_ERR_UNSUPPORTED;
+  if (align_up(rows, 16) * d.ffn * 2 >= kMaxOperandBytes) h_tiled = false;   // (the buffer holds the plain rows too)
   return select_path(d, T, [&](auto path) {
     using P = decltype(path);
     return run_bf16_ffn<typename P::C1, typename P::C2, P::kSplitDown, P::kStreamB, P::kRotate>(
-        d, x, w, local_src, local_offsets, T, y, h, tiles, part, slice_part, st, stage_events, deferred_splits,
+        d, x, w, local_src, local_offsets, T, y, h, h_tiled, tiles, part, slice_part, st, stage_events, deferred_splits,
         schedules_built);
   });
 }

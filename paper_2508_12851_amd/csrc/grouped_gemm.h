@@ -67,8 +67,17 @@ struct GemmArgs {
   int top_k;
   int E;
   int b_tiled;              // weights in 16 x 32 tiles (prism.h) instead of row-major
+  int h_tiled;              // h (C of the GATED GEMM, A of the plain one) in the same tiles ("Intermediate" below)
 };
 
+// Intermediate.  h is written by one of the two GEMMs and read by the other, so it lies in the order
+// that serves both: 16 x 32 tiles of 1 KiB over the absolute row number, like packed weights.  The
+// down projection then fetches its activation k-tiles as whole cache lines (a row-major row gives
+// 64 bytes per 32-wide k-tile, half a line, and the L2 is asked for the other half again in the next
+// one), and a store instruction of the gate/up epilogue covers 32 pieces of 16 bytes that the next
+// three complete to a contiguous 2 KiB instead of lines whole rows apart.  Down projection, row-major
+// before: 4096 tokens of the 4096 x 14336 layer 716 -> 643 us, 8192 of the 60-expert layer 306 -> 293,
+// 2500 of the 64-expert one 122 -> 117; 64-wide k-tiles took whole lines already and gain 0 to 2 %.
 constexpr int kGemmThreads = 256;
 
 // Epilogue strips: 32 rows x 64 bf16 columns per wavefront at a row pitch of 144 bytes
@@ -296,7 +305,8 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
       // Rows past the end of a partly filled tile get an offset beyond the buffer: the
       // hardware then returns zeros, and all-zero operands cost the matrix cores far
       // less power than real data (the chip is power-limited in this kernel).
-      cx.a_voff[i] = lrow + 4 * RPG * i < it.row_count ? (src * (uint32_t)p.K + c * 8) * 2 : kOutOfRange;
+      const uint32_t off = !GATED && p.h_tiled ? tiled_offset(src, (uint32_t)p.K) : (src * (uint32_t)p.K + c * 8) * 2;
+      cx.a_voff[i] = lrow + 4 * RPG * i < it.row_count ? off : kOutOfRange;
     }
 #pragma unroll
     for (int i = 0; i < B_CH; ++i) {
@@ -326,7 +336,9 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
     }
     const int kel = (kt_first + (SLICES ? cx.kt0 : 0) + kt_mem) * BK;   // first contraction element
     const int koff = kel * 2;
-    const int koff_b = p.b_tiled ? (kel >> 5) * 1024 : koff;   // kel is a multiple of 32
+    const int koff_tiled = (kel >> 5) * 1024;   // kel is a multiple of 32
+    const int koff_b = p.b_tiled ? koff_tiled : koff;
+    const int koff_a = !GATED && p.h_tiled ? koff_tiled : koff;
     const __amdgpu_buffer_rsrc_t b0_rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)cx.b0, 0, (int)p.b_bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t b1_rsrc =
@@ -335,7 +347,7 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
     for (int i = 0; i < A_CH; ++i)
       if (i >= first && i < last)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_ptr_t)(base + i * 4 * RPG * kRowBytes),
-                                                 16, cx.a_voff[i], koff, 0, 0);
+                                                 16, cx.a_voff[i], koff_a, 0, 0);
 #pragma unroll
     for (int i = 0; i < B_CH; ++i)
       if (A_CH + i >= first && A_CH + i < last) {
@@ -551,17 +563,21 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
       const size_t crow = (size_t)(cx.row_start + row);
       if (GATED) {
         constexpr int NH = NJ / 2;
+        const int f0 = cx.nt * (BN / 2) + wn * (WN / 2);       // a multiple of 32
+        uint16_t* const out = p.C + (p.h_tiled ? (crow >> 4) * (size_t)(p.N >> 5) * 512 + (size_t)(f0 >> 5) * 512 +
+                                                     (crow & 15) * 32
+                                               : crow * p.N + f0) + q * 4;
+        const int col_step = p.h_tiled ? 512 : 32;             // elements from one column subtile to the next
 #pragma unroll
         for (int j = 0; j < NH; ++j)
 #pragma unroll
           for (int vg = 0; vg < 4; ++vg) {
-            const int f = cx.nt * (BN / 2) + wn * (WN / 2) + j * 32 + vg * 8 + q * 4;
-            if (f < p.N) {
+            if (f0 + j * 32 + vg * 8 + q * 4 < p.N) {
               bf16x4 o;
 #pragma unroll
               for (int e = 0; e < 4; ++e)
                 o[e] = (bf16_t)(silu(acc[i][j][vg * 4 + e]) * acc[i][j + NH][vg * 4 + e]);
-              *reinterpret_cast<bf16x4*>(p.C + crow * p.N + f) = o;
+              *reinterpret_cast<bf16x4*>(out + j * col_step + vg * 8) = o;
             }
           }
       } else {

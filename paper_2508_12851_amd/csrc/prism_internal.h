@@ -48,11 +48,12 @@ struct Workspace {
   int32_t* inv;            // [A]  row of assignment a in y, or -1 when remote
   int32_t* block_hist;     // [n_chunks * E]
   int32_t* tiles;          // 2 x [tile_table_ints]: schedules of the two grouped GEMMs
-  void* h;                 // [(A + S*T) * F] layer dtype: silu(gate)*up
+  void* h;                 // [(A + S*T) * F] layer dtype: silu(gate)*up; bf16: rows rounded up to 16 if h_tiled
   void* y;                 // [(A + S*T) * H] layer dtype: expert outputs
   float* part;             // batches up to kStreamMaxTokens: [max_splits(T)][A + S*T][H] fp32 partial sums
   float* slice_part;       // larger batches of wide layers: 256 partial tiles of 256 x 256 fp32 (cut last round of the down projection)
   double* route_part;      // decode batches: [token tiles][kRouteMaxHSplit][route_col_tiles][64][4] fp64
+  bool h_tiled;            // h in 16 x 32 tiles (grouped_gemm.h, "Intermediate")
   size_t total;
 };
 
@@ -103,8 +104,12 @@ static inline int max_splits(const prism_layer_desc& d, int T) {
   return (long long)T * (d.top_k + d.n_shared) <= kManySplitsRows ? kDecodeSplits : kStreamSplits;
 }
 
-static inline Workspace carve(const prism_layer_desc& d, int T, void* base) {
+// tiled_h: h of bf16 layers in 16 x 32 tiles, which takes up to 15 more rows.  That is the layout
+// prism_workspace_bytes() asks for; a buffer with room for the plain rows alone is served as well,
+// with h row-major.
+static inline Workspace carve(const prism_layer_desc& d, int T, void* base, bool tiled_h = true) {
   Workspace w;
+  w.h_tiled = tiled_h && d.dtype == PRISM_BF16;
   const size_t A = (size_t)T * d.top_k;
   const size_t rows = A + (size_t)d.n_shared * T;
   const size_t es = elem_size(d.dtype);
@@ -117,7 +122,7 @@ static inline Workspace carve(const prism_layer_desc& d, int T, void* base) {
   w.inv = (int32_t*)take(A * 4);
   w.block_hist = (int32_t*)take((size_t)n_chunks * d.n_experts * 4);
   w.tiles = (int32_t*)take(2 * tile_table_ints(d, T) * 4);
-  w.h = take(rows * d.ffn * es);
+  w.h = take((w.h_tiled ? align_up(rows, 16) : rows) * d.ffn * es);
   w.y = take(rows * d.hidden * es);
   // The regions of the small-batch paths are reserved for every T (sized for min(T, limit of
   // the path) tokens), so that the total never shrinks as T grows: a workspace sized for
@@ -213,6 +218,7 @@ prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk
                                   int64_t* counts_accum, hipStream_t st, int32_t* tiles);
 
 // schedules_built: the two schedules in tiles already exist (decode front end).
+// h_tiled: layout of h (Workspace).
 // slice_part: scratch for a cut last round of the down projection (slice_part_bytes).
 // deferred_splits NULL: y holds the finished expert outputs.  Otherwise the paths that split the
 // down projection's contraction leave it as fp32 slices in part, y unwritten, for launch_combine
@@ -221,7 +227,7 @@ prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk
 prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
                                const prism_expert_weights& w, const int32_t* local_src,
                                const int32_t* local_offsets, int T, void* y, void* h,
-                               int32_t* tiles, float* part, float* slice_part, hipStream_t st,
+                               bool h_tiled, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
                                void* const* stage_events, const int32_t** deferred_splits,
                                bool schedules_built = false);
 
