@@ -257,16 +257,9 @@ prism_status prism_moe_layer_traced(const prism_layer_desc* desc, const void* x,
   const hipStream_t st = (hipStream_t)stream;
   void* const* ev = stage_events;
   const int32_t* n_splits = nullptr;   // set if the down projection is left as contraction slices
-  if (decode_front_end_applies(*desc, T)) {
-    PRISM_TRY(launch_decode_front_end(*desc, x, w_router, router_bias, local_mask, T, topk_idx,
-                                      topk_gate, counts, counts_accum, ws.local_src,
-                                      ws.local_offsets, remote_src, remote_offsets, n_local_remote,
-                                      remote_bytes, ws.inv, ws.route_part, ws.tiles, st, ev));
-    PRISM_TRY(launch_expert_ffn(*desc, x, *weights, ws.local_src, ws.local_offsets, T, ws.y, ws.h,
-                                ws.h_tiled, ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, true));
-  } else if (SplitRoutePlan plan;
-             // h and y lie side by side and are written by the GEMMs only
-             plan_split_route(*desc, T, ws.h, (size_t)((char*)ws.part - (char*)ws.h), &plan)) {
+  if (SplitRoutePlan plan;
+      // h and y lie side by side and are written by the GEMMs only
+      plan_split_route(*desc, T, ws.h, (size_t)((char*)ws.part - (char*)ws.h), &plan)) {
     trace(ev, PRISM_STAGE_ROUTE, 0, st);
     PRISM_TRY(launch_split_route(*desc, x, w_router, router_bias, T, topk_idx, topk_gate, plan, st));
     trace(ev, PRISM_STAGE_ROUTE, 1, st);
@@ -275,6 +268,13 @@ prism_status prism_moe_layer_traced(const prism_layer_desc* desc, const void* x,
                                    remote_offsets, n_local_remote, remote_bytes, ws.inv, plan, counts,
                                    counts_accum, st, ws.tiles));
     trace(ev, PRISM_STAGE_DISPATCH, 1, st);
+    PRISM_TRY(launch_expert_ffn(*desc, x, *weights, ws.local_src, ws.local_offsets, T, ws.y, ws.h,
+                                ws.h_tiled, ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, true));
+  } else if (decode_front_end_applies(*desc, T)) {
+    PRISM_TRY(launch_decode_front_end(*desc, x, w_router, router_bias, local_mask, T, topk_idx,
+                                      topk_gate, counts, counts_accum, ws.local_src,
+                                      ws.local_offsets, remote_src, remote_offsets, n_local_remote,
+                                      remote_bytes, ws.inv, ws.route_part, ws.tiles, st, ev));
     PRISM_TRY(launch_expert_ffn(*desc, x, *weights, ws.local_src, ws.local_offsets, T, ws.y, ws.h,
                                 ws.h_tiled, ws.tiles, ws.part, ws.slice_part, st, ev, &n_splits, true));
   } else {

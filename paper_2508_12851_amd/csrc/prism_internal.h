@@ -195,7 +195,7 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
                              hipStream_t st, int32_t* tiles = nullptr,
                              bool* schedules_built = nullptr);
 
-// bf16 batches of more than 64 tokens inside the whole layer: the router as two launches.  The
+// bf16 batches inside the whole layer (all but decode batches of few experts): the router as two launches.  The
 // first spreads (token tile, experts, hidden elements) over the chip and leaves fp64 partial
 // logits, the second sums them, picks the experts and counts them per block of assignments.
 struct SplitRoutePlan {

@@ -836,7 +836,12 @@ prism_status launch_route(const prism_layer_desc& d, const void* x, const void* 
 }
 
 bool plan_split_route(const prism_layer_desc& d, int T, void* scratch, size_t scratch_bytes, SplitRoutePlan* plan) {
-  if (d.dtype != PRISM_BF16 || T <= kDecodeMaxTokens || (uint64_t)T * d.hidden * 2 >= 0xFFFF0000ull) return false;
+  // Decode batches of at most 16 experts: the two launches of the decode front end are as good as the
+  // three of this one (32 tokens x 8 experts: layer 300 against 299 us).  Beyond, its one workgroup
+  // takes long over the slice sums and the picks of every token (layer, 24 tokens x 64 experts 112
+  // against 105 us, 64 x 60: 119 against 107, 1 x 64: 53 against 48, 64 x 256: 153 against 94).
+  if (T <= kDecodeMaxTokens && d.n_experts <= 16) return false;
+  if (d.dtype != PRISM_BF16 || T <= 0 || (uint64_t)T * d.hidden * 2 >= 0xFFFF0000ull) return false;
   // With 32-token workgroups for three quarters of the CUs the router in one launch is as good
   // (8192 tokens x 60 experts: 51 us with its histogram launch of 5, split 52 + 6 us, and the
   // layer 1 % slower).

@@ -16,6 +16,10 @@ pytestmark = pytest.mark.gpu
     (700, 1024, 129, 7),     # 9 of 16 expert tiles
     (300, 256, 256, 5),
     (5000, 64, 16, 2),
+    (1, 256, 17, 1),         # decode batches: fewest experts, one token
+    (24, 2048, 64, 6),
+    (64, 192, 256, 8),
+    (3, 64, 256, 1),         # partial logits too large: decode front end
 ])
 @pytest.mark.parametrize("gates", ["renormalized", "softmax_all"])
 def test_split_router_in_layer(T, H, E, k, gates):
