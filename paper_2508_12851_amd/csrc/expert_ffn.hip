@@ -134,10 +134,45 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const int32_t* __restri
   }
 }
 
+// Prefill batches of wide layers: the token of every row the gate/up GEMM multiplies, copied into
+// 16 x 32 tiles in row order, so that the GEMM fetches its 32-wide activation k-tiles as whole cache
+// lines instead of half a line of each gathered row (grouped_gemm.h, "Intermediate").
+// Bound: HBM, 4 H bytes per row.  4096 tokens of the 4096 x 14336 layer: gate/up with the copy 1341
+// us against 1411 gathered (row-major weights 1386 against 1457), 1000 tokens 395 against 410, 600
+// tokens 380 against 382.  A wavefront takes 16 rows x 256 columns.
+__global__ __launch_bounds__(256) void pack_tokens_kernel(const uint4* __restrict__ x,
+                                                          const int32_t* __restrict__ local_src,
+                                                          const int32_t* __restrict__ local_offsets, int E, int A,
+                                                          int rows, int T, int top_k, int H, uint4* __restrict__ out,
+                                                          int32_t* __restrict__ row_places) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * 16 + (lane >> 2);
+  if (r >= rows || (r >= local_offsets[E] && r < A)) return;   // rows that hold no assignment
+  const int tok = r < A ? local_src[r] / top_k : (r - A) % T;
+  if (blockIdx.y == 0 && threadIdx.x < 64 && (lane & 3) == 0) row_places[r] = blockIdx.x * (H / 32) * 16 + (lane >> 2);
+  const int tiles = H / 32, tile0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 8;
+  const uint4* src = x + (size_t)tok * (H / 8) + (lane & 3);
+  uint4* dst = out + (size_t)blockIdx.x * tiles * 64 + lane;
+  uint4 v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = src[min(tile0 + j, tiles - 1) * 4];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (tile0 + j < tiles) dst[(tile0 + j) * 64] = v[j];
+}
+// The copy costs 4 H bytes of traffic per row, what it saves grows with the 4 H F operations of the
+// row's gate/up products: layers as wide as those whose down projection cuts its last round.
+static inline bool pack_rows_pays(const prism_layer_desc& d, int T) {
+  const size_t rows = (size_t)T * (d.top_k + d.n_shared);
+  // (the places lie behind the rows, in the partial sums' region: four fp32 rows per token and more)
+  return slicing_shape(d) && T > kStreamMaxTokens && T <= 512 * d.hidden && align_up(rows, 16) * d.hidden * 2 < 0xFFFF0000ull;
+}
+
 template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B, bool ROTATE>
 prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_expert_weights& w,
                           const int32_t* local_src, const int32_t* local_offsets, int T, void* y,
-                          void* h, bool h_tiled, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
+                          void* h, bool h_tiled, void* x_rows, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
                           void* const* stage_events, const int32_t** deferred_splits,
                           bool schedules_built) {
   using gg::GemmArgs;
@@ -173,8 +208,25 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   g1.b_bytes = (uint32_t)((size_t)d.ffn * d.hidden * 2);
   g1.K = d.hidden; g1.N = d.ffn; g1.top_k = d.top_k; g1.E = d.n_experts;
   g1.b_tiled = d.weight_layout == PRISM_WEIGHTS_TILED;
-  g1.h_tiled = h_tiled;
+  g1.c_tiled = h_tiled;
+  g1.a_pitch = (uint32_t)d.hidden * 2;
+  g1.a_kstep = 64;
   trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
+  if (kCanSlice && pack_rows_pays(d, T)) {
+    int32_t* row_places = (int32_t*)((uint8_t*)x_rows + align_up(rows, 16) * d.hidden * 2);
+    hipLaunchKernelGGL(pack_tokens_kernel, dim3((unsigned)ceil_div(rows, 16), (unsigned)ceil_div(d.hidden, 1024)),
+                       dim3(256), 0, st, (const uint4*)x, local_src, local_offsets, d.n_experts, A, rows, T, d.top_k,
+                       d.hidden, (uint4*)x_rows, row_places);
+    PRISM_CHECK_LAUNCH();
+    g1.A = (const uint16_t*)x_rows;
+    g1.a_bytes = (uint32_t)(align_up(rows, 16) * d.hidden * 2);
+    g1.a_tiled = 1;
+    g1.local_src = row_places;
+    g1.src_bytes = (uint32_t)rows * 4;
+    g1.top_k = 1;
+    g1.a_pitch = 64;
+    g1.a_kstep = 1024;
+  }
   PRISM_TRY((gg::launch_gemm<C1::BM, C1::BN, 2, 2, C1::BK, C1::STAGES, true, false, ROTATE, STREAM_B>(
       g1, gg::sched_capacity(d, T, C1::BM, nt1), st)));
   trace(stage_events, PRISM_STAGE_FFN_UP, 1, st);
@@ -189,7 +241,9 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   g2.b_bytes = (uint32_t)((size_t)d.ffn * d.hidden * 2);
   g2.K = d.ffn; g2.N = d.hidden; g2.top_k = d.top_k; g2.E = d.n_experts;
   g2.b_tiled = d.weight_layout == PRISM_WEIGHTS_TILED;
-  g2.h_tiled = h_tiled;
+  g2.a_tiled = h_tiled;
+  g2.a_pitch = (uint32_t)d.ffn * 2;
+  g2.a_kstep = h_tiled ? 1024 : 64;
   // SPLIT_DOWN: the number of contraction slices is in the schedule's header (schedule.h, "Splits")
   const int32_t* n_splits = sched2 + 2;
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 0, st);
@@ -294,7 +348,7 @@ auto select_path(const prism_layer_desc& d, int T, Fn&& fn) {
 prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
                                const prism_expert_weights& w, const int32_t* local_src,
                                const int32_t* local_offsets, int T, void* y, void* h,
-                               bool h_tiled, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
+                               bool h_tiled, void* x_rows, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
                                void* const* stage_events, const int32_t** deferred_splits,
                                bool schedules_built) {
   if (deferred_splits != nullptr) *deferred_splits = nullptr;
@@ -313,7 +367,7 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
   return select_path(d, T, [&](auto path) {
     using P = decltype(path);
     return run_bf16_ffn<typename P::C1, typename P::C2, P::kSplitDown, P::kStreamB, P::kRotate>(
-        d, x, w, local_src, local_offsets, T, y, h, h_tiled, tiles, part, slice_part, st, stage_events, deferred_splits,
+        d, x, w, local_src, local_offsets, T, y, h, h_tiled, x_rows, tiles, part, slice_part, st, stage_events, deferred_splits,
         schedules_built);
   });
 }

@@ -67,7 +67,11 @@ struct GemmArgs {
   int top_k;
   int E;
   int b_tiled;              // weights in 16 x 32 tiles (prism.h) instead of row-major
-  int h_tiled;              // h (C of the GATED GEMM, A of the plain one) in the same tiles ("Intermediate" below)
+  int a_tiled;              // A in the same tiles.  GATED: A is the packed copy of x, and local_src holds, for every
+                            // output row, the place of its first 32 elements in 64-byte units (top_k is 1)
+  uint32_t a_pitch;         // bytes from one source row of A to the next (GATED and a_tiled: 64)
+  int a_kstep;              // bytes from 32 contraction elements of a row of A to the next 32
+  int c_tiled;              // GATED: h is written in the same tiles ("Intermediate" below)
 };
 
 // Intermediate.  h is written by one of the two GEMMs and read by the other, so it lies in the order
@@ -273,7 +277,7 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
     if (GATED)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           src_rsrc, (lds_ptr_t)src_lds, 16,
-          it.tok_base >= 0 ? kOutOfRange : (uint32_t)it.row_start * 4u + (uint32_t)lane * 16u, 0, 0, 0);
+          it.tok_base >= 0 && !p.a_tiled ? kOutOfRange : (uint32_t)it.row_start * 4u + (uint32_t)lane * 16u, 0, 0, 0);
     return r;
   };
   // Byte offset of this lane's 16-byte chunk c of weight row n in k-tile 0 (the k-tile offset
@@ -298,14 +302,15 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
       uint32_t src;
       if (GATED) {
         const int a = reinterpret_cast<const int*>(src_lds)[rr];
-        src = it.tok_base >= 0 ? (uint32_t)(it.tok_base + rr) : (uint32_t)(a / p.top_k);
+        src = it.tok_base >= 0 && !p.a_tiled ? (uint32_t)(it.tok_base + rr) : (uint32_t)(a / p.top_k);
       } else {
         src = (uint32_t)(it.row_start + rr);
       }
       // Rows past the end of a partly filled tile get an offset beyond the buffer: the
       // hardware then returns zeros, and all-zero operands cost the matrix cores far
       // less power than real data (the chip is power-limited in this kernel).
-      const uint32_t off = !GATED && p.h_tiled ? tiled_offset(src, (uint32_t)p.K) : (src * (uint32_t)p.K + c * 8) * 2;
+      const uint32_t off = !GATED && p.a_tiled ? tiled_offset(src, (uint32_t)p.K)
+                                               : src * p.a_pitch + c * 16;
       cx.a_voff[i] = lrow + 4 * RPG * i < it.row_count ? off : kOutOfRange;
     }
 #pragma unroll
@@ -338,7 +343,7 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
     const int koff = kel * 2;
     const int koff_tiled = (kel >> 5) * 1024;   // kel is a multiple of 32
     const int koff_b = p.b_tiled ? koff_tiled : koff;
-    const int koff_a = !GATED && p.h_tiled ? koff_tiled : koff;
+    const int koff_a = (kel >> 5) * p.a_kstep;
     const __amdgpu_buffer_rsrc_t b0_rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)cx.b0, 0, (int)p.b_bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t b1_rsrc =
@@ -564,10 +569,10 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
       if (GATED) {
         constexpr int NH = NJ / 2;
         const int f0 = cx.nt * (BN / 2) + wn * (WN / 2);       // a multiple of 32
-        uint16_t* const out = p.C + (p.h_tiled ? (crow >> 4) * (size_t)(p.N >> 5) * 512 + (size_t)(f0 >> 5) * 512 +
+        uint16_t* const out = p.C + (p.c_tiled ? (crow >> 4) * (size_t)(p.N >> 5) * 512 + (size_t)(f0 >> 5) * 512 +
                                                      (crow & 15) * 32
                                                : crow * p.N + f0) + q * 4;
-        const int col_step = p.h_tiled ? 512 : 32;             // elements from one column subtile to the next
+        const int col_step = p.c_tiled ? 512 : 32;             // elements from one column subtile to the next
 #pragma unroll
         for (int j = 0; j < NH; ++j)
 #pragma unroll

@@ -219,6 +219,8 @@ prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk
 
 // schedules_built: the two schedules in tiles already exist (decode front end).
 // h_tiled: layout of h (Workspace).
+// x_rows: the workspace's y (which may be the y given).  Batches of more than kStreamMaxTokens may keep a copy
+// of the token rows there, and at the start of the partial sums behind it, until the gate/up GEMM is done.
 // slice_part: scratch for a cut last round of the down projection (slice_part_bytes).
 // deferred_splits NULL: y holds the finished expert outputs.  Otherwise the paths that split the
 // down projection's contraction leave it as fp32 slices in part, y unwritten, for launch_combine
@@ -227,7 +229,7 @@ prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk
 prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
                                const prism_expert_weights& w, const int32_t* local_src,
                                const int32_t* local_offsets, int T, void* y, void* h,
-                               bool h_tiled, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
+                               bool h_tiled, void* x_rows, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
                                void* const* stage_events, const int32_t** deferred_splits,
                                bool schedules_built = false);
 
