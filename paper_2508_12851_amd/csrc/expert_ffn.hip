@@ -161,12 +161,15 @@ __global__ __launch_bounds__(256) void pack_tokens_kernel(const uint4* __restric
   for (int j = 0; j < 8; ++j)
     if (tile0 + j < tiles) dst[(tile0 + j) * 64] = v[j];
 }
-// The copy costs 4 H bytes of traffic per row, what it saves grows with the 4 H F operations of the
-// row's gate/up products: layers as wide as those whose down projection cuts its last round.
+// The copy costs 4 H bytes of traffic per row and a launch; what it saves grows with the 4 H F
+// operations of the row's gate/up products.  Layers whose down projection may cut its last round, from
+// 2.2e10 elements of rows x H x F on (layer with the copy against without: 600 tokens, 2 picks, of
+// 3072 x 6144, 2.3e10, 216 against 231 us; of 1024 x 14336, 1.8e10, 184 / 178; of 2048 x 8192, 2.0e10, 192 / 190).
 static inline bool pack_rows_pays(const prism_layer_desc& d, int T) {
   const size_t rows = (size_t)T * (d.top_k + d.n_shared);
   // (the places lie behind the rows, in the partial sums' region: four fp32 rows per token and more)
-  return slicing_shape(d) && T > kStreamMaxTokens && T <= 512 * d.hidden && align_up(rows, 16) * d.hidden * 2 < 0xFFFF0000ull;
+  return slicing_shape(d) && T > kStreamMaxTokens && T <= 512 * d.hidden &&
+         rows * d.hidden * d.ffn >= (size_t)22000000000 && align_up(rows, 16) * d.hidden * 2 < 0xFFFF0000ull;
 }
 
 template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B, bool ROTATE>
@@ -315,6 +318,17 @@ auto select_path(const prism_layer_desc& d, int T, Fn&& fn) {
   // even at 1024 tokens (between 512 and there: not split here, see kStreamMaxTokens).
   // Up to 256 tokens most experts have one row tile and the weight loads are marked non-temporal
   // (341 against 360 us at 180 tokens, 375 against 375 at 230, 424 against 411 at 300).
+  // With few output columns (H up to 2560) the wide tiles make too few items for the machine, in the
+  // down projection above all: 128 x 128 there (5 of 8 experts, layer: 1024 x 14336, 130 tokens 128
+  // against 141 us, 300: 143 / 157; 2048 x 4096, 80: 67 / 71; 3 experts of 1024 x 4096, 220: 44 / 55; at
+  // H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).  Long rows of F >= 8 H hold mostly
+  // gate/up weights, which stream best dealt item by item and non-temporal up to 256 tokens (1024 x
+  // 14336: 102 against 107 us at 80 tokens, 116 / 128 at 130; 2048 x 4096 the other way, 78 / 67).
+  if (stream_tiles_apply(d, T) && d.hidden <= 2560) {
+    using Tile = TileCfg<128, 128, 64, 4>;
+    if (T <= kMidMaxTokens && d.ffn >= 8 * d.hidden) return fn(Path<Tile, Tile, true, true, true>{});
+    return fn(Path<Tile, Tile, true, false, false>{});
+  }
   if (stream_tiles_apply(d, T)) {
     using Tile = TileCfg<128, 256, 64, 3>;
     if (T <= kMidMaxTokens) return fn(Path<Tile, Tile, true, true, false>{});
