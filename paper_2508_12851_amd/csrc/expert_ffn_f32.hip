@@ -9,8 +9,8 @@
 // Split: a workgroup owns 64 rows of one expert x 64 weight rows (GATED: 32 gate rows and the 32 up
 // rows of the same f), and its 8 wavefronts split the contraction: each multiplies its own eighth in
 // 16-wide k-tiles that it stages through 8 KiB of LDS of its own, so the k-loop has no workgroup
-// barrier, two workgroups of 8 wavefronts share a CU, and a tile of even the smallest layer is spread
-// over all four SIMDs.  The next k-tile travels from memory to registers during the MFMAs of this
+// barrier, and a tile of even the smallest layer is spread over all four SIMDs (242 registers: one
+// workgroup, two wavefronts per SIMD).  The next k-tile travels from memory to registers during the MFMAs of this
 // one (32 MFMAs of 64 clocks per wavefront and k-tile).
 //
 // Sums: fp32 results must not get worse with the length of the contraction, so no accumulator runs
