@@ -20,8 +20,6 @@
 #include "prism_internal.h"
 
 namespace prism {
-static bool stream_tiles_apply(const prism_layer_desc& d, int T);
-static bool few_rows_per_expert(const prism_layer_desc& d, int T);
 namespace {
 
 // ---------------------------------------------------------------------------
@@ -161,17 +159,6 @@ __global__ __launch_bounds__(256) void pack_tokens_kernel(const uint4* __restric
   for (int j = 0; j < 8; ++j)
     if (tile0 + j < tiles) dst[(tile0 + j) * 64] = v[j];
 }
-// The copy costs 4 H bytes of traffic per row and a launch; what it saves grows with the 4 H F
-// operations of the row's gate/up products.  Layers whose down projection may cut its last round, from
-// 2.2e10 elements of rows x H x F on (layer with the copy against without: 600 tokens, 2 picks, of
-// 3072 x 6144, 2.3e10, 216 against 231 us; of 1024 x 14336, 1.8e10, 184 / 178; of 2048 x 8192, 2.0e10, 192 / 190).
-static inline bool pack_rows_pays(const prism_layer_desc& d, int T) {
-  const size_t rows = (size_t)T * (d.top_k + d.n_shared);
-  // (the places lie behind the rows, in the partial sums' region: four fp32 rows per token and more)
-  return slicing_shape(d) && T > kStreamMaxTokens && T <= 512 * d.hidden &&
-         rows * d.hidden * d.ffn >= (size_t)22000000000 && align_up(rows, 16) * d.hidden * 2 < 0xFFFF0000ull;
-}
-
 template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B, bool ROTATE>
 prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_expert_weights& w,
                           const int32_t* local_src, const int32_t* local_offsets, int T, void* y,
@@ -283,78 +270,25 @@ template <typename C1_, typename C2_, bool SPLIT_DOWN_, bool STREAM_B_, bool ROT
   static constexpr bool kSplitDown = SPLIT_DOWN_, kStreamB = STREAM_B_, kRotate = ROTATE_;
 };
 
-// Calls fn(Path<...>{}) with the path that serves a bf16 batch of T tokens of layer d.
+// Calls fn(Path<...>{}) with the path that serves a bf16 batch of T tokens of layer d (ffn_paths.h).
 template <typename Fn>
 auto select_path(const prism_layer_desc& d, int T, Fn&& fn) {
-  if (T <= kDecodeMaxTokens) {
-    // Decode batch: every expert has at most 64 rows, the layer is bound by streaming
-    // the weights once.  Small tiles make ~1000 work items; the down projection also
-    // splits its contraction (the slices are summed by a last kernel or by the combine).
-    // No weight tile is shared between workgroups here, so every item starts its
-    // contraction at a different k-tile: at any moment the workgroups then read
-    // different column ranges of the weight rows, whose power-of-two pitch would
-    // otherwise send them all to the same few memory channels.
-    // Tiled weights: 32-wide k-tiles, so that one load instruction takes one whole 1 KiB
-    // tile (with 64-wide k-tiles it would take halves of two), and twice the stages.
-    // An expert has one row tile here, so every weight element is read by exactly one
-    // workgroup, once: the weight loads are marked non-temporal (see STREAM_B).
-    if (d.weight_layout == PRISM_WEIGHTS_TILED && d.hidden >= 256 && d.ffn >= 1024)
-      return fn(Path<TileCfg<64, 128, 32, 8>, TileCfg<64, 128, 32, 8>, true, true, true>{});
-    if (d.hidden >= 192 && d.ffn >= 192)
-      return fn(Path<TileCfg<64, 128, 64, 4>, TileCfg<64, 128, 64, 4>, true, true, true>{});
-    return fn(Path<TileCfg<64, 128, 32, 3>, TileCfg<64, 128, 32, 3>, true, true, true>{});
+  using Decode = TileCfg<64, 128, 64, 4>;
+  using Square = TileCfg<128, 128, 64, 4>;
+  using Wide = TileCfg<128, 256, 64, 3>;
+  switch (ffn_path(d, T)) {
+    case FfnPath::kDecodeTiled: return fn(Path<TileCfg<64, 128, 32, 8>, TileCfg<64, 128, 32, 8>, true, true, true>{});
+    case FfnPath::kDecode: return fn(Path<Decode, Decode, true, true, true>{});
+    case FfnPath::kDecodeShort: return fn(Path<TileCfg<64, 128, 32, 3>, TileCfg<64, 128, 32, 3>, true, true, true>{});
+    case FfnPath::kStream: return fn(Path<Square, Square, true, true, true>{});
+    case FfnPath::kSplitSquare: return fn(Path<Square, Square, true, false, false>{});
+    case FfnPath::kSplitWideNt: return fn(Path<Wide, Wide, true, true, false>{});
+    case FfnPath::kSplitWide: return fn(Path<Wide, Wide, true, false, false>{});
+    case FfnPath::kFewRows64: return fn(Path<Decode, Decode, false, true, false>{});
+    case FfnPath::kFewRows128: return fn(Path<Wide, Square, false, false, false>{});
+    case FfnPath::kPrefill: return fn(Path<TileCfg<256, 256, 32, 4>, TileCfg<256, 256, 32, 4>, false, false, false>{});
+    default: return fn(Path<TileCfg<256, 256, 32, 3>, TileCfg<256, 256, 32, 3>, false, false, false>{});
   }
-  // Batches of a few hundred tokens of a wide layer are still bound by streaming the weights
-  // once, but an expert now has up to a few hundred rows; the down projection splits its
-  // contraction as for decode batches.  Tiles of 128 activation rows x 256 weight rows bring twice
-  // the HBM bytes per k-tile for the same waits and barriers as 128 x 128, and 64-wide k-tiles take
-  // whole 128-byte lines of the activations (and of row-major weights), which 32-wide ones ask the
-  // L2 for twice.  The row tiles of an expert stand next to each other in an XCD's list, so the
-  // second one finds the weight tile in the L2.  4096 x 14336 layer, 5 of 8 experts hosted, tiled
-  // weights, against 128 x 128 x 64 tiles dealt item by item (up to 256 tokens) and 128 x 256 x 32
-  // ones beyond: 328 -> 317 us at 110 tokens, 344 -> 335 at 160, 417 -> 375 at 230, 502 -> 419 at
-  // 352; against prefill tiles 529 -> 445 at 400, 554 -> 502 at 512.  A padded row tile of 256
-  // costs its loads and MFMAs like a full one: prefill tiles with the cut last round are
-  // even at 1024 tokens (between 512 and there: not split here, see kStreamMaxTokens).
-  // Up to 256 tokens most experts have one row tile and the weight loads are marked non-temporal
-  // (341 against 360 us at 180 tokens, 375 against 375 at 230, 424 against 411 at 300).
-  // With few output columns (H up to 2560) the wide tiles make too few items for the machine, in the
-  // down projection above all: 128 x 128 there (5 of 8 experts, layer: 1024 x 14336, 130 tokens 128
-  // against 141 us, 300: 143 / 157; 2048 x 4096, 80: 67 / 71; 3 experts of 1024 x 4096, 220: 44 / 55; at
-  // H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).  Long rows of F >= 8 H hold mostly
-  // gate/up weights, which stream best dealt item by item and non-temporal up to 256 tokens (1024 x
-  // 14336: 102 against 107 us at 80 tokens, 116 / 128 at 130; 2048 x 4096 the other way, 78 / 67).
-  if (stream_tiles_apply(d, T) && d.hidden <= 2560) {
-    using Tile = TileCfg<128, 128, 64, 4>;
-    if (T <= kMidMaxTokens && d.ffn >= 8 * d.hidden) return fn(Path<Tile, Tile, true, true, true>{});
-    return fn(Path<Tile, Tile, true, false, false>{});
-  }
-  if (stream_tiles_apply(d, T)) {
-    using Tile = TileCfg<128, 256, 64, 3>;
-    if (T <= kMidMaxTokens) return fn(Path<Tile, Tile, true, true, false>{});
-    return fn(Path<Tile, Tile, true, false, false>{});
-  }
-  // Many narrow experts with few rows each (rows per expert: what an even spread of the picks over
-  // all experts would give).  256-row tiles are mostly padding there, and the narrow layers have
-  // items enough without a split.  Time of both GEMMs against the 256 x 256 tiles:
-  //   gate/up 128 x 256, down 128 x 128, 64-wide k-tiles: 60 experts, 4 picks, 4 shared, 333 tokens
-  //   (22 rows) 172 -> 148 us, 600 tokens 221 -> 179; 256 experts, 8 picks, 800 tokens 173 -> 158,
-  //   4096 (128 rows) 343 -> 325; 64 experts, 6 picks, 1500 tokens (141 rows) 273 -> 264; beyond,
-  //   the full tiles win (60 experts at 2500 tokens, 167 rows: 390 against 411).
-  //   64 x 128, weights non-temporal, up to 16 rows (an expert has one tile, its weights are read
-  //   once): 64 experts, 80 tokens 138 -> 107 us; 256 experts, 100 tokens 108 -> 81, 400 tokens
-  //   147 -> 116 (126 in the tiles above).  Shared experts take all tokens and read their weights
-  //   once per 64 rows: with 4 of them at 200 tokens the larger tiles are ahead, 128 against 140.
-  if (few_rows_per_expert(d, T)) {
-    if ((long long)T * d.top_k <= 16LL * d.n_experts && (long long)T * d.n_shared <= 512)
-      return fn(Path<TileCfg<64, 128, 64, 4>, TileCfg<64, 128, 64, 4>, false, true, false>{});
-    return fn(Path<TileCfg<128, 256, 64, 3>, TileCfg<128, 128, 64, 4>, false, false, false>{});
-  }
-  // Prefill batch: 256 x 256 tiles (GEMM1: 128 gate + 128 up weight rows).  Very short
-  // contractions (H or F of 64) get the shallowest ring.
-  if (d.hidden >= 128 && d.ffn >= 128)
-    return fn(Path<TileCfg<256, 256, 32, 4>, TileCfg<256, 256, 32, 4>, false, false, false>{});
-  return fn(Path<TileCfg<256, 256, 32, 3>, TileCfg<256, 256, 32, 3>, false, false, false>{});
 }
 
 }  // namespace
@@ -384,23 +318,6 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
         d, x, w, local_src, local_offsets, T, y, h, h_tiled, x_rows, tiles, part, slice_part, st, stage_events, deferred_splits,
         schedules_built);
   });
-}
-
-// Batches between the decode and the prefill sizes whose down projection in prefill tiles would
-// have too few items for the machine: column tiles x row tiles, the latter estimated from what the
-// host knows (half of the experts hosted, rows spread evenly).  Layers of many small experts have
-// enough items at any batch size.
-static bool stream_tiles_apply(const prism_layer_desc& d, int T) {
-  if (T <= kDecodeMaxTokens || T > kStreamMaxTokens || d.hidden < 256 || d.ffn < 1024) return false;
-  const int row_tiles = ceil_div(T * d.top_k, 256) + d.n_experts / 2 + d.n_shared * ceil_div(T, 256);
-  return row_tiles * ceil_div(d.hidden, 256) <= 128;
-}
-
-// The line at 144 rows per expert is measured on narrow layers (select_path); layers whose down
-// projection may cut its last round keep the prefill tiles, which the cut fills better.
-static bool few_rows_per_expert(const prism_layer_desc& d, int T) {
-  if (T <= kDecodeMaxTokens || d.hidden < 192 || d.ffn < 192 || slicing_shape(d)) return false;
-  return (long long)T * d.top_k <= 144LL * d.n_experts;
 }
 
 FfnShapes ffn_schedule_shapes(const prism_layer_desc& d, int T) {

@@ -1,0 +1,152 @@
+// Which tile path serves a bf16 expert FFN, by the sizes the host knows (no HIP in here: the rules run
+// and are tested on the CPU).
+#ifndef PRISM_FFN_PATHS_H_
+#define PRISM_FFN_PATHS_H_
+
+#include <stddef.h>
+
+#include "prism.h"
+
+namespace prism {
+
+constexpr int kDecodeMaxTokens = 64;    // batches up to this size take the weight-streaming path
+constexpr int kMidMaxTokens = 256;      // see ffn_path
+constexpr int kStreamMaxTokens = 512;   // wide bf16 layers: batches up to this size also split the down projection
+
+static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Partial tiles of a down projection whose last round of work items is cut along the contraction:
+// one tile per workgroup.  Prefill batches of layers whose contraction is long enough for the cut
+// to pay: an item of K / 32 k-tiles takes about 0.74 us per k-tile, the cut saves at least half of
+// one item per launch and costs two short launches plus up to 64 MB of fp32 tiles written and read
+// (about 40 us); with fewer than 128 k-tiles (the gate/up GEMM of the same layers included, whose
+// contraction is H) it was measured to lose.
+constexpr int kSliceMinFfn = 4096;
+// Smaller batches of such layers are not cut.  (Up to kStreamMaxTokens most of these layers split the
+// whole down projection instead; those with too many row tiles for that, 16 experts of 4096 columns at
+// 400 tokens for instance, run in prefill tiles and are cut from here on.)
+constexpr int kSliceMinTokens = 353;
+static inline bool slicing_shape(const prism_layer_desc& d) {
+  return d.dtype == PRISM_BF16 && d.ffn >= kSliceMinFfn && d.hidden >= 128;
+}
+static inline bool down_slicing_applies(const prism_layer_desc& d, int T) {
+  return slicing_shape(d) && T >= kSliceMinTokens;
+}
+
+// Batches between the decode and the prefill sizes whose down projection in prefill tiles would
+// have too few items for the machine: column tiles x row tiles, the latter estimated from what the
+// host knows (half of the experts hosted, rows spread evenly).  Layers of many small experts have
+// enough items at any batch size.
+static inline bool stream_tiles_apply(const prism_layer_desc& d, int T) {
+  if (T <= kDecodeMaxTokens || T > kStreamMaxTokens || d.hidden < 256 || d.ffn < 1024) return false;
+  const int row_tiles = ceil_div(T * d.top_k, 256) + d.n_experts / 2 + d.n_shared * ceil_div(T, 256);
+  return row_tiles * ceil_div(d.hidden, 256) <= 128;
+}
+
+// The line at 144 rows per expert is measured on narrow layers (ffn_path); layers whose down
+// projection may cut its last round keep the prefill tiles, which the cut fills better.
+static inline bool few_rows_per_expert(const prism_layer_desc& d, int T) {
+  if (T <= kDecodeMaxTokens || d.hidden < 192 || d.ffn < 192 || slicing_shape(d)) return false;
+  return (long long)T * d.top_k <= 144LL * d.n_experts;
+}
+
+enum class FfnPath {
+  kDecodeTiled,    // 64 x 128 tiles, 32-wide k-tiles; contraction of the down projection split
+  kDecode,         // 64 x 128, 64-wide k-tiles; split
+  kDecodeShort,    // the same with a short ring, for short contractions
+  kStream,         // 128 x 128, weights non-temporal, items dealt to the XCDs one by one; split
+  kSplitSquare,    // 128 x 128; split
+  kSplitWideNt,    // 128 x 256, weights non-temporal; split
+  kSplitWide,      // 128 x 256; split
+  kFewRows64,      // 64 x 128, weights non-temporal
+  kFewRows128,     // gate/up 128 x 256, down 128 x 128
+  kPrefill,        // 256 x 256
+  kPrefillShort    // the same with a short ring
+};
+
+// The path of a batch of T > 0 tokens of layer d (bf16).
+static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
+  if (T <= kDecodeMaxTokens) {
+    // Decode batch: every expert has at most 64 rows, the layer is bound by streaming
+    // the weights once.  Small tiles make ~1000 work items; the down projection also
+    // splits its contraction (the slices are summed by a last kernel or by the combine).
+    // No weight tile is shared between workgroups here, so every item starts its
+    // contraction at a different k-tile: at any moment the workgroups then read
+    // different column ranges of the weight rows, whose power-of-two pitch would
+    // otherwise send them all to the same few memory channels.
+    // Tiled weights: 32-wide k-tiles, so that one load instruction takes one whole 1 KiB
+    // tile (with 64-wide k-tiles it would take halves of two), and twice the stages.
+    // An expert has one row tile here, so every weight element is read by exactly one
+    // workgroup, once: the weight loads are marked non-temporal (grouped_gemm.h, STREAM_B).
+    if (d.weight_layout == PRISM_WEIGHTS_TILED && d.hidden >= 256 && d.ffn >= 1024)
+      return FfnPath::kDecodeTiled;
+    if (d.hidden >= 192 && d.ffn >= 192)
+      return FfnPath::kDecode;
+    return FfnPath::kDecodeShort;
+  }
+  // Batches of a few hundred tokens of a wide layer are still bound by streaming the weights
+  // once, but an expert now has up to a few hundred rows; the down projection splits its
+  // contraction as for decode batches.  Tiles of 128 activation rows x 256 weight rows bring twice
+  // the HBM bytes per k-tile for the same waits and barriers as 128 x 128, and 64-wide k-tiles take
+  // whole 128-byte lines of the activations (and of row-major weights), which 32-wide ones ask the
+  // L2 for twice.  The row tiles of an expert stand next to each other in an XCD's list, so the
+  // second one finds the weight tile in the L2.  4096 x 14336 layer, 5 of 8 experts hosted, tiled
+  // weights, against 128 x 128 x 64 tiles dealt item by item (up to 256 tokens) and 128 x 256 x 32
+  // ones beyond: 328 -> 317 us at 110 tokens, 344 -> 335 at 160, 417 -> 375 at 230, 502 -> 419 at
+  // 352; against prefill tiles 529 -> 445 at 400, 554 -> 502 at 512.  A padded row tile of 256
+  // costs its loads and MFMAs like a full one: prefill tiles with the cut last round are
+  // even at 1024 tokens (between 512 and there: not split here, see kStreamMaxTokens).
+  // Up to 256 tokens most experts have one row tile and the weight loads are marked non-temporal
+  // (341 against 360 us at 180 tokens, 375 against 375 at 230, 424 against 411 at 300).
+  // With few output columns (H up to 2560) the wide tiles make too few items for the machine, in the
+  // down projection above all: 128 x 128 there (5 of 8 experts, layer: 1024 x 14336, 130 tokens 128
+  // against 141 us, 300: 143 / 157; 2048 x 4096, 80: 67 / 71; 3 experts of 1024 x 4096, 220: 44 / 55; at
+  // H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).  Long rows of F >= 8 H hold mostly
+  // gate/up weights, which stream best dealt item by item and non-temporal up to 256 tokens (1024 x
+  // 14336: 102 against 107 us at 80 tokens, 116 / 128 at 130; 2048 x 4096 the other way, 78 / 67).
+  if (stream_tiles_apply(d, T) && d.hidden <= 2560) {
+    if (T <= kMidMaxTokens && d.ffn >= 8 * d.hidden) return FfnPath::kStream;
+    return FfnPath::kSplitSquare;
+  }
+  if (stream_tiles_apply(d, T)) {
+    if (T <= kMidMaxTokens) return FfnPath::kSplitWideNt;
+    return FfnPath::kSplitWide;
+  }
+  // Many narrow experts with few rows each (rows per expert: what an even spread of the picks over
+  // all experts would give).  256-row tiles are mostly padding there, and the narrow layers have
+  // items enough without a split.  Time of both GEMMs against the 256 x 256 tiles:
+  //   gate/up 128 x 256, down 128 x 128, 64-wide k-tiles: 60 experts, 4 picks, 4 shared, 333 tokens
+  //   (22 rows) 172 -> 148 us, 600 tokens 221 -> 179; 256 experts, 8 picks, 800 tokens 173 -> 158,
+  //   4096 (128 rows) 343 -> 325; 64 experts, 6 picks, 1500 tokens (141 rows) 273 -> 264; beyond,
+  //   the full tiles win (60 experts at 2500 tokens, 167 rows: 390 against 411).
+  //   64 x 128, weights non-temporal, up to 16 rows (an expert has one tile, its weights are read
+  //   once): 64 experts, 80 tokens 138 -> 107 us; 256 experts, 100 tokens 108 -> 81, 400 tokens
+  //   147 -> 116 (126 in the tiles above).  Shared experts take all tokens and read their weights
+  //   once per 64 rows: with 4 of them at 200 tokens the larger tiles are ahead, 128 against 140.
+  if (few_rows_per_expert(d, T)) {
+    if ((long long)T * d.top_k <= 16LL * d.n_experts && (long long)T * d.n_shared <= 512)
+      return FfnPath::kFewRows64;
+    return FfnPath::kFewRows128;
+  }
+  // Prefill batch: 256 x 256 tiles (GEMM1: 128 gate + 128 up weight rows).  Very short
+  // contractions (H or F of 64) get the shallowest ring.
+  if (d.hidden >= 128 && d.ffn >= 128)
+    return FfnPath::kPrefill;
+  return FfnPath::kPrefillShort;
+}
+
+// Whether the gate/up GEMM of a kPrefill batch reads its tokens from a copy in row order (expert_ffn.hip, pack_tokens_kernel).
+// The copy costs 4 H bytes of traffic per row and a launch; what it saves grows with the 4 H F
+// operations of the row's gate/up products.  Layers whose down projection may cut its last round, from
+// 2.2e10 elements of rows x H x F on (layer with the copy against without: 600 tokens, 2 picks, of
+// 3072 x 6144, 2.3e10, 216 against 231 us; of 1024 x 14336, 1.8e10, 184 / 178; of 2048 x 8192, 2.0e10, 192 / 190).
+static inline bool pack_rows_pays(const prism_layer_desc& d, int T) {
+  const size_t rows = (size_t)T * (d.top_k + d.n_shared);
+  // (the places lie behind the rows, in the partial sums' region: four fp32 rows per token and more)
+  return slicing_shape(d) && T > kStreamMaxTokens && T <= 512 * d.hidden &&
+         rows * d.hidden * d.ffn >= (size_t)22000000000 && align_up(rows, 16) * d.hidden * 2 < 0xFFFF0000ull;
+}
+
+}  // namespace prism
+#endif  // PRISM_FFN_PATHS_H_

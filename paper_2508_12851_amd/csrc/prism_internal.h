@@ -9,6 +9,7 @@
 
 #include <atomic>
 
+#include "ffn_paths.h"
 #include "prism.h"
 
 namespace prism {
@@ -23,21 +24,15 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;
 
-static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
-static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
-
 // ---------------------------------------------------------------------------
 // Workspace layout.  One layout serves every entry point, so a buffer sized by
 // prism_workspace_bytes() fits all of them.
 // ---------------------------------------------------------------------------
 constexpr int kDispatchChunk = 2048;   // assignments per dispatch block
 constexpr int kFineChunk = 512;        // ... of batches whose router counted them already, and of decode batches
-constexpr int kDecodeMaxTokens = 64;    // batches up to this size take the weight-streaming path
 constexpr int kDecodeSplits = 8;        // most contraction slices of its down projection (the schedule builder picks how many) ...
 constexpr int kStreamSplits = 4;        // ... and of batches with more than kManySplitsRows rows that still split it
 constexpr int kManySplitsRows = 256;    // (every slice is one more fp32 copy of all rows)
-constexpr int kStreamMaxTokens = 512;   // wide bf16 layers: batches up to this size also split the down projection (expert_ffn.hip)
-constexpr int kMidMaxTokens = 256;      // ... and up to this size with non-temporal weight loads (expert_ffn.hip)
 constexpr int kMinTileM = 64;           // smallest row tile of the grouped GEMM (bounds table sizes)
 constexpr int kRouteTokTile = 16;       // tokens per router tile
 constexpr int kRouteMaxHSplit = 16;     // hidden-dimension slices of the decode router
@@ -79,22 +74,6 @@ static inline size_t tile_table_ints(const prism_layer_desc& d, int T) {
   return align_up(32 + 8 * 8 * (mt * nj8 + 32) + 8 * 16 * 8, 64);
 }
 
-// Partial tiles of a down projection whose last round of work items is cut along the contraction:
-// one tile per workgroup.  Prefill batches of layers whose contraction is long enough for the cut
-// to pay: an item of K / 32 k-tiles takes about 0.74 us per k-tile, the cut saves at least half of
-// one item per launch and costs two short launches plus up to 64 MB of fp32 tiles written and read
-// (about 40 us); with fewer than 128 k-tiles (the gate/up GEMM of the same layers included, whose
-// contraction is H) it was measured to lose.
-constexpr int kSliceMinFfn = 4096;
-// Batches beyond this size may take prefill tiles (layers with too many row tiles for the streaming
-// path, expert_ffn.hip); no smaller one needs the partial tiles.
-constexpr int kStreamMaxTokensSliced = 352;
-static inline bool slicing_shape(const prism_layer_desc& d) {
-  return d.dtype == PRISM_BF16 && d.ffn >= kSliceMinFfn && d.hidden >= 128;
-}
-static inline bool down_slicing_applies(const prism_layer_desc& d, int T) {
-  return slicing_shape(d) && T > kStreamMaxTokensSliced;
-}
 static inline size_t slice_part_bytes(const prism_layer_desc& d, int T) {
   return down_slicing_applies(d, T) ? (size_t)256 * 256 * 256 * 4 : 0;
 }

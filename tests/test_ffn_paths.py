@@ -1,0 +1,25 @@
+"""CPU: the rules that choose the tiles of the expert FFN (csrc/ffn_paths.h)."""
+import pytest
+
+from ffn_paths import cuts_last_round, ffn_path, packs_rows
+
+
+@pytest.mark.parametrize("H,F,E,k,S,T,tiled,path", [
+    (4096, 14336, 8, 2, 0, 32, True, "kDecodeTiled"),
+    (4096, 14336, 8, 2, 0, 64, False, "kDecode"),
+    (64, 64, 8, 2, 0, 64, False, "kDecodeShort"),
+    (4096, 14336, 8, 2, 0, 300, True, "kSplitWide"),
+    (1024, 4096, 8, 2, 0, 300, False, "kSplitSquare"),
+    (2048, 1408, 60, 4, 4, 333, True, "kFewRows128"),
+    (1024, 1024, 256, 8, 0, 100, True, "kFewRows64"),
+    (4096, 14336, 8, 2, 0, 4096, True, "kPrefill"),
+    (64, 64, 8, 2, 0, 65, False, "kPrefillShort"),
+])
+def test_path_of_the_usual_sizes(H, F, E, k, S, T, tiled, path):
+    assert ffn_path(H, F, E, k, S, T, tiled) == path
+
+
+def test_cut_and_copy_of_the_usual_sizes():
+    assert cuts_last_round(4096, 14336, 8, 2, 0, 4096) and packs_rows(4096, 14336, 8, 2, 0, 4096)
+    assert not cuts_last_round(2048, 1408, 60, 4, 4, 8192) and not packs_rows(2048, 1408, 60, 4, 4, 8192)
+    assert cuts_last_round(4096, 4096, 16, 2, 0, 400)       # too many row tiles for the split path
