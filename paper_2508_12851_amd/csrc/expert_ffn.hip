@@ -282,7 +282,6 @@ auto select_path(const prism_layer_desc& d, int T, Fn&& fn) {
     case FfnPath::kDecodeShort: return fn(Path<TileCfg<64, 128, 32, 3>, TileCfg<64, 128, 32, 3>, true, true, true>{});
     case FfnPath::kStream: return fn(Path<Square, Square, true, true, true>{});
     case FfnPath::kSplitSquare: return fn(Path<Square, Square, true, false, false>{});
-    case FfnPath::kSplitWideNt: return fn(Path<Wide, Wide, true, true, false>{});
     case FfnPath::kSplitWide: return fn(Path<Wide, Wide, true, false, false>{});
     case FfnPath::kFewRows64: return fn(Path<Decode, Decode, false, true, false>{});
     case FfnPath::kFewRows128: return fn(Path<Wide, Square, false, false, false>{});

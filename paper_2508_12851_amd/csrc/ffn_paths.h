@@ -10,7 +10,7 @@
 namespace prism {
 
 constexpr int kDecodeMaxTokens = 64;    // batches up to this size take the weight-streaming path
-constexpr int kMidMaxTokens = 256;      // see ffn_path
+constexpr int kMidMaxTokens = 256;      // ... in 128 x 128 tiles with non-temporal weight loads up to this one (ffn_path)
 constexpr int kStreamMaxTokens = 512;   // wide bf16 layers: batches up to this size also split the down projection
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -57,7 +57,6 @@ enum class FfnPath {
   kDecodeShort,    // the same with a short ring, for short contractions
   kStream,         // 128 x 128, weights non-temporal, items dealt to the XCDs one by one; split
   kSplitSquare,    // 128 x 128; split
-  kSplitWideNt,    // 128 x 256, weights non-temporal; split
   kSplitWide,      // 128 x 256; split
   kFewRows64,      // 64 x 128, weights non-temporal
   kFewRows128,     // gate/up 128 x 256, down 128 x 128
@@ -87,32 +86,28 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   }
   // Batches of a few hundred tokens of a wide layer are still bound by streaming the weights
   // once, but an expert now has up to a few hundred rows; the down projection splits its
-  // contraction as for decode batches.  Tiles of 128 activation rows x 256 weight rows bring twice
-  // the HBM bytes per k-tile for the same waits and barriers as 128 x 128, and 64-wide k-tiles take
-  // whole 128-byte lines of the activations (and of row-major weights), which 32-wide ones ask the
-  // L2 for twice.  The row tiles of an expert stand next to each other in an XCD's list, so the
-  // second one finds the weight tile in the L2.  4096 x 14336 layer, 5 of 8 experts hosted, tiled
-  // weights, against 128 x 128 x 64 tiles dealt item by item (up to 256 tokens) and 128 x 256 x 32
-  // ones beyond: 328 -> 317 us at 110 tokens, 344 -> 335 at 160, 417 -> 375 at 230, 502 -> 419 at
-  // 352; against prefill tiles 529 -> 445 at 400, 554 -> 502 at 512.  A padded row tile of 256
-  // costs its loads and MFMAs like a full one: prefill tiles with the cut last round are
-  // even at 1024 tokens (between 512 and there: not split here, see kStreamMaxTokens).
-  // Up to 256 tokens most experts have one row tile and the weight loads are marked non-temporal
-  // (341 against 360 us at 180 tokens, 375 against 375 at 230, 424 against 411 at 300).
+  // contraction as for decode batches.  64-wide k-tiles take whole 128-byte lines of the
+  // activations (and of row-major weights), which 32-wide ones ask the L2 for twice.
+  // Up to 256 tokens an expert has one or two row tiles: 128 x 128, dealt item by item and
+  // non-temporal.  128 x 256 tiles halve the number of items, and the host does not know how many
+  // experts are hosted: with one or two of 8, a layer has fewer wide tiles than the machine has
+  // workgroups.  Layer, weights from HBM, 128 x 128 against 128 x 256: 4096 x 14336, 66 tokens, 1 hosted
+  // 94 / 128 us; 200 tokens, 1 hosted, evenly spread picks 104 / 143 (the other way with 5 hosted, 412 /
+  // 376); 3072 x 8192, 96 tokens, 2 hosted 83 / 101; 2048 x 8192, 66 tokens, 5 hosted 116 / 132, and 131 if
+  // dealt in rectangles with temporal loads.  16 shapes, 1 to 8 hosted: up to 160 tokens 128 x 128 is
+  // ahead by 6 % on average and by up to 27 %, from there to 256 the averages are even.
+  if (stream_tiles_apply(d, T) && T <= kMidMaxTokens) return FfnPath::kStream;
+  // Beyond, the row tiles of an expert stand next to each other in an XCD's list, so that the later
+  // ones find the weight tile in the L2, and tiles of 128 activation rows x 256 weight rows bring twice
+  // the HBM bytes per k-tile for the same waits and barriers as 128 x 128.  4096 x 14336 layer, 5 of 8 experts
+  // hosted, tiled weights, against 128 x 256 x 32 tiles up to 352 tokens and prefill tiles from there: 502 -> 419 us
+  // at 352, 529 -> 445 at 400, 554 -> 502 at 512.  A padded row tile of 256 costs its loads and MFMAs like
+  // a full one: prefill tiles with the cut last round are even at 1024 tokens (between 512 and there: not
+  // split here, see kStreamMaxTokens).
   // With few output columns (H up to 2560) the wide tiles make too few items for the machine, in the
-  // down projection above all: 128 x 128 there (5 of 8 experts, layer: 1024 x 14336, 130 tokens 128
-  // against 141 us, 300: 143 / 157; 2048 x 4096, 80: 67 / 71; 3 experts of 1024 x 4096, 220: 44 / 55; at
-  // H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).  Long rows of F >= 8 H hold mostly
-  // gate/up weights, which stream best dealt item by item and non-temporal up to 256 tokens (1024 x
-  // 14336: 102 against 107 us at 80 tokens, 116 / 128 at 130; 2048 x 4096 the other way, 78 / 67).
-  if (stream_tiles_apply(d, T) && d.hidden <= 2560) {
-    if (T <= kMidMaxTokens && d.ffn >= 8 * d.hidden) return FfnPath::kStream;
-    return FfnPath::kSplitSquare;
-  }
-  if (stream_tiles_apply(d, T)) {
-    if (T <= kMidMaxTokens) return FfnPath::kSplitWideNt;
-    return FfnPath::kSplitWide;
-  }
+  // down projection above all: 128 x 128 there (5 of 8 experts, layer: 1024 x 14336, 300 tokens 143 against 157
+  // us; at H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).
+  if (stream_tiles_apply(d, T)) return d.hidden <= 2560 ? FfnPath::kSplitSquare : FfnPath::kSplitWide;
   // Many narrow experts with few rows each (rows per expert: what an even spread of the picks over
   // all experts would give).  256-row tiles are mostly padding there, and the narrow layers have
   // items enough without a split.  Time of both GEMMs against the 256 x 256 tiles:

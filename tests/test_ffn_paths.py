@@ -23,3 +23,13 @@ def test_cut_and_copy_of_the_usual_sizes():
     assert cuts_last_round(4096, 14336, 8, 2, 0, 4096) and packs_rows(4096, 14336, 8, 2, 0, 4096)
     assert not cuts_last_round(2048, 1408, 60, 4, 4, 8192) and not packs_rows(2048, 1408, 60, 4, 4, 8192)
     assert cuts_last_round(4096, 4096, 16, 2, 0, 400)       # too many row tiles for the split path
+
+
+@pytest.mark.parametrize("T", [65, 128, 129, 200, 256])
+@pytest.mark.parametrize("H,F,E,k,S", [
+    (4096, 14336, 8, 2, 0), (4096, 14336, 8, 1, 0), (4096, 4096, 8, 2, 0), (3072, 8192, 8, 2, 0), (2304, 9216, 8, 2, 0),
+    (2560, 10240, 8, 2, 0), (2048, 8192, 4, 2, 0), (2048, 4096, 16, 2, 1), (1536, 6144, 8, 2, 0), (1024, 2048, 8, 2, 0),
+])
+def test_weight_streaming_batches_take_the_small_tiles(H, F, E, k, S, T):
+    """Few hosted experts (the host cannot know) leave most of the machine idle in wider tiles."""
+    assert ffn_path(H, F, E, k, S, T) == "kStream"

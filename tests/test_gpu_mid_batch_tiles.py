@@ -8,13 +8,13 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,H,F,E,k,S,hosted", [
     (65, 256, 1024, 4, 2, 0, 3),       # split down projection: fewest tokens, shortest contractions
-    (256, 320, 1088, 4, 2, 1, 4),      # ragged columns, last size with non-temporal weights
+    (256, 320, 1088, 4, 2, 1, 4),      # ragged columns, last size of the streaming tiles
     (257, 320, 1088, 4, 4, 0, 4),      # every expert 257 rows: a third row tile of one row
     (512, 256, 1024, 8, 2, 1, 5),      # last split size
     (513, 256, 1024, 8, 2, 1, 5),
-    (256, 2624, 1024, 4, 2, 0, 3),     # wide tiles: ragged columns, last size with non-temporal weights
+    (256, 2624, 1024, 4, 2, 0, 3),     # more columns, last size of the streaming tiles
     (257, 2624, 1088, 4, 4, 0, 4),     # and a third row tile of one row
-    (130, 256, 2048, 4, 2, 0, 3),      # F = 8 H: items dealt one by one
+    (130, 256, 2048, 4, 2, 0, 3),      # F = 8 H
     (360, 256, 4096, 8, 2, 0, 5),      # a contraction long enough for the cut, not cut any more
     (384, 192, 192, 48, 2, 0, 40),     # 16 rows per expert, shortest ring
     (385, 192, 192, 48, 2, 0, 40),     # one pick over it
