@@ -44,11 +44,16 @@ static inline bool stream_tiles_apply(const prism_layer_desc& d, int T) {
   return row_tiles * ceil_div(d.hidden, 256) <= 128;
 }
 
-// The line at 144 rows per expert is measured on narrow layers (ffn_path); layers whose down
-// projection may cut its last round keep the prefill tiles, which the cut fills better.
+// Rows per expert: what an even spread of the picks over all experts would give, all the host knows.
+// Layers whose down projection may cut its last round keep the prefill tiles, which the cut fills better.
+constexpr int kFewRows = 112;            // most rows per expert of the 128-row tiles
+constexpr int kFewRowsOnePick = 2560;    // ... and most rows of a batch of one pick per token
+constexpr int kVeryFewRows = 16;         // most rows per expert of the 64-row tiles
+constexpr int kVeryFewTokens = 1024;     // ... and most tokens: an expert has at most that many rows
 static inline bool few_rows_per_expert(const prism_layer_desc& d, int T) {
   if (T <= kDecodeMaxTokens || d.hidden < 192 || d.ffn < 192 || slicing_shape(d)) return false;
-  return (long long)T * d.top_k <= 144LL * d.n_experts;
+  if (d.top_k == 1 && T > kFewRowsOnePick) return false;
+  return (long long)T * d.top_k <= (long long)kFewRows * d.n_experts;
 }
 
 enum class FfnPath {
@@ -108,19 +113,23 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   // down projection above all: 128 x 128 there (5 of 8 experts, layer: 1024 x 14336, 300 tokens 143 against 157
   // us; at H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).
   if (stream_tiles_apply(d, T)) return d.hidden <= 2560 ? FfnPath::kSplitSquare : FfnPath::kSplitWide;
-  // Many narrow experts with few rows each (rows per expert: what an even spread of the picks over
-  // all experts would give).  256-row tiles are mostly padding there, and the narrow layers have
-  // items enough without a split.  Time of both GEMMs against the 256 x 256 tiles:
+  // Many narrow experts with few rows each.  256-row tiles are mostly padding there, and the narrow
+  // layers have items enough without a split.  Time of both GEMMs against the 256 x 256 tiles:
   //   gate/up 128 x 256, down 128 x 128, 64-wide k-tiles: 60 experts, 4 picks, 4 shared, 333 tokens
-  //   (22 rows) 172 -> 148 us, 600 tokens 221 -> 179; 256 experts, 8 picks, 800 tokens 173 -> 158,
-  //   4096 (128 rows) 343 -> 325; 64 experts, 6 picks, 1500 tokens (141 rows) 273 -> 264; beyond,
-  //   the full tiles win (60 experts at 2500 tokens, 167 rows: 390 against 411).
+  //   (22 rows) 172 -> 148 us, 600 tokens 221 -> 179; 256 experts, 8 picks, 800 tokens 173 -> 158; whole
+  //   layer, 160 of 256 hosted, 3500 tokens (109 rows) 327 -> 314.  From 120 rows on the two are even or
+  //   the full tiles ahead (evenly spread picks, layer: 60 experts, 2150 tokens, 143 rows, 454 against
+  //   478 us; 64 experts, 8 hosted, 1300 tokens, 122 rows, 122 against 134).
+  //   One pick per token is what a peer asks for: all rows are for the hosted experts, however few
+  //   they are, and one with hundreds of rows pays for every row tile (8 of 256 experts of 2048 x 1408
+  //   hosted, FFN: 2200 rows 94 -> 77 us, 3000 rows 92 -> 100, 4096 rows 100 -> 117).
   //   64 x 128, weights non-temporal, up to 16 rows (an expert has one tile, its weights are read
   //   once): 64 experts, 80 tokens 138 -> 107 us; 256 experts, 100 tokens 108 -> 81, 400 tokens
   //   147 -> 116 (126 in the tiles above).  Shared experts take all tokens and read their weights
-  //   once per 64 rows: with 4 of them at 200 tokens the larger tiles are ahead, 128 against 140.
+  //   once per 64 rows: with 4 of them at 200 tokens the larger tiles are ahead, 128 against 140.  So
+  //   do the experts of that peer: 1000 rows 65 us in either, 1500 rows 79 against 62.
   if (few_rows_per_expert(d, T)) {
-    if ((long long)T * d.top_k <= 16LL * d.n_experts && (long long)T * d.n_shared <= 512)
+    if ((long long)T * d.top_k <= (long long)kVeryFewRows * d.n_experts && (long long)T * d.n_shared <= 512 && T <= kVeryFewTokens)
       return FfnPath::kFewRows64;
     return FfnPath::kFewRows128;
   }

@@ -33,3 +33,20 @@ def test_cut_and_copy_of_the_usual_sizes():
 def test_weight_streaming_batches_take_the_small_tiles(H, F, E, k, S, T):
     """Few hosted experts (the host cannot know) leave most of the machine idle in wider tiles."""
     assert ffn_path(H, F, E, k, S, T) == "kStream"
+
+
+@pytest.mark.parametrize("H,F,E,k,S,T,path", [
+    (2048, 1408, 256, 1, 0, 1024, "kFewRows64"),      # a peer's rows: few hosted experts may get them all
+    (2048, 1408, 256, 1, 0, 1025, "kFewRows128"),
+    (2048, 1408, 256, 1, 0, 2560, "kFewRows128"),
+    (2048, 1408, 256, 1, 0, 2561, "kPrefill"),
+    (2048, 1408, 64, 1, 0, 4096, "kPrefill"),
+    (1024, 1024, 256, 8, 0, 512, "kFewRows64"),       # 16 rows per expert
+    (1024, 1024, 256, 8, 0, 513, "kFewRows128"),
+    (1024, 1024, 256, 8, 0, 3584, "kFewRows128"),     # 112 rows per expert
+    (1024, 1024, 256, 8, 0, 3585, "kPrefill"),
+    (2048, 1408, 60, 4, 4, 2150, "kPrefill"),
+    (2048, 1408, 64, 6, 2, 1500, "kPrefill"),
+])
+def test_lines_of_the_few_rows_tiles(H, F, E, k, S, T, path):
+    assert ffn_path(H, F, E, k, S, T) == path

@@ -22,6 +22,15 @@ pytestmark = pytest.mark.gpu
     (129, 192, 704, 32, 4, 4, 20),     # 516
     (1152, 320, 448, 24, 3, 0, 24),    # 144 rows per expert
     (1153, 320, 448, 24, 3, 1, 24),
+    (896, 320, 448, 24, 3, 0, 24),     # 112 rows per expert: last size of the 128-row tiles
+    (897, 320, 448, 24, 3, 1, 24),
+    # One pick per token, the popular experts with several row tiles.  (All experts hosted: with a share p of
+    # the tokens local, the rms of the batch is sqrt(p) of a local row's, and a rounding error of 3e-3 of the
+    # row's rms counts as 3e-3 / sqrt(p) against the bar of 2e-2; one token of 1025 would count 9e-2.)
+    (1024, 192, 192, 64, 1, 0, 64),    # last size of the 64-row tiles
+    (1025, 192, 192, 65, 1, 0, 65),
+    (2560, 192, 192, 64, 1, 0, 64),    # last size of the 128-row tiles
+    (2561, 192, 192, 64, 1, 0, 64),
     (128, 192, 320, 2, 2, 1, 2),       # full 128-row tiles
     (129, 192, 320, 2, 2, 1, 1),       # and one row more
     (70, 128, 192, 64, 2, 0, 64),      # contraction below the rings': prefill tiles
