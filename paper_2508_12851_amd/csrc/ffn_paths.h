@@ -11,6 +11,7 @@ namespace prism {
 
 constexpr int kDecodeMaxTokens = 64;    // batches up to this size take the weight-streaming path
 constexpr int kMidMaxTokens = 256;      // ... in 128 x 128 tiles with non-temporal weight loads up to this one (ffn_path)
+constexpr int kSquareMaxTokens = 448;   // ... in 128 x 128 tiles, if their hidden size is 1025 to 2560 (ffn_path)
 constexpr int kStreamMaxTokens = 512;   // wide bf16 layers: batches up to this size also split the down projection
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -111,8 +112,15 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   // split here, see kStreamMaxTokens).
   // With few output columns (H up to 2560) the wide tiles make too few items for the machine, in the
   // down projection above all: 128 x 128 there (5 of 8 experts, layer: 1024 x 14336, 300 tokens 143 against 157
-  // us; at H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).
-  if (stream_tiles_apply(d, T)) return d.hidden <= 2560 ? FfnPath::kSplitSquare : FfnPath::kSplitWide;
+  // us; at H = 3072 the wide ones lead, 14336 x 3072, 300 tokens, 194 / 223).  Near 512 tokens popular
+  // experts have three and four row tiles, which make items enough: 4 hosted, evenly spread picks,
+  // 512 tokens, wide against 128 x 128: 2560 x 7168 179 / 203 us, 1536 x 8192 125 / 144, 2048 x 14336 217 / 247; at
+  // 420 tokens the 128 x 128 ones still lead (mean over 1 to 6 hosted 1536 x 8192 -9 %, 2560 x 7168 -5 %), and
+  // with H = 1024 at all sizes (4096 wide, 512 tokens: -9 %).
+  if (stream_tiles_apply(d, T)) {
+    const bool square = d.hidden <= 1024 || (d.hidden <= 2560 && T <= kSquareMaxTokens);
+    return square ? FfnPath::kSplitSquare : FfnPath::kSplitWide;
+  }
   // Many narrow experts with few rows each.  256-row tiles are mostly padding there, and the narrow
   // layers have items enough without a split.  Time of both GEMMs against the 256 x 256 tiles:
   //   gate/up 128 x 256, down 128 x 128, 64-wide k-tiles: 60 experts, 4 picks, 4 shared, 333 tokens

@@ -50,3 +50,12 @@ def test_weight_streaming_batches_take_the_small_tiles(H, F, E, k, S, T):
 ])
 def test_lines_of_the_few_rows_tiles(H, F, E, k, S, T, path):
     assert ffn_path(H, F, E, k, S, T) == path
+
+
+@pytest.mark.parametrize("H,T,path", [
+    (1024, 257, "kSplitSquare"), (1024, 512, "kSplitSquare"), (1088, 448, "kSplitSquare"), (1088, 449, "kSplitWide"),
+    (2560, 257, "kSplitSquare"), (2560, 448, "kSplitSquare"), (2560, 449, "kSplitWide"), (2560, 512, "kSplitWide"),
+    (2624, 257, "kSplitWide"), (4096, 512, "kSplitWide"),
+])
+def test_lines_of_the_split_tiles(H, T, path):
+    assert ffn_path(H, 8192, 8, 2, 0, T) == path

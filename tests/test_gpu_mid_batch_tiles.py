@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
     (257, 320, 1088, 4, 4, 0, 4),      # every expert 257 rows: a third row tile of one row
     (512, 256, 1024, 8, 2, 1, 5),      # last split size
     (513, 256, 1024, 8, 2, 1, 5),
+    (448, 1088, 1088, 4, 2, 0, 3),     # last size in 128 x 128 tiles: ragged columns
+    (449, 1088, 1088, 4, 2, 1, 3),     # and one token more, in 128 x 256 ones
     (256, 2624, 1024, 4, 2, 0, 3),     # more columns, last size of the streaming tiles
     (257, 2624, 1088, 4, 4, 0, 4),     # and a third row tile of one row
     (130, 256, 2048, 4, 2, 0, 3),      # F = 8 H
