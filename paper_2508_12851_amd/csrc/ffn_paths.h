@@ -148,16 +148,21 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   return FfnPath::kPrefillShort;
 }
 
-// Whether the gate/up GEMM of a kPrefill batch reads its tokens from a copy in row order (expert_ffn.hip, pack_tokens_kernel).
-// The copy costs 4 H bytes of traffic per row and a launch; what it saves grows with the 4 H F
-// operations of the row's gate/up products.  Layers whose down projection may cut its last round, from
-// 2.2e10 elements of rows x H x F on (layer with the copy against without: 600 tokens, 2 picks, of
-// 3072 x 6144, 2.3e10, 216 against 231 us; of 1024 x 14336, 1.8e10, 184 / 178; of 2048 x 8192, 2.0e10, 192 / 190).
+// Whether the gate/up GEMM of a kPrefill batch reads its tokens from a copy in row order
+// (expert_ffn.hip, pack_tokens_kernel).  The copy costs 4 H bytes of traffic per row and a launch; what
+// it saves grows with the 4 H F operations of the row's gate/up products.  Layers whose down projection
+// may cut its last round, tiled weights: from 2.2e10 elements of rows x H x F on (layer with the copy
+// against without: 600 tokens, 2 picks, of 3072 x 6144, 2.3e10, 216 against 231 us; of 1024 x 14336, 1.8e10,
+// 184 / 178; of 2048 x 8192, 2.0e10, 192 / 190).  Row-major weights arrive as half lines too, and the GEMM
+// waits for those first: from 1.1e11 on (4096 x 14336, all hosted, 560 tokens, 6.6e10, 859 / 799 us, 800 tokens,
+// 9.4e10, 934 / 904, 1400 tokens, 1.6e11, 1126 / 1153; 4096 x 4096, 5 hosted, 800 tokens, 2.7e10, 231 / 218).
+constexpr size_t kPackTiled = 22000000000, kPackRowMajor = 110000000000;
 static inline bool pack_rows_pays(const prism_layer_desc& d, int T) {
   const size_t rows = (size_t)T * (d.top_k + d.n_shared);
+  const size_t from = d.weight_layout == PRISM_WEIGHTS_TILED ? kPackTiled : kPackRowMajor;
   // (the places lie behind the rows, in the partial sums' region: four fp32 rows per token and more)
-  return slicing_shape(d) && T > kStreamMaxTokens && T <= 512 * d.hidden &&
-         rows * d.hidden * d.ffn >= (size_t)22000000000 && align_up(rows, 16) * d.hidden * 2 < 0xFFFF0000ull;
+  return slicing_shape(d) && T > kStreamMaxTokens && T <= 512 * d.hidden && rows * d.hidden * d.ffn >= from &&
+         align_up(rows, 16) * d.hidden * 2 < 0xFFFF0000ull;
 }
 
 }  // namespace prism

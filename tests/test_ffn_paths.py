@@ -20,7 +20,7 @@ def test_path_of_the_usual_sizes(H, F, E, k, S, T, tiled, path):
 
 
 def test_cut_and_copy_of_the_usual_sizes():
-    assert cuts_last_round(4096, 14336, 8, 2, 0, 4096) and packs_rows(4096, 14336, 8, 2, 0, 4096)
+    assert cuts_last_round(4096, 14336, 8, 2, 0, 4096) and packs_rows(4096, 14336, 8, 2, 0, 4096, True)
     assert not cuts_last_round(2048, 1408, 60, 4, 4, 8192) and not packs_rows(2048, 1408, 60, 4, 4, 8192)
     assert cuts_last_round(4096, 4096, 16, 2, 0, 400)       # too many row tiles for the split path
 
@@ -59,3 +59,12 @@ def test_lines_of_the_few_rows_tiles(H, F, E, k, S, T, path):
 ])
 def test_lines_of_the_split_tiles(H, T, path):
     assert ffn_path(H, 8192, 8, 2, 0, T) == path
+
+
+@pytest.mark.parametrize("H,F,T,tiled,packs", [
+    (4096, 14336, 512, True, False), (4096, 14336, 513, True, True),
+    (4096, 14336, 513, False, False), (4096, 14336, 936, False, False), (4096, 14336, 937, False, True),
+    (4096, 4096, 800, False, False), (2048, 8192, 655, True, False), (2048, 8192, 656, True, True),
+])
+def test_lines_of_the_token_row_copy(H, F, T, tiled, packs):
+    assert packs_rows(H, F, 8, 2, 0, T, tiled) == packs
