@@ -42,6 +42,8 @@ constexpr int kBK = 16;                  // contraction elements per k-tile
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * kWave;
 constexpr int kXcds = 8;
+constexpr int kMaxGridX = 1 << 22;       // workgroups in one row of the grid
+static_assert((long long)kMaxGridX * kThreads < (1LL << 32) && kMaxGridX % kXcds == 0, "a row the hardware takes, whole XCD turns");
 constexpr int kRowBytes = kBK * 4;
 constexpr int kStageBytes = (kBM + kBN) * kRowBytes;         // one wavefront's k-tile
 constexpr int kRedPitch = kBN + 4;                           // floats; rows start in different banks
@@ -103,7 +105,8 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p, int 
   // Consecutive workgroups go to the 8 XCDs in turn; every XCD takes a contiguous eighth of the
   // items, row tiles running fastest, so that the row tiles of an expert read its weight rows
   // through one L2.
-  const int item = (int)(blockIdx.x % kXcds) * (int)(gridDim.x / kXcds) + (int)(blockIdx.x / kXcds);
+  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x, wgs = gridDim.x * gridDim.y;   // (gridDim.x % 8 == 0)
+  const int item = (int)(wg % kXcds * (wgs / kXcds) + wg / kXcds);
   if (item >= n_items) return;
   const int ct = item / n_row_tiles;
   const RowTile rt = find_row_tile(p, item - ct * n_row_tiles);
@@ -305,11 +308,15 @@ prism_status launch_f32_gemm(const F32Args& a, hipStream_t st) {
   // row tiles there can be: a full one per 64 assignments, and one that is not per expert with rows
   const long long row_tiles = (long long)A / kBM + std::min(a.E, A) + (long long)a.S * ceil_div(a.T, kBM);
   const long long items = row_tiles * ceil_div(GATED ? a.F : a.H, GATED ? kBN / 2 : kBN);
-  if (items > 0x7FFFFF00LL) return PRISM_ERR_UNSUPPORTED;   // (operands of terabytes)
+  // One dimension of a grid may hold fewer than 2^32 threads: beyond kMaxGridX workgroups they stand in
+  // several rows of equal length.  (2^31 items, each for up to 64 x 32 elements of h, are beyond any memory.)
+  if (items >= 0x7FFF0000LL) return PRISM_ERR_UNSUPPORTED;
+  const unsigned down = (unsigned)((items + kMaxGridX - 1) / kMaxGridX);
+  const unsigned across = (unsigned)align_up((size_t)((items + down - 1) / down), kXcds);
   static LdsLimitOnce lds_limit;   // one per instantiation
   if (!raise_lds_limit(lds_limit, (const void*)ffn_f32_kernel<GATED>, kLdsBytes)) return PRISM_ERR_LAUNCH;
-  const unsigned blocks = (unsigned)((items + kXcds - 1) / kXcds * kXcds);
-  hipLaunchKernelGGL(ffn_f32_kernel<GATED>, dim3(blocks), dim3(kThreads), kLdsBytes, st, a, (int)row_tiles, (int)items);
+  hipLaunchKernelGGL(ffn_f32_kernel<GATED>, dim3(across, down), dim3(kThreads), kLdsBytes, st, a,
+                     (int)row_tiles, (int)items);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }

@@ -55,3 +55,34 @@ def test_f32_ffn_edges(T, H, F, rows, S):
     assert (y[off[E]:A] == -7.0).all()           # rows without an assignment are not written
     for s in range(S):
         check(y[A + s * T:A + (s + 1) * T], ffn(x, w[E + s]))
+
+
+def test_f32_ffn_of_more_tiles_than_one_grid_dimension_holds():
+    """16392 row tiles x 512 column tiles = 8.4 million workgroups of 512 threads, more than 2^32 threads in a row
+    (h takes 69 GB).  Every row written, rows at the edges of every expert against 64-bit arithmetic."""
+    import paper_2508_12851_amd as P
+    T, H, F, E = 131072, 64, 16384, 8
+    A = T * E                                    # every token picks every expert
+    gen = torch.Generator(device="cuda").manual_seed(5)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda") / (shape[-1] ** 0.5 if len(shape) == 2 and shape != (T, H) else 1)
+
+    x = normal(T, H)
+    w = [(normal(F, H), normal(F, H), normal(H, F)) for _ in range(E)]
+    desc = P.make_desc(H, F, E, E, 0, "f32")
+    off = torch.arange(0, A + 1, T, dtype=torch.int32, device="cuda")
+    tok = torch.arange(T, dtype=torch.int32, device="cuda")
+    src = torch.cat([tok * E + e for e in range(E)])
+    y = torch.full((A, H), float("nan"), device="cuda")
+    P.prism_expert_ffn(desc, x, P.WeightTable(w, []), src, off, P.alloc_workspace(desc, T), y=y)
+    assert bool(torch.isfinite(y).all())
+    picks = torch.cat([torch.arange(0, 130), torch.arange(T - 130, T), torch.arange(0, T, 997)]).cuda()
+    for e in range(E):
+        g, u, d = (m.double() for m in w[e])
+        a = x[picks].double()
+        z = a @ g.T
+        ref = (z / (1 + torch.exp(-z)) * (a @ u.T)) @ d.T
+        got = y[e * T:(e + 1) * T][picks].double()
+        # 4 + 2 + F / 128 + 3 roundings of 2^-24, independent: sqrt(137) * 6e-8 = 7e-7 of a sum's norm; three sums
+        assert float((got - ref).norm() / ref.norm()) <= 2e-6
