@@ -186,6 +186,7 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   if (slice_kt != f.slice_kt2) return PRISM_ERR_INVALID_ARG;   // the schedule would hold slice entries
   constexpr bool kCanSlice = !SPLIT_DOWN && C2::BM == kSliceTile;   // as shapes_of
   static_assert(!kCanSlice || (C2::BN == kSliceTile && C2::BK == 32), "sum_slices_kernel assumes the prefill tile");
+  static_assert(!kCanSlice || C1::BK == 32, "a gate/up k-tile reads one 64-byte row of the tiles of the token copy");
   if (!schedules_built) PRISM_TRY(gg::launch_build_schedules(d, local_offsets, T, tiles, st));
 
   GemmArgs g1{};
