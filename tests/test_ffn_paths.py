@@ -68,3 +68,24 @@ def test_lines_of_the_split_tiles(H, T, path):
 ])
 def test_lines_of_the_token_row_copy(H, F, T, tiled, packs):
     assert packs_rows(H, F, 8, 2, 0, T, tiled) == packs
+
+
+def test_random_cases_span_the_paths():
+    """The random parity cases reach every path, those of wide and of streaming layers the ones they are drawn for."""
+    from collections import Counter
+
+    from random_cases import N_STREAMING_CASES, N_WIDE_CASES, draw_case, draw_streaming_case, draw_wide_case
+
+    def args(kw, tiled):
+        return kw["H"], kw["F"], kw["E"], kw["k"], kw["S"], kw["T"], tiled
+
+    layers = [(kw, tiled) for kw, _, tiled in map(draw_case, range(32)) if kw["dtype"] == "bf16"]
+    wide = list(map(draw_wide_case, range(N_WIDE_CASES)))
+    streaming = list(map(draw_streaming_case, range(N_STREAMING_CASES)))
+    assert all(cuts_last_round(*args(*c)) for c in wide)
+    count = Counter(ffn_path(*args(*c)) for c in streaming)
+    for path in ("kDecode", "kDecodeTiled", "kStream", "kSplitSquare", "kSplitWide"):
+        assert count[path] >= 2, count
+    assert {ffn_path(*args(*c)) for c in layers + wide + streaming} == {
+        "kDecodeTiled", "kDecode", "kDecodeShort", "kStream", "kSplitSquare", "kSplitWide", "kFewRows64",
+        "kFewRows128", "kPrefill", "kPrefillShort"}

@@ -3,15 +3,15 @@ conventions and weight layouts (all within the documented limits): what the hand
 of the other files might miss.  Every case prints its parameters before it runs.
 
 The output error is max |a - ref| / (|ref| + rms(ref)) with the rms of the whole batch, for every
-stage of every case but one: the layer output of the cases in random_cases.PER_ROW_CASES is
-measured against the rms of the token's own row, because the bf16 roundings the layer is defined
+stage of every case but two: the layer output of the cases in random_cases.PER_ROW_CASES and
+PER_ROW_STREAMING_CASES is measured against the rms of the token's own row, because the bf16 roundings the layer is defined
 with exceed the bar against the batch rms there in exact arithmetic (shown on the CPU by
 tests/test_error_measure.py, which also shows that no other case needs it)."""
 import numpy as np
 import pytest
 
 from prism_inputs import make_config, make_inputs
-from random_cases import N_CASES, PER_ROW_CASES, draw_case
+from random_cases import N_CASES, N_STREAMING_CASES, N_WIDE_CASES, PER_ROW_CASES, PER_ROW_STREAMING_CASES, draw_case
 
 from gpu_util import check_layer, oracle_layer, run_layer, weight_table
 
@@ -105,7 +105,7 @@ def test_separate_calls_parity_on_a_random_shape(i):
     print(f"case {i}: n_local {nl}, n_remote {nr}: all stages agree")
 
 
-@pytest.mark.parametrize("i", range(12))
+@pytest.mark.parametrize("i", range(N_WIDE_CASES))
 def test_layer_parity_on_a_random_wide_shape(i):
     """Prefill batches whose down projection may have its last round of items cut along the
     contraction (F >= 4096): whole layer against the oracle, whole-batch error measure."""
@@ -120,11 +120,11 @@ def test_layer_parity_on_a_random_wide_shape(i):
     print(f"wide case {i}: out err {err:.3g}, n_local {ref.dispatch.n_local}, n_remote {ref.dispatch.n_remote}")
 
 
-@pytest.mark.parametrize("i", range(24))
+@pytest.mark.parametrize("i", range(N_STREAMING_CASES))
 def test_layer_parity_on_a_random_streaming_shape(i):
-    """Batches of 1 to 352 tokens of wide layers, where the expert FFN streams the weights once and
+    """Batches of 1 to 512 tokens of wide layers, where the expert FFN streams the weights once and
     splits the down projection's contraction by a count chosen on the device: whole layer against
-    the oracle, whole-batch error measure."""
+    the oracle; error measure of the whole batch, but for the cases in PER_ROW_STREAMING_CASES."""
     from random_cases import draw_streaming_case
     kw, tiled = draw_streaming_case(i)
     print(f"streaming case {i}: {kw} tiled={tiled}", flush=True)
@@ -132,6 +132,6 @@ def test_layer_parity_on_a_random_streaming_shape(i):
     inp = make_inputs(cfg)
     ref = oracle_layer(inp)
     o = run_layer(cfg, inp, wt=weight_table(inp, tiled=tiled), weight_layout="tiled" if tiled else "row_major")
-    err = check_layer(cfg, o, ref)
+    err = check_layer(cfg, o, ref, per_row=i in PER_ROW_STREAMING_CASES)
     print(f"streaming case {i}: out err {err:.3g}, n_local {ref.dispatch.n_local}, n_remote {ref.dispatch.n_remote}")
 
