@@ -257,9 +257,7 @@ prism_status prism_moe_layer_traced(const prism_layer_desc* desc, const void* x,
   const hipStream_t st = (hipStream_t)stream;
   void* const* ev = stage_events;
   const int32_t* n_splits = nullptr;   // set if the down projection is left as contraction slices
-  if (SplitRoutePlan plan;
-      // h and y lie side by side and are written by the GEMMs only
-      plan_split_route(*desc, T, ws.h, (size_t)((char*)ws.part - (char*)ws.h), &plan)) {
+  if (SplitRoutePlan plan; plan_split_route(*desc, T, ws, &plan)) {
     trace(ev, PRISM_STAGE_ROUTE, 0, st);
     PRISM_TRY(launch_split_route(*desc, x, w_router, router_bias, T, topk_idx, topk_gate, plan, st));
     trace(ev, PRISM_STAGE_ROUTE, 1, st);

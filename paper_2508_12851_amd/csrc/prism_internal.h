@@ -47,7 +47,7 @@ struct Workspace {
   void* y;                 // [(A + S*T) * H] layer dtype: expert outputs
   float* part;             // batches up to kStreamMaxTokens: [max_splits(T)][A + S*T][H] fp32 partial sums
   float* slice_part;       // larger batches of wide layers: 256 partial tiles of 256 x 256 fp32 (cut last round of the down projection)
-  double* route_part;      // decode batches: [token tiles][kRouteMaxHSplit][route_col_tiles][64][4] fp64
+  double* route_part;      // decode batches: kRouteMaxHSplit partial sums of the logits, fp64, tokens and experts in tiles of 16
   bool h_tiled;            // h in 16 x 32 tiles (grouped_gemm.h, "Intermediate")
   size_t total;
 };
@@ -174,7 +174,8 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
                              hipStream_t st, int32_t* tiles = nullptr,
                              bool* schedules_built = nullptr);
 
-// bf16 batches inside the whole layer (all but decode batches of few experts): the router as two launches.  The
+// bf16 batches inside the whole layer, but for decode batches of at most 16 experts (launch_decode_front_end) and large
+// batches of at most 64 (launch_route; so do shapes whose h and y cannot hold the sums): the router as two launches.  The
 // first spreads (token tile, experts, hidden elements) over the chip and leaves fp64 partial
 // logits, the second sums them, picks the experts and counts them per block of assignments.
 struct SplitRoutePlan {
@@ -183,9 +184,8 @@ struct SplitRoutePlan {
   double* partial;        // [hs][T][16 * route_col_tiles] partial logits
   int32_t* block_hist;    // [n_blocks][E]
 };
-// Whether that serves a batch of T tokens: scratch / scratch_bytes is memory nothing else uses until
-// the GEMMs start (16-byte aligned).
-bool plan_split_route(const prism_layer_desc& d, int T, void* scratch, size_t scratch_bytes, SplitRoutePlan* plan);
+// Whether that serves a batch of T tokens, and how.
+bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, SplitRoutePlan* plan);
 prism_status launch_split_route(const prism_layer_desc& d, const void* x, const void* w_router, const float* bias,
                                 int T, int32_t* topk_idx, float* topk_gate, const SplitRoutePlan& plan,
                                 hipStream_t st);
@@ -196,7 +196,7 @@ prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk
                                   int32_t* inv, const SplitRoutePlan& plan, int32_t* counts,
                                   int64_t* counts_accum, hipStream_t st, int32_t* tiles);
 
-// schedules_built: the two schedules in tiles already exist (decode front end).
+// schedules_built: the two schedules in tiles already exist.
 // h_tiled: layout of h (Workspace).
 // x_rows: the workspace's y (which may be the y given).  Batches of more than kStreamMaxTokens may keep a copy
 // of the token rows there, and at the start of the partial sums behind it, until the gate/up GEMM is done.

@@ -17,12 +17,17 @@
 // group, so the k best experts are picked right there with xor-shuffle
 // arg-max reductions over (logit, index) pairs, four tokens at a time.
 //
-// Decode batches (at most 64 tokens, bf16) have only 1..4 token tiles, which would
-// leave the router on 1..4 compute units.  There the hidden dimension is also
-// split over workgroups: route_kernel<PARTIAL> writes each workgroup's fp64 tile
-// to memory, and a single-workgroup kernel sums those in a fixed order, finishes
-// the routing and, being alone on the critical path anyway, goes on to do the
-// placement split and to build the work schedules of the two grouped GEMMs.
+// One workgroup per token tile leaves most of the machine idle unless the batch has thousands of
+// tokens, so inside the whole layer the work is spread further:
+//   decode batches (at most 64 tokens, bf16) of at most 16 experts: route_kernel<PARTIAL> splits the
+//     hidden dimension over workgroups and writes each one's fp64 tile to memory, and a
+//     single-workgroup kernel sums those in a fixed order, finishes the routing and, being alone
+//     on the critical path anyway, goes on to do the placement split and to build the work
+//     schedules of the two grouped GEMMs (decode_front_end_kernel);
+//   other bf16 batches: route_staged_kernel<SPLIT> spreads token tiles, experts and hidden elements,
+//     route_pick_kernel sums the parts, picks, and counts the picks per block of the placement.
+// prism_route on its own, fp32 layers and the largest batches take one launch (route_staged_kernel
+// for bf16 batches of more than 64 tokens and at most 64 experts, else route_kernel).
 #include "dispatch_device.h"
 #include "prism_internal.h"
 #include "schedule.h"
@@ -174,39 +179,34 @@ __device__ __forceinline__ void finish_group(const double (&s)[NT], const float 
                                              bool has_bias, int t, int T, int E, int k, int gate_mode,
                                              float* __restrict__ logits, int32_t* topk_idx,
                                              float* __restrict__ topk_gate, int* s_counts,
-                                             int32_t* s_idx = nullptr, int* picked = nullptr) {
+                                             int* picked = nullptr) {
   double s1[1][NT];
   float b1[1][NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) { s1[0][n] = s[n]; b1[0][n] = b[n]; }
   const int t1[1] = {t};
   finish_groups<NT, 1>(s1, b1, has_bias, t1, T, E, k, gate_mode, logits, topk_idx, topk_gate, s_counts,
-                       s_idx, picked);
+                       nullptr, picked);
 }
 
 // The same for a tile of 16 tokens held by one wavefront in the accumulator layout of
 // v_mfma_f64_16x16x4: register v of lane (r, q) is token 4 v + q, expert 16 n + r.
-// v_mask (wave-uniform): bit v set = handle the four tokens 4v + q of the tile, so
-// several wavefronts can share one tile's work.
 template <int NT>
-__device__ __forceinline__ void finish_tile(const f64x4 (&acc)[NT], int tok0, int v_mask,
+__device__ __forceinline__ void finish_tile(const f64x4 (&acc)[NT], int tok0,
                                             const float* __restrict__ bias, int T, int E, int k,
                                             int bias_group_tokens, int gate_mode,
                                             float* __restrict__ logits, int32_t* topk_idx,
-                                            float* __restrict__ topk_gate, int* s_counts,
-                                            int32_t* s_idx = nullptr) {
+                                            float* __restrict__ topk_gate, int* s_counts) {
   const int q = (threadIdx.x & 63) >> 4;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    if (!((v_mask >> v) & 1)) continue;
     const int t = tok0 + 4 * v + q;
     double s[NT];
     float b[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) s[n] = acc[n][v];
     load_bias_group<NT>(bias, t, T, E, bias_group_tokens, b);
-    finish_group<NT>(s, b, bias != nullptr, t, T, E, k, gate_mode, logits, topk_idx, topk_gate,
-                     s_counts, s_idx);
+    finish_group<NT>(s, b, bias != nullptr, t, T, E, k, gate_mode, logits, topk_idx, topk_gate, s_counts);
   }
 }
 
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_kernel(
     return;
   }
 
-  finish_tile<NT>(acc, tok0, 0xF, bias, T, E, k, bias_group_tokens, gate_mode, logits, topk_idx,
+  finish_tile<NT>(acc, tok0, bias, T, E, k, bias_group_tokens, gate_mode, logits, topk_idx,
                   topk_gate, counts != nullptr ? s_counts : nullptr);
   if (counts == nullptr) return;   // the caller derives the counts from the dispatch histogram
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // this wavefront's LDS atomics, then its reads
@@ -321,8 +321,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_kernel(
   }
 }
 
-// Router for bf16 batches of more than 64 tokens and at most 64 experts: operands staged
-// through LDS.
+// Router with its operands staged through LDS (bf16).
 //
 // Loading operands from global memory straight in the MFMA layout (route_kernel) makes every
 // quarter of a load instruction touch 16 rows, 16 bytes of each, and the vector cache then
@@ -601,7 +600,7 @@ __global__ __launch_bounds__(kPickThreads) void route_pick_kernel(
   const int blk0 = tok0 * k / block_len;
   const int cut = (blk0 + 1) * block_len;          // first assignment of the next block
   int picked = -1;
-  finish_group<NT>(s, b, bias != nullptr, t, T, E, k, gate_mode, nullptr, topk_idx, topk_gate, nullptr, nullptr, &picked);
+  finish_group<NT>(s, b, bias != nullptr, t, T, E, k, gate_mode, nullptr, topk_idx, topk_gate, nullptr, &picked);
   if (picked >= 0) atomicAdd(&s_hist[t * k + r >= cut ? 1 : 0][picked], 1);
   lds_barrier();
   const int e = threadIdx.x;
@@ -624,7 +623,7 @@ __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v) {
 // the layer, so the steps hand their results to each other in LDS (expert indices, local
 // offsets): no step waits for a store to memory or re-reads what the step before wrote there.
 constexpr int kFrontThreads = dispatch_dev::kThreads;
-template <int NT>
+constexpr int kFrontMaxExperts = 16;   // one expert tile
 __global__ __launch_bounds__(kFrontThreads) void decode_front_end_kernel(
     const double* __restrict__ partial, int n_hsplit, const float* __restrict__ bias, int T, int E,
     int k, int S, int bias_group_tokens, int gate_mode, int32_t* topk_idx,
@@ -632,6 +631,7 @@ __global__ __launch_bounds__(kFrontThreads) void decode_front_end_kernel(
     const uint8_t* __restrict__ mask, const dispatch_dev::SplitOut o,
     int32_t* __restrict__ local_src, int32_t* __restrict__ remote_src, int32_t* __restrict__ inv,
     const gg::SchedParams p0, const gg::SchedParams p1) {
+  constexpr int NT = kFrontMaxExperts / 16;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int n_tiles = (T + kTokPerBlock - 1) / kTokPerBlock;
@@ -644,65 +644,44 @@ __global__ __launch_bounds__(kFrontThreads) void decode_front_end_kernel(
   // four wavefronts busy.  The logits are the sums over the router's slices, in slice order.
   static_assert(kFrontThreads / kWave == 4, "one wavefront per accumulator register index");
   constexpr int kMaxTiles = kDecodeMaxTokens / kTokPerBlock;
-  if constexpr (NT <= 4) {
-    // All threads share the slice sums -- element j of tile t is a 4-double vector of the
-    // NT * 64 that make a tile, its 16 slice loads issued together -- and leave them in LDS.
-    __shared__ __align__(32) double s_sum[kMaxTiles * NT * 256];
-    for (int item = threadIdx.x; item < n_tiles * NT * 64; item += kFrontThreads) {
-      const int tile = item / (NT * 64), j = item % (NT * 64);
-      const double* base = partial + (size_t)tile * n_hsplit * (NT * 256) + j * 4;
-      f64x4 part[kRouteMaxHSplit];
+  // All threads share the slice sums -- element j of tile t is a 4-double vector of the
+  // NT * 64 that make a tile, its 16 slice loads issued together -- and leave them in LDS.
+  __shared__ __align__(32) double s_sum[kMaxTiles * NT * 256];
+  for (int item = threadIdx.x; item < n_tiles * NT * 64; item += kFrontThreads) {
+    const int tile = item / (NT * 64), j = item % (NT * 64);
+    const double* base = partial + (size_t)tile * n_hsplit * (NT * 256) + j * 4;
+    f64x4 part[kRouteMaxHSplit];
 #pragma unroll
-      for (int y = 0; y < kRouteMaxHSplit; ++y)   // slices past the end re-read the last one (unused)
-        part[y] = *reinterpret_cast<const f64x4*>(base + (size_t)min(y, n_hsplit - 1) * (NT * 256));
-      f64x4 sum = {0.0, 0.0, 0.0, 0.0};
+    for (int y = 0; y < kRouteMaxHSplit; ++y)   // slices past the end re-read the last one (unused)
+      part[y] = *reinterpret_cast<const f64x4*>(base + (size_t)min(y, n_hsplit - 1) * (NT * 256));
+    f64x4 sum = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int y = 0; y < kRouteMaxHSplit; ++y) {
-        const bool on = y < n_hsplit;
+    for (int y = 0; y < kRouteMaxHSplit; ++y) {
+      const bool on = y < n_hsplit;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sum[v] += on ? part[y][v] : 0.0;
-      }
-      *reinterpret_cast<f64x4*>(s_sum + (size_t)tile * (NT * 256) + j * 4) = sum;
+      for (int v = 0; v < 4; ++v) sum[v] += on ? part[y][v] : 0.0;
     }
-    lds_barrier();
-    // Wavefront w routes tokens 4w + q of every tile, two tiles per pass side by side.  The
-    // second tile of the last pass may not exist: its tokens are past T, so nothing is stored.
-    static_assert(kMaxTiles % 2 == 0, "tile pairs stay inside s_sum");
-    const int q = lane >> 4;
-    for (int tile = 0; tile < n_tiles; tile += 2) {
-      double s2[2][NT];
-      float b2[2][NT];
-      int t2[2];
+    *reinterpret_cast<f64x4*>(s_sum + (size_t)tile * (NT * 256) + j * 4) = sum;
+  }
+  lds_barrier();
+  // Wavefront w routes tokens 4w + q of every tile, two tiles per pass side by side.  The
+  // second tile of the last pass may not exist: its tokens are past T, so nothing is stored.
+  static_assert(kMaxTiles % 2 == 0, "tile pairs stay inside s_sum");
+  const int q = lane >> 4;
+  for (int tile = 0; tile < n_tiles; tile += 2) {
+    double s2[2][NT];
+    float b2[2][NT];
+    int t2[2];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        t2[u] = (tile + u) * kTokPerBlock + 4 * wave + q;
+    for (int u = 0; u < 2; ++u) {
+      t2[u] = (tile + u) * kTokPerBlock + 4 * wave + q;
 #pragma unroll
-        for (int n = 0; n < NT; ++n)   // register v = wave of lane `lane` of the accumulator tile
-          s2[u][n] = s_sum[(size_t)(tile + u) * (NT * 256) + n * 256 + lane * 4 + wave];
-        load_bias_group<NT>(bias, t2[u], T, E, bias_group_tokens, b2[u]);
-      }
-      finish_groups<NT, 2>(s2, b2, bias != nullptr, t2, T, E, k, gate_mode, nullptr, topk_idx, topk_gate,
-                           nullptr, s_idx);
+      for (int n = 0; n < NT; ++n)   // register v = wave of lane `lane` of the accumulator tile
+        s2[u][n] = s_sum[(size_t)(tile + u) * (NT * 256) + n * 256 + lane * 4 + wave];
+      load_bias_group<NT>(bias, t2[u], T, E, bias_group_tokens, b2[u]);
     }
-  } else {
-    // Too many expert columns for LDS: every wavefront sums the component it needs itself.
-    for (int tile = 0; tile < n_tiles; ++tile) {
-      const double* base = partial + (size_t)tile * n_hsplit * (NT * 256) + lane * 4 + wave;
-      f64x4 acc[NT];
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        double part[kRouteMaxHSplit];
-#pragma unroll
-        for (int y = 0; y < kRouteMaxHSplit; ++y)
-          part[y] = base[(size_t)min(y, n_hsplit - 1) * (NT * 256) + n * 256];
-        double sum = 0.0;
-#pragma unroll
-        for (int y = 0; y < kRouteMaxHSplit; ++y) sum += y < n_hsplit ? part[y] : 0.0;
-        acc[n] = f64x4{sum, sum, sum, sum};         // finish_tile reads component `wave` only
-      }
-      finish_tile<NT>(acc, tile * kTokPerBlock, 1 << wave, bias, T, E, k, bias_group_tokens, gate_mode,
-                      nullptr, topk_idx, topk_gate, nullptr, s_idx);
-    }
+    finish_groups<NT, 2>(s2, b2, bias != nullptr, t2, T, E, k, gate_mode, nullptr, topk_idx, topk_gate,
+                         nullptr, s_idx);
   }
   lds_barrier();   // s_idx is complete (the copy in memory is for the caller)
   dispatch_dev::dispatch_place_block<false, kFineChunk>(s_idx, T * k, E, mask, nullptr, 1, 1, 0, o, local_src,
@@ -782,11 +761,9 @@ prism_status launch_typed(const prism_layer_desc& d, const void* x, const void* 
   const dim3 block(kWavesPerBlock * kWave);
   // the 256-expert tile needs 128 KiB of LDS for the partial sums
   if (nt > 8) {
-    static LdsLimitOnce lds_full, lds_partial;
+    static LdsLimitOnce lds_limit;
     const int bytes = (kWavesPerBlock / 2) * 16 * 4 * 64 * 8;
-    if (!raise_lds_limit(lds_full, (const void*)route_kernel<TIn, 16, false>, bytes) ||
-        !raise_lds_limit(lds_partial, (const void*)route_kernel<TIn, 16, true>, bytes))
-      return PRISM_ERR_LAUNCH;
+    if (!raise_lds_limit(lds_limit, (const void*)route_kernel<TIn, 16, false>, bytes)) return PRISM_ERR_LAUNCH;
   }
 #define PRISM_ROUTE_LAUNCH(NT, PARTIAL)                                                          \
   hipLaunchKernelGGL((route_kernel<TIn, NT, PARTIAL>), grid, block,                              \
@@ -794,17 +771,15 @@ prism_status launch_typed(const prism_layer_desc& d, const void* x, const void* 
                      bias, T, d.hidden, E, d.top_k, d.bias_group_tokens, d.gate_mode, logits,    \
                      idx, gate,                                                                  \
                      counts, (unsigned long long*)accum, h_span, partial)
-#define PRISM_ROUTE_CASE(NT)                                                                     \
-  do {                                                                                           \
-    if (partial != nullptr) PRISM_ROUTE_LAUNCH(NT, true);                                        \
-    else PRISM_ROUTE_LAUNCH(NT, false);                                                          \
-  } while (0)
-  if (nt <= 1) PRISM_ROUTE_CASE(1);
-  else if (nt <= 2) PRISM_ROUTE_CASE(2);
-  else if (nt <= 4) PRISM_ROUTE_CASE(4);
-  else if (nt <= 8) PRISM_ROUTE_CASE(8);
-  else PRISM_ROUTE_CASE(16);
-#undef PRISM_ROUTE_CASE
+  if (partial != nullptr) {   // decode front end: one expert tile
+    if (nt != 1) return PRISM_ERR_INVALID_ARG;
+    if constexpr (sizeof(TIn) == 2) PRISM_ROUTE_LAUNCH(1, true);
+  }
+  else if (nt <= 1) PRISM_ROUTE_LAUNCH(1, false);
+  else if (nt <= 2) PRISM_ROUTE_LAUNCH(2, false);
+  else if (nt <= 4) PRISM_ROUTE_LAUNCH(4, false);
+  else if (nt <= 8) PRISM_ROUTE_LAUNCH(8, false);
+  else PRISM_ROUTE_LAUNCH(16, false);
 #undef PRISM_ROUTE_LAUNCH
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
@@ -835,13 +810,9 @@ prism_status launch_route(const prism_layer_desc& d, const void* x, const void* 
                                 counts_accum, nullptr, st);
 }
 
-bool plan_split_route(const prism_layer_desc& d, int T, void* scratch, size_t scratch_bytes, SplitRoutePlan* plan) {
-  // Decode batches of at most 16 experts: the two launches of the decode front end are as good as the
-  // three of this one (32 tokens x 8 experts: layer 300 against 299 us).  Beyond, its one workgroup
-  // takes long over the slice sums and the picks of every token (layer, 24 tokens x 64 experts 112
-  // against 105 us, 64 x 60: 119 against 107, 1 x 64: 53 against 48, 64 x 256: 153 against 94).
-  if (T <= kDecodeMaxTokens && d.n_experts <= 16) return false;
+bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, SplitRoutePlan* plan) {
   if (d.dtype != PRISM_BF16 || T <= 0 || (uint64_t)T * d.hidden * 2 >= 0xFFFF0000ull) return false;
+  if (decode_front_end_applies(d, T)) return false;
   // With 32-token workgroups for three quarters of the CUs the router in one launch is as good
   // (8192 tokens x 60 experts: 51 us with its histogram launch of 5, split 52 + 6 us, and the
   // layer 1 % slower).
@@ -853,8 +824,13 @@ bool plan_split_route(const prism_layer_desc& d, int T, void* scratch, size_t sc
   plan->chunk = A <= 16 * kFineChunk ? kFineChunk : kDispatchChunk;
   plan->sub = dispatch_dev::sub_chunks(A, plan->chunk);
   plan->n_blocks = ceil_div(A, plan->sub * plan->chunk);
-  const size_t hist_bytes = align_up((size_t)plan->n_blocks * d.n_experts * 4, 256);
   const size_t part_bytes = (size_t)T * route_col_tiles(d.n_experts) * 16 * 8;   // one part of the hidden dimension
+  // Decode batches have one block and a region of kRouteMaxHSplit parts.  Others borrow h and y, which lie
+  // side by side and are written by the GEMMs only.
+  const bool decode = T <= kDecodeMaxTokens;
+  const size_t hist_bytes = decode ? 0 : align_up((size_t)plan->n_blocks * d.n_experts * 4, 256);
+  const size_t scratch_bytes = decode ? part_bytes * kSplitRouteMaxParts : (size_t)((char*)ws.part - (char*)ws.h);
+  static_assert(kSplitRouteMaxParts <= kRouteMaxHSplit && kDecodeMaxTokens * PRISM_MAX_TOPK <= kFineChunk, "decode regions");
   if (hist_bytes + part_bytes > scratch_bytes) return false;
   // The shape of a workgroup: the one with the least estimated time.  A SIMD holds two of its
   // wavefronts, and a v_mfma_f64_16x16x4 takes 64 clocks, the conversion of an operand element
@@ -879,8 +855,8 @@ bool plan_split_route(const prism_layer_desc& d, int T, void* scratch, size_t sc
       }
     }
   }
-  plan->block_hist = (int32_t*)scratch;
-  plan->partial = (double*)((char*)scratch + hist_bytes);
+  plan->block_hist = decode ? ws.block_hist : (int32_t*)ws.h;
+  plan->partial = decode ? ws.route_part : (double*)((char*)ws.h + hist_bytes);
   return true;
 }
 
@@ -911,7 +887,11 @@ prism_status launch_split_route(const prism_layer_desc& d, const void* x, const 
 }
 
 bool decode_front_end_applies(const prism_layer_desc& d, int T) {
-  return d.dtype == PRISM_BF16 && T > 0 && T <= kDecodeMaxTokens;
+  // Beyond 16 experts the spread router's three launches are ahead: the front end's one workgroup takes long
+  // over the slice sums and the picks of every token (layer, 24 tokens x 64 experts 112 against 105 us, 64 x
+  // 60: 119 against 107, 1 x 64: 53 against 48, 64 x 256: 153 against 94).  Up to 16 they are even (32
+  // tokens x 8 experts: layer 300 against 299 us).
+  return d.dtype == PRISM_BF16 && T > 0 && T <= kDecodeMaxTokens && d.n_experts <= kFrontMaxExperts;
 }
 
 prism_status launch_decode_front_end(const prism_layer_desc& d, const void* x, const void* w_router,
@@ -935,19 +915,9 @@ prism_status launch_decode_front_end(const prism_layer_desc& d, const void* x, c
   gg::SchedParams p0, p1;
   gg::ffn_sched_params(d, T, tiles, &p0, &p1);
   trace(stage_events, PRISM_STAGE_DISPATCH, 0, st);
-#define PRISM_FRONT_CASE(NT)                                                                     \
-  hipLaunchKernelGGL((decode_front_end_kernel<NT>), dim3(1), dim3(kFrontThreads), 0, st,        \
-                     route_part, n_hsplit, bias, T, E, d.top_k, d.n_shared,                     \
-                     d.bias_group_tokens, d.gate_mode, topk_idx, topk_gate, mask, o, local_src,  \
-                     remote_src,                                                                 \
-                     inv, p0, p1)
-  const int nt = route_col_tiles(E);
-  if (nt <= 1) PRISM_FRONT_CASE(1);
-  else if (nt <= 2) PRISM_FRONT_CASE(2);
-  else if (nt <= 4) PRISM_FRONT_CASE(4);
-  else if (nt <= 8) PRISM_FRONT_CASE(8);
-  else PRISM_FRONT_CASE(16);
-#undef PRISM_FRONT_CASE
+  hipLaunchKernelGGL(decode_front_end_kernel, dim3(1), dim3(kFrontThreads), 0, st, route_part, n_hsplit, bias, T, E,
+                     d.top_k, d.n_shared, d.bias_group_tokens, d.gate_mode, topk_idx, topk_gate, mask, o,
+                     local_src, remote_src, inv, p0, p1);
   PRISM_CHECK_LAUNCH();
   trace(stage_events, PRISM_STAGE_DISPATCH, 1, st);
   return PRISM_OK;

@@ -1,5 +1,6 @@
-"""GPU: the router of batches of more than 64 tokens inside the layer (experts and hidden elements spread over
-workgroups, picks counted per placement block) at its edges, against the oracle, whole numbers bit for bit."""
+"""GPU: the router inside the layer (experts and hidden elements spread over workgroups, picks counted per placement
+block; decode batches of at most 16 experts: the decode front end) at its edges, against the oracle, whole numbers
+bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +20,10 @@ pytestmark = pytest.mark.gpu
     (1, 256, 17, 1),         # decode batches: fewest experts, one token
     (24, 2048, 64, 6),
     (64, 192, 256, 8),
-    (3, 64, 256, 1),         # partial logits too large: decode front end
+    (3, 64, 256, 1),         # partial logits larger than the FFN buffers: a decode batch has a region for them
+    (16, 64, 33, 1),
+    (64, 4160, 65, 8),       # long hidden dimension, most assignments
+    (64, 320, 16, 2),        # last expert count of the decode front end
 ])
 @pytest.mark.parametrize("gates", ["renormalized", "softmax_all"])
 def test_split_router_in_layer(T, H, E, k, gates):
