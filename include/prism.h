@@ -291,14 +291,17 @@ prism_status prism_layer_permutation(const prism_layer_desc* desc, int32_t T, co
  * is a HOST array of 2 * PRISM_N_STAGES hipEvent_t handles (as void*), or
  * NULL.  For stage s, if stage_events[2s] and stage_events[2s+1] are both
  * non-NULL, the first is recorded on `stream` right before and the second
- * right after that stage's kernels: the router kernel, the dispatch kernels,
- * the gate/up grouped GEMM alone, the down grouped GEMM, the combine kernel.
- * For decode-sized bf16 batches (T <= 64) the work is cut differently: ROUTE
- * is the router GEMM with the hidden dimension split over workgroups,
- * DISPATCH the single-workgroup kernel that finishes the routing, does the
- * placement split and builds the GEMM work lists, and COMBINE also sums the
- * contraction slices of the down projection.  Nothing else differs from
- * prism_moe_layer, which is this call with stage_events == NULL.
+ * right after that stage's kernels: the router, the dispatch kernels (with the
+ * copy of the token rows that large batches of wide layers multiply), the
+ * gate/up grouped GEMM alone, the down grouped GEMM with the sums of its last
+ * round, the combine kernel.  For decode-sized bf16 batches (T <= 64) of at most
+ * 16 experts the work is cut differently: ROUTE is the router GEMM with the
+ * hidden dimension split over workgroups, DISPATCH the single-workgroup kernel
+ * that finishes the routing, does the placement split and builds the GEMM work
+ * lists.  In batches whose down projection is split along its contraction
+ * (decode sizes, and up to 512 tokens of wide layers) COMBINE also sums the
+ * slices.  Nothing else differs from prism_moe_layer, which is this call with
+ * stage_events == NULL.
  */
 #define PRISM_STAGE_ROUTE 0
 #define PRISM_STAGE_DISPATCH 1

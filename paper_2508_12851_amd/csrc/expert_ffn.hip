@@ -202,13 +202,13 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   g1.c_tiled = h_tiled;
   g1.a_pitch = (uint32_t)d.hidden * 2;
   g1.a_kstep = 64;
-  trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
   if (kCanSlice && pack_rows_pays(d, T)) {
     int32_t* row_places = (int32_t*)((uint8_t*)x_rows + align_up(rows, 16) * d.hidden * 2);
     hipLaunchKernelGGL(pack_tokens_kernel, dim3((unsigned)ceil_div(rows, 16), (unsigned)ceil_div(d.hidden, 1024)),
                        dim3(256), 0, st, (const uint4*)x, local_src, local_offsets, d.n_experts, A, rows, T, d.top_k,
                        d.hidden, (uint4*)x_rows, row_places);
     PRISM_CHECK_LAUNCH();
+    trace(stage_events, PRISM_STAGE_DISPATCH, 1, st);   // the copy counts as dispatch: its end is recorded anew
     g1.A = (const uint16_t*)x_rows;
     g1.a_bytes = (uint32_t)(align_up(rows, 16) * d.hidden * 2);
     g1.a_tiled = 1;
@@ -218,6 +218,7 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
     g1.a_pitch = 64;
     g1.a_kstep = 1024;
   }
+  trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
   PRISM_TRY((gg::launch_gemm<C1::BM, C1::BN, 2, 2, C1::BK, C1::STAGES, true, false, ROTATE, STREAM_B>(
       g1, gg::sched_capacity(d, T, C1::BM, nt1), st)));
   trace(stage_events, PRISM_STAGE_FFN_UP, 1, st);
