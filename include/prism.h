@@ -40,8 +40,8 @@
  *   - Errors are return codes only.  Arguments are validated on the host
  *     before anything is launched: a NULL required pointer, T < 0, k < 1 or
  *     k > E give PRISM_ERR_INVALID_ARG; sizes outside the compiled limits
- *     give PRISM_ERR_UNSUPPORTED; a workspace smaller than
- *     prism_workspace_bytes() gives PRISM_ERR_WORKSPACE_TOO_SMALL; a failed
+ *     give PRISM_ERR_UNSUPPORTED; a workspace too small for the call (see
+ *     prism_workspace_bytes) gives PRISM_ERR_WORKSPACE_TOO_SMALL; a failed
  *     kernel launch gives PRISM_ERR_LAUNCH.  T == 0 is PRISM_OK and writes
  *     zero counts / offsets / totals.
  *   - Inputs are assumed finite (not checked).
@@ -134,6 +134,11 @@ const char* prism_status_string(prism_status s);
  * aligned; its contents between calls are irrelevant; two calls that use the
  * same workspace must not overlap in time (run them on one stream, or give
  * each stream its own workspace).
+ * bf16: the size rounds the T*k + S*T rows of the FFN intermediate up to a
+ * multiple of 16, for a layout that the down projection reads faster.  A
+ * workspace that lacks no more than those extra rows (each F elements, the sum
+ * rounded up to 256 bytes) is accepted too; the intermediate is then
+ * row-major, with the same results bit for bit.
  */
 prism_status prism_workspace_bytes(const prism_layer_desc* desc, int32_t max_tokens, size_t* bytes);
 
@@ -249,9 +254,10 @@ prism_status prism_moe_layer(const prism_layer_desc* desc, const void* x, const 
  * array of PRISM_STATIC_SCRATCH_BYTES that lives in the library's device image (every GPU
  * the process uses holds its own copy until the process ends).  The call allocates and frees
  * nothing, and neither does anything it calls.
- *   - Accepted while prism_workspace_bytes(desc, T) <= PRISM_STATIC_SCRATCH_BYTES (32 MiB:
- *     e.g. decode batches of up to 64 tokens of a 4096 x 14336 layer with 8 experts, 2048
- *     tokens of a 256 x 448 layer); beyond that PRISM_ERR_WORKSPACE_TOO_SMALL, nothing launched.
+ *   - Accepted while the workspace the call needs without the extra rows described at
+ *     prism_workspace_bytes fits PRISM_STATIC_SCRATCH_BYTES (32 MiB: e.g. decode batches of
+ *     up to 64 tokens of a 4096 x 14336 layer with 8 experts, 2048 tokens of a 256 x 448
+ *     layer); beyond that PRISM_ERR_WORKSPACE_TOO_SMALL, nothing launched.
  *   - The first call on a device looks up that device's address of the array (one
  *     hipGetSymbolAddress; PRISM_ERR_LAUNCH if it fails); make that call outside any capture.
  *   - All calls on one GPU share the one array, which keeps the previous call's contents
