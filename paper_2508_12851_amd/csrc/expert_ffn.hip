@@ -14,8 +14,9 @@
 // LDS ring filled by direct-to-LDS loads), in the tile shapes chosen at the end
 // of this file.  GEMM1 loads the gate rows and the up rows of the same f range
 // into one tile, so silu(gate)*up is a register epilogue and only h is written.
-// Activation rows of GEMM1 are gathered through local_src (no permuted copy of
-// x is materialised).  fp32 layers: expert_ffn_f32.hip.
+// Activation rows of GEMM1 are gathered through local_src; large batches of wide
+// layers first copy them in row order (pack_tokens_kernel).  Which tiles a batch
+// takes: ffn_paths.h.  fp32 layers: expert_ffn_f32.hip.
 #include "grouped_gemm.h"
 #include "prism_internal.h"
 

@@ -3,8 +3,8 @@
 //   GATED   h[r, f] = silu( x[tok(r)] . W_gate^e[f] ) * ( x[tok(r)] . W_up^e[f] )
 //   plain   y[r, n] = h[r] . W_down^e[n]
 //
-// Bound: v_mfma_f32_32x32x2_f32 (157 TFLOP/s on 256 CUs) once an expert has a few dozen rows, the
-// weight stream below that.
+// Bound: the matrix cores' fp32 rate (v_mfma_f32_32x32x2_f32: 157 TFLOP/s nominal on 256 CUs) once an expert
+// has a few dozen rows, the weight stream below that.
 //
 // Split: a workgroup owns 64 rows of one expert x 64 weight rows (GATED: 32 gate rows and the 32 up
 // rows of the same f), and its 8 wavefronts split the contraction: each multiplies its own eighth in
@@ -13,11 +13,11 @@
 // workgroup, two wavefronts per SIMD).  The next k-tile travels from memory to registers during the MFMAs of this
 // one (32 MFMAs of 64 clocks per wavefront and k-tile).
 //
-// Sums: fp32 results must not get worse with the length of the contraction, so no accumulator runs
-// over it.  Four products are added in the matrix core, the four partial sums of a k-tile pairwise,
-// the k-tile sums in the order of the tiles, the eighths as a tree.  Against 64 bits this is as close
-// as the sum over 64 lanes and a tree that this kernel replaced (relative 2-norm of the error, random
-// operands, 256 / 1024 / 2048 terms: 7.8e-8 / 9.2e-8 / 1.06e-7, before 7.9e-8 / 1.0e-7 / 1.23e-7).
+// Sums: fp32 results must not get worse than those of the kernel that this one replaced (64 lane sums
+// of K / 64 terms, then a tree).  Four products are added in the matrix core, the four partial sums of
+// a k-tile pairwise, the k-tile sums of a wavefront one after the other (K / 128 terms, the only chain
+// that grows with the contraction), the eighths as a tree.  Relative 2-norm of the error against 64 bits,
+// random operands, 256 / 1024 / 2048 terms: 7.8e-8 / 9.2e-8 / 1.06e-7, before 7.9e-8 / 1.0e-7 / 1.23e-7.
 //
 // One wavefront per output element with the products on the vector ALU (the kernel before) read
 // every weight row once per activation row: at 500 tokens of a 1024 x 2048 layer, 5 of 8 experts

@@ -100,8 +100,8 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   // workgroups.  Layer, weights from HBM, 128 x 128 against 128 x 256: 4096 x 14336, 66 tokens, 1 hosted
   // 94 / 128 us; 200 tokens, 1 hosted, evenly spread picks 104 / 143 (the other way with 5 hosted, 412 /
   // 376); 3072 x 8192, 96 tokens, 2 hosted 83 / 101; 2048 x 8192, 66 tokens, 5 hosted 116 / 132, and 131 if
-  // dealt in rectangles with temporal loads.  16 shapes, 1 to 8 hosted: up to 160 tokens 128 x 128 is
-  // ahead by 6 % on average and by up to 27 %, from there to 256 the averages are even.
+  // dealt in rectangles with temporal loads.  16 shapes, 1 to 8 hosted, against the better of those two for
+  // the shape: up to 160 tokens ahead by 6 % on average and up to 27 %, from there to 256 even on average.
   if (stream_tiles_apply(d, T) && T <= kMidMaxTokens) return FfnPath::kStream;
   // Beyond, the row tiles of an expert stand next to each other in an XCD's list, so that the later
   // ones find the weight tile in the L2, and tiles of 128 activation rows x 256 weight rows bring twice
@@ -137,7 +137,8 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   //   once per 64 rows: with 4 of them at 200 tokens the larger tiles are ahead, 128 against 140.  So
   //   do the experts of that peer: 1000 rows 65 us in either, 1500 rows 79 against 62.
   if (few_rows_per_expert(d, T)) {
-    if ((long long)T * d.top_k <= (long long)kVeryFewRows * d.n_experts && (long long)T * d.n_shared <= 512 && T <= kVeryFewTokens)
+    if ((long long)T * d.top_k <= (long long)kVeryFewRows * d.n_experts && (long long)T * d.n_shared <= 512 &&
+        T <= kVeryFewTokens)
       return FfnPath::kFewRows64;
     return FfnPath::kFewRows128;
   }
