@@ -1,6 +1,6 @@
-"""Short text summaries of rocprofv3 runs of bench.py, as kept under profiles/.
+"""Short text summaries of rocprofv3 runs of bench.py (or of another program), as kept under profiles/.
 
-    python -m paper_2508_12851_amd.profile_summary kernel-stats <rocprofv3 -d dir> <workload> [--args "..."]
+    python -m paper_2508_12851_amd.profile_summary kernel-stats <rocprofv3 -d dir> <workload> [--args "..." | --program "..."]
     python -m paper_2508_12851_amd.profile_summary traffic <dir with fetch/ write/ cal_fetch/ cal_write/> <workload>
     python -m paper_2508_12851_amd.profile_summary counters <rocprofv3 -d dir> <name> --title "..." --command "..."
 
@@ -65,13 +65,13 @@ def _write(name, lines):
     print("->", os.path.relpath(path, ROOT))
 
 
-def kernel_stats(run_dir, workload, bench_args):
+def kernel_stats(run_dir, workload, bench_args, program=""):
     rows = list(csv.DictReader(open(_one(os.path.join(run_dir, "**", "*kernel_stats.csv")))))
     cmd = ("cd /tmp && export TMPDIR=/tmp && rocprofv3 --kernel-trace --stats -d <out> --output-format csv -- "
-           f"python3 /root/repo/bench.py {bench_args}").rstrip()
+           f"{program or 'python3 /root/repo/bench.py ' + bench_args}").rstrip()
     out = [f"rocprofv3 kernel statistics, workload {workload}, one MI355X", *provenance(),
            f"command: {cmd}",
-           "(every layer kernel is launched warm-up + timed steps times, plus the per-step timing calls)", "",
+           "" if program else "(every layer kernel is launched warm-up + timed steps times, plus the per-step timing calls)", "",
            f"{'kernel':<100} {'calls':>6} {'avg_us':>10} {'min_us':>10} {'max_us':>10} {'pct':>7}"]
     for r in rows:
         if float(r["Percentage"]) < 0.05:
@@ -156,6 +156,7 @@ def main():
     sub = ap.add_subparsers(dest="what", required=True)
     a = sub.add_parser("kernel-stats")
     a.add_argument("run_dir"); a.add_argument("workload"); a.add_argument("--args", default="")
+    a.add_argument("--program", default="", help="what was profiled, if not bench.py")
     b = sub.add_parser("traffic")
     b.add_argument("base"); b.add_argument("workload"); b.add_argument("--args", default="")
     c = sub.add_parser("counters")
@@ -163,7 +164,7 @@ def main():
     c.add_argument("--command", required=True)
     args = ap.parse_args()
     if args.what == "kernel-stats":
-        kernel_stats(args.run_dir, args.workload, args.args)
+        kernel_stats(args.run_dir, args.workload, args.args, args.program)
     elif args.what == "traffic":
         traffic(args.base, args.workload, args.args)
     else:
