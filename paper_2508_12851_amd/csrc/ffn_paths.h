@@ -9,10 +9,10 @@
 
 namespace prism {
 
-constexpr int kDecodeMaxTokens = 64;    // batches up to this size take the weight-streaming path
-constexpr int kMidMaxTokens = 256;      // ... in 128 x 128 tiles with non-temporal weight loads up to this one (ffn_path)
-constexpr int kSquareMaxTokens = 448;   // ... in 128 x 128 tiles, if their hidden size is 1025 to 2560 (ffn_path)
-constexpr int kStreamMaxTokens = 512;   // wide bf16 layers: batches up to this size also split the down projection
+constexpr int kDecodeMaxTokens = 64;    // batches up to this size take the decode tiles
+constexpr int kStreamMaxTokens = 512;   // wide bf16 layers: batches up to this size split the down projection as those do,
+constexpr int kMidMaxTokens = 256;      // up to this one in 128 x 128 tiles with non-temporal weight loads,
+constexpr int kSquareMaxTokens = 448;   // up to this one in 128 x 128 tiles if the hidden size is 1025 to 2560 (ffn_path)
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -35,26 +35,32 @@ static inline bool down_slicing_applies(const prism_layer_desc& d, int T) {
   return slicing_shape(d) && T >= kSliceMinTokens;
 }
 
+// Work items of the down projection in prefill tiles: column tiles x row tiles, the latter estimated
+// from what the host knows (half of the experts hosted, rows spread evenly).
+static inline int prefill_down_items(const prism_layer_desc& d, int T) {
+  const int row_tiles = ceil_div(T * d.top_k, 256) + d.n_experts / 2 + d.n_shared * ceil_div(T, 256);
+  return row_tiles * ceil_div(d.hidden, 256);
+}
+
 // Batches between the decode and the prefill sizes whose down projection in prefill tiles would
-// have too few items for the machine: column tiles x row tiles, the latter estimated from what the
-// host knows (half of the experts hosted, rows spread evenly).  Layers of many small experts have
-// enough items at any batch size.
+// have too few items for the machine.  Layers of many small experts have enough at any batch size.
 static inline bool stream_tiles_apply(const prism_layer_desc& d, int T) {
   if (T <= kDecodeMaxTokens || T > kStreamMaxTokens || d.hidden < 256 || d.ffn < 1024) return false;
-  const int row_tiles = ceil_div(T * d.top_k, 256) + d.n_experts / 2 + d.n_shared * ceil_div(T, 256);
-  return row_tiles * ceil_div(d.hidden, 256) <= 128;
+  return prefill_down_items(d, T) <= 128;
 }
 
 // Rows per expert: what an even spread of the picks over all experts would give, all the host knows.
 // Layers whose down projection may cut its last round keep the prefill tiles, which the cut fills better.
-constexpr int kFewRows = 112;            // most rows per expert of the 128-row tiles
-constexpr int kFewRowsOnePick = 2560;    // ... and most rows of a batch of one pick per token
+constexpr int kFewRows = 112;            // most rows per expert of the 128-row tiles ...
+constexpr int kFewRowsFewItems = 144;    // ... if prefill tiles would leave compute units without an item
+constexpr int kFewRowsOnePick = 2560;    // most rows of a batch of one pick per token in them
 constexpr int kVeryFewRows = 16;         // most rows per expert of the 64-row tiles
-constexpr int kVeryFewTokens = 1024;     // ... and most tokens: an expert has at most that many rows
+constexpr int kVeryFewTokens = 1024;     // most tokens in them: an expert has at most that many rows
 static inline bool few_rows_per_expert(const prism_layer_desc& d, int T) {
   if (T <= kDecodeMaxTokens || d.hidden < 192 || d.ffn < 192 || slicing_shape(d)) return false;
   if (d.top_k == 1 && T > kFewRowsOnePick) return false;
-  return (long long)T * d.top_k <= (long long)kFewRows * d.n_experts;
+  const int most = prefill_down_items(d, T) <= 256 ? kFewRowsFewItems : kFewRows;
+  return (long long)T * d.top_k <= (long long)most * d.n_experts;
 }
 
 enum class FfnPath {
@@ -127,7 +133,10 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   //   (22 rows) 172 -> 148 us, 600 tokens 221 -> 179; 256 experts, 8 picks, 800 tokens 173 -> 158; whole
   //   layer, 160 of 256 hosted, 3500 tokens (109 rows) 327 -> 314.  From 120 rows on the two are even or
   //   the full tiles ahead (evenly spread picks, layer: 60 experts, 2150 tokens, 143 rows, 454 against
-  //   478 us; 64 experts, 8 hosted, 1300 tokens, 122 rows, 122 against 134).
+  //   478 us; 64 experts, 8 hosted, 1300 tokens, 122 rows, 122 against 134) where those make items enough.
+  //   In smaller layers the lower tiles win up to 144 rows by their number (314 random layers of 113 to 144
+  //   rows, mean time against the full tiles: up to 128 items of the down projection in full tiles -22 %,
+  //   129 to 192 -16 %, 193 to 256 -11 %, 257 to 384 -5 % and up to +8 %, beyond 800 -1 % and up to +9 %).
   //   One pick per token is what a peer asks for: all rows are for the hosted experts, however few
   //   they are, and one with hundreds of rows pays for every row tile (8 of 256 experts of 2048 x 1408
   //   hosted, FFN: 2200 rows 94 -> 77 us, 3000 rows 92 -> 100, 4096 rows 100 -> 117).

@@ -47,6 +47,10 @@ def test_weight_streaming_batches_take_the_small_tiles(H, F, E, k, S, T):
     (1024, 1024, 256, 8, 0, 3585, "kPrefill"),
     (2048, 1408, 60, 4, 4, 2150, "kPrefill"),
     (2048, 1408, 64, 6, 2, 1500, "kPrefill"),
+    (896, 448, 32, 6, 0, 768, "kFewRows128"),         # small layers, 144 rows per expert: (18 + 16) x 4 full-tile items
+    (896, 448, 32, 6, 0, 769, "kPrefill"),
+    (2048, 448, 32, 6, 0, 682, "kFewRows128"),        # 128 rows, 32 x 8 items
+    (2048, 448, 32, 6, 0, 683, "kPrefill"),           # 33 x 8
 ])
 def test_lines_of_the_few_rows_tiles(H, F, E, k, S, T, path):
     assert ffn_path(H, F, E, k, S, T) == path

@@ -22,10 +22,10 @@ pytestmark = pytest.mark.gpu
     (385, 192, 192, 48, 2, 0, 40),     # one pick over it
     (128, 192, 704, 32, 4, 4, 20),     # 512 shared rows
     (129, 192, 704, 32, 4, 4, 20),     # 516
-    (1152, 320, 448, 24, 3, 0, 24),    # 144 rows per expert
+    (1152, 320, 448, 24, 3, 0, 24),    # 144 rows per expert: last size of the 128-row tiles of a small layer
     (1153, 320, 448, 24, 3, 1, 24),
-    (896, 320, 448, 24, 3, 0, 24),     # 112 rows per expert: last size of the 128-row tiles
-    (897, 320, 448, 24, 3, 1, 24),
+    (3584, 320, 192, 256, 8, 0, 200),  # 112 rows per expert of a layer with many: last size of the 128-row tiles
+    (3585, 320, 192, 256, 8, 0, 200),
     # One pick per token, the popular experts with several row tiles.  (All experts hosted: with a share p of
     # the tokens local, the rms of the batch is sqrt(p) of a local row's, and a rounding error of 3e-3 of the
     # row's rms counts as 3e-3 / sqrt(p) against the bar of 2e-2; one token of 1025 would count 9e-2.)
