@@ -3,25 +3,24 @@
 //   GATED   h[r, f] = silu( x[tok(r)] . W_gate^e[f] ) * ( x[tok(r)] . W_up^e[f] )
 //   plain   y[r, n] = h[r] . W_down^e[n]
 //
-// Bound: the matrix cores' fp32 rate (v_mfma_f32_32x32x2_f32: 157 TFLOP/s nominal on 256 CUs) once an expert
-// has a few dozen rows, the weight stream below that.
+// Bound: the matrix cores.  In fp32 (v_mfma_f32_32x32x2_f32) they do 157 TFLOP/s nominal, in bf16 sixteen
+// times that, so every fp32 operand is taken as the sum of three bf16 parts of 8 bits and a product as the six
+// products of parts that reach 2^-24 of it (three of the nine are left out, 2^-26 and below).
 //
 // Split: a workgroup owns 64 rows of one expert x 64 weight rows (GATED: 32 gate rows and the 32 up
 // rows of the same f), and its 8 wavefronts split the contraction: each multiplies its own eighth in
 // 16-wide k-tiles that it stages through 8 KiB of LDS of its own, so the k-loop has no workgroup
-// barrier, and a tile of even the smallest layer is spread over all four SIMDs (242 registers: one
-// workgroup, two wavefronts per SIMD).  The next k-tile travels from memory to registers during the MFMAs of this
-// one (32 MFMAs of 64 clocks per wavefront and k-tile).
+// barrier, and a tile of even the smallest layer is spread over all four SIMDs (one workgroup, two
+// wavefronts per SIMD).  The next k-tile travels from memory to registers during the products of this one (24
+// MFMAs of 32 clocks and about as much conversion, which the SIMD's other wavefront overlaps).  The workgroups are
+// persistent: the first operands of the next item are asked for before the sums of this one.
 //
-// Sums: fp32 results must not get worse than those of the kernel that this one replaced (64 lane sums
-// of K / 64 terms, then a tree).  Four products are added in the matrix core, the four partial sums of
-// a k-tile pairwise, the k-tile sums of a wavefront one after the other (K / 128 terms, the only chain
-// that grows with the contraction), the eighths as a tree.  Relative 2-norm of the error against 64 bits,
-// random operands, 256 / 1024 / 2048 terms: 7.8e-8 / 9.2e-8 / 1.06e-7, before 7.9e-8 / 1.0e-7 / 1.23e-7.
-//
-// One wavefront per output element with the products on the vector ALU (the kernel before) read
-// every weight row once per activation row: at 500 tokens of a 1024 x 2048 layer, 5 of 8 experts
-// hosted, gate/up + down took 1173 + 1105 us.
+// Sums: fp32 results must not get worse than those of fp32 products.  The leading parts' products
+// have accumulators of their own (16 terms per rounding, chains of K / 128), the other five products, 2^-8 and
+// below, share a second set, and the eighths are added as a tree.  Relative 2-norm of the FFN's error against
+// 64 bits, N(0, 1) tokens, H x F: 256 x 512 1.27e-7 (in fp32 1.50e-7), 1024 x 2048 1.72e-7 (1.78e-7), 2048 x 1024
+// 1.79e-7 (1.86e-7), 4096 x 512 2.18e-7 (2.10e-7): contractions beyond 2048 stay in fp32, and so does a
+// wavefront's eighth whose sums are not finite, because an infinity has no parts.
 #include "prism_internal.h"
 
 namespace prism {
@@ -42,14 +41,14 @@ constexpr int kBK = 16;                  // contraction elements per k-tile
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * kWave;
 constexpr int kXcds = 8;
-constexpr int kMaxGridX = 1 << 22;       // workgroups in one row of the grid
-static_assert((long long)kMaxGridX * kThreads < (1LL << 32) && kMaxGridX % kXcds == 0, "a row the hardware takes, whole XCD turns");
+constexpr int kWorkgroups = 256;         // persistent: one per CU
+constexpr int kSplitMaxK = 2048;         // longest contraction multiplied in bf16 parts
 constexpr int kRowBytes = kBK * 4;
 constexpr int kStageBytes = (kBM + kBN) * kRowBytes;         // one wavefront's k-tile
 constexpr int kRedPitch = kBN + 4;                           // floats; rows start in different banks
 constexpr int kRedFloats = kBM * kRedPitch;                  // one wavefront's partial tile
-constexpr int kLdsBytes = kWaves / 2 * kRedFloats * 4;
-static_assert(kLdsBytes >= kWaves * kStageBytes, "the partial tiles replace the k-tiles");
+constexpr int kLdsBytes = kWaves * kStageBytes + kWaves / 2 * kRedFloats * 4;   // k-tiles, partial tiles
+static_assert(kLdsBytes <= 160 * 1024, "LDS per workgroup");
 
 // Rows of fp32 matrices start at any multiple of 4 bytes (F need not be a multiple of 4).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -64,80 +63,132 @@ struct RowTile {
   int tok_base;    // shared experts: token of the first row; routed ones: -1
 };
 
-// Row tile number b: the tiles of the routed experts in expert order, then those of the shared
-// ones.  Every wavefront finds it for itself (4 experts per lane, one scan).
-__device__ __forceinline__ RowTile find_row_tile(const F32Args& p, int b) {
+// The row tiles: those of the routed experts in expert order, then those of the shared ones.  Every
+// wavefront holds the offsets of four experts per lane and finds a tile by its number with a ballot.
+struct RowTiles {
+  int off[5];      // offsets of experts 4 lane .. 4 lane + 4
+  int before;      // row tiles of the experts before lane's
+  int routed;      // row tiles of all routed experts
+};
+__device__ __forceinline__ int tiles_of(int rows) { return (rows + kBM - 1) / kBM; }
+__device__ __forceinline__ RowTiles load_row_tiles(const F32Args& p) {
   const int lane = threadIdx.x & 63;
-  int off[5];
+  RowTiles r;
 #pragma unroll
-  for (int j = 0; j < 5; ++j) off[j] = p.local_offsets[min(4 * lane + j, p.E)];
+  for (int j = 0; j < 5; ++j) r.off[j] = p.local_offsets[min(4 * lane + j, p.E)];
   int tiles = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) tiles += (off[j + 1] - off[j] + kBM - 1) / kBM;
+  for (int j = 0; j < 4; ++j) tiles += tiles_of(r.off[j + 1] - r.off[j]);
   const int incl = wave_inclusive_scan(tiles);
-  const int total = __builtin_amdgcn_readlane(incl, 63);
-  if (b < total) {
-    int rel = b - (incl - tiles), e = 0, start = 0, count = 0;
-    const unsigned long long mine = __ballot(rel >= 0 && rel < tiles);
+  r.before = incl - tiles;
+  r.routed = __builtin_amdgcn_readlane(incl, 63);
+  return r;
+}
+__device__ __forceinline__ RowTile row_tile(const F32Args& p, const RowTiles& r, int b) {
+  if (b < r.routed) {
+    int rel = b - r.before, e = 0, start = 0, count = 0;
+    bool mine = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int t = (off[j + 1] - off[j] + kBM - 1) / kBM;
+      const int t = tiles_of(r.off[j + 1] - r.off[j]);
       if (rel >= 0 && rel < t) {
-        e = 4 * lane + j;
-        start = off[j] + rel * kBM;
-        count = min(kBM, off[j + 1] - start);
+        mine = true;
+        e = 4 * (threadIdx.x & 63) + j;
+        start = r.off[j] + rel * kBM;
+        count = min(kBM, r.off[j + 1] - start);
       }
       rel -= t;
     }
-    const int owner = __ffsll(mine) - 1;
+    const int owner = __ffsll((unsigned long long)__ballot(mine)) - 1;
     return RowTile{__builtin_amdgcn_readlane(e, owner), __builtin_amdgcn_readlane(start, owner),
                    __builtin_amdgcn_readlane(count, owner), -1};
   }
-  const int per_shared = (p.T + kBM - 1) / kBM;
-  const int s = (b - total) / per_shared, tok = (b - total - s * per_shared) * kBM;
-  if (s >= p.S) return RowTile{-1, 0, 0, -1};
+  const int per_shared = tiles_of(p.T), s = (b - r.routed) / per_shared, tok = (b - r.routed - s * per_shared) * kBM;
   return RowTile{p.E + s, p.T * (p.top_k + s) + tok, min(kBM, p.T - tok), tok};
 }
 
+// An fp32 value is the sum of three bf16 values: the nearest one, the nearest one to what is left, and
+// the rest, whose 24 - 8 - 8 bits fit (exact unless the value is below 2^-110 or overflows when rounded).  The
+// differences come from a dot product with (-1, 0) or (0, -1), one instruction instead of unpacking
+// a half and subtracting it.  (From registers: the compiler's inline constant for (0, -1) is not that pair.)
+struct Parts {
+  bf16x8 v[3];
+};
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t minus_lo, uint32_t minus_hi, uint32_t (&o)[3]) {
+  float r[2] = {a, b};
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const bf16x2 h = {(bf16_t)r[0], (bf16_t)r[1]};
+    o[u] = __builtin_bit_cast(uint32_t, h);
+    if (u < 2) {
+      r[0] = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, minus_lo), r[0], false);
+      r[1] = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, minus_hi), r[1], false);
+    }
+  }
+}
+
 template <bool GATED>
-__global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p, int n_row_tiles, int n_items) {
+__global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the bf16 dot product exists in device code only
   extern __shared__ __align__(16) float smem[];
+  const int K = GATED ? p.H : p.F, N = GATED ? p.F : p.H;
+  constexpr int kCols = GATED ? kBN / 2 : kBN;      // output columns of the tile
   // Consecutive workgroups go to the 8 XCDs in turn; every XCD takes a contiguous eighth of the
   // items, row tiles running fastest, so that the row tiles of an expert read its weight rows
   // through one L2.
-  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x, wgs = gridDim.x * gridDim.y;   // (gridDim.x % 8 == 0)
-  const int item = (int)(wg % kXcds * (wgs / kXcds) + wg / kXcds);
-  if (item >= n_items) return;
-  const int ct = item / n_row_tiles;
-  const RowTile rt = find_row_tile(p, item - ct * n_row_tiles);
-  if (rt.g < 0) return;
+  const RowTiles tiles = load_row_tiles(p);
+  const int n_row_tiles = tiles.routed + p.S * tiles_of(p.T);
+  const int n_items = n_row_tiles * ((N + kCols - 1) / kCols);
+  const int xcd = blockIdx.x % kXcds, slots = gridDim.x / kXcds;
+  const int item_end = (int)((long long)n_items * (xcd + 1) / kXcds);
+  int item = (int)((long long)n_items * xcd / kXcds) + blockIdx.x / kXcds;
+  if (item >= item_end) return;
 
-  const int K = GATED ? p.H : p.F, N = GATED ? p.F : p.H;
-  constexpr int kCols = GATED ? kBN / 2 : kBN;      // output columns of the tile
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r32 = lane & 31, q = lane >> 5;
 
   // ---- global -> LDS assignment: lane l brings chunk l % 4 (4 elements) of rows l / 4 + 16 i ----
   const int lrow = lane >> 2, chunk = lane & 3;
-  const bool routed = rt.g < p.E;
-  const int gi = routed ? rt.g : rt.g - p.E;
   const float* a_ptr[4];
   uint32_t b_off[4];      // elements (H and F are at most 16384)
+  global_ptr b_lo, b_hi;  // weight rows 0 .. 31 and 32 .. 63
+  // What an item needs from memory before its first operand can be fetched.
+  struct Item {
+    RowTile rt;
+    int ct;
+    int src[4];                  // GATED, routed: entries of local_src of this lane's rows
+    const void* lo;
+    const void* hi;
+  };
+  auto find_item = [&](int it) {
+    Item n;
+    n.ct = it / n_row_tiles;
+    n.rt = row_tile(p, tiles, it - n.ct * n_row_tiles);
+    const bool routed = n.rt.g < p.E;
+    const int gi = routed ? n.rt.g : n.rt.g - p.E;
+    n.lo = GATED ? (routed ? p.wg[gi] : p.swg[gi]) : (routed ? p.wd[gi] : p.swd[gi]);
+    n.hi = GATED ? (routed ? p.wu[gi] : p.swu[gi]) : n.lo;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int br = lrow + 16 * i;
-    const int rr = min(br, rt.row_count - 1);   // rows past the end repeat the last one
-    if (GATED) {
-      const int tok = routed ? p.local_src[rt.row_start + rr] / p.top_k : rt.tok_base + rr;
-      a_ptr[i] = p.x + (size_t)tok * K;
-    } else {
-      a_ptr[i] = p.h + (size_t)(rt.row_start + rr) * K;
+    for (int i = 0; i < 4; ++i)
+      n.src[i] = GATED && routed ? p.local_src[n.rt.row_start + min(lrow + 16 * i, n.rt.row_count - 1)] : 0;
+    return n;
+  };
+  auto set_addresses = [&](const Item& n) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int br = lrow + 16 * i;
+      const int rr = min(br, n.rt.row_count - 1);   // rows past the end repeat the last one
+      if (GATED)
+        a_ptr[i] = p.x + (size_t)(n.rt.g < p.E ? n.src[i] / p.top_k : n.rt.tok_base + rr) * K;
+      else
+        a_ptr[i] = p.h + (size_t)(n.rt.row_start + rr) * K;
+      b_off[i] = (uint32_t)min(n.ct * kCols + br % kCols, N - 1) * (uint32_t)K;
     }
-    b_off[i] = (uint32_t)min(ct * kCols + br % kCols, N - 1) * (uint32_t)K;
-  }
-  const global_ptr b_lo = (global_ptr)(GATED ? (routed ? p.wg[gi] : p.swg[gi]) : (routed ? p.wd[gi] : p.swd[gi]));
-  const global_ptr b_hi = GATED ? (global_ptr)(routed ? p.wu[gi] : p.swu[gi]) : b_lo;   // rows 32 .. 63
+    b_lo = (global_ptr)n.lo;
+    b_hi = (global_ptr)n.hi;
+  };
 
   // this wavefront's k-tiles
   const int n_kt = (K + kBK - 1) / kBK;
@@ -151,6 +202,20 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p, int 
     for (int i = 0; i < 4; ++i) {
       fa[i] = *reinterpret_cast<const f32x4u*>(a_ptr[i] + k);
       fb[i] = *(global_ptr4)((i < 2 ? b_lo : b_hi) + (b_off[i] + k));
+    }
+  };
+  auto fetch_first = [&] {
+    if (kt0 >= kt1) return;
+    if (K >= 4) {
+      fetch(kt0);
+    } else {   // rows of 1 to 3 elements
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          fa[i][e] = a_ptr[i][min(e, K - 1)];
+          fb[i][e] = ((i < 2 ? b_lo : b_hi) + b_off[i])[min(e, K - 1)];
+        }
     }
   };
   // Last k-tile, if the rows end inside it: what was fetched sits d elements further on; zeros past K.
@@ -179,31 +244,8 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p, int 
   uint8_t* const stage = reinterpret_cast<uint8_t*>(smem) + wave * kStageBytes;
   const int wr = lrow * kRowBytes + (chunk ^ ((lrow >> 2) & 3)) * 16;
   const int key = (r32 >> 2) & 3;
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const bool two = rt.row_count > 32;   // tiles of at most 32 rows leave out the second half
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-  if (kt0 < kt1) {
-    if (K >= 4) {
-      fetch(kt0);
-    } else {   // rows of 1 to 3 elements
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          fa[i][e] = a_ptr[i][min(e, K - 1)];
-          fb[i][e] = ((i < 2 ? b_lo : b_hi) + b_off[i])[min(e, K - 1)];
-        }
-    }
-  }
-  for (int kt = kt0; kt < kt1; ++kt) {
+  // puts the k-tile that was fetched into LDS and asks for the next one
+  auto next_k_tile = [&](int kt) {
     if (kt * kBK + kBK > K) cut_tail(kt);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -213,42 +255,117 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p, int 
     // the LDS of a wavefront executes in program order; the fence keeps the compiler to it
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (kt + 1 < kt1) fetch(kt + 1);
-    // Lane (r32, q) holds chunk 2 c + q of its row: MFMA j of pair c consumes element j, i.e. the
-    // elements 8 c + j and 8 c + 4 + j of the k-tile, the same ones on both sides.
-    f32x4 a[2][2], b[2][2];
+  };
+  // Lane (r32, q) holds chunks q and 2 + q of its row, the same elements on both sides.
+  auto read_chunk = [&](int row, int c) {
+    return *reinterpret_cast<const f32x4*>(stage + row * kRowBytes + ((2 * c + q) ^ key) * 16);
+  };
+  uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;   // (-1, 0) and (0, -1)
+  asm volatile("" : "+s"(minus_lo), "+s"(minus_hi));
+  auto read_parts = [&](int row) {
+    u32x4 w[3];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      const int slot = ((2 * c + q) ^ key) * 16;
+      const f32x4 v = read_chunk(row, c);
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        a[s][c] = *reinterpret_cast<const f32x4*>(stage + (s * 32 + r32) * kRowBytes + slot);
-        b[s][c] = *reinterpret_cast<const f32x4*>(stage + (kBM + s * 32 + r32) * kRowBytes + slot);
+      for (int e = 0; e < 2; ++e) {
+        uint32_t o[3];
+        split_pair(v[2 * e], v[2 * e + 1], minus_lo, minus_hi, o);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) w[u][2 * c + e] = o[u];
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    auto multiply = [&](int i) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        f32x16 part[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][u >> 1][2 * (u & 1)], a[i][u >> 1][2 * (u & 1)], zero, 0, 0, 0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][u >> 1][2 * (u & 1) + 1], a[i][u >> 1][2 * (u & 1) + 1],
-                                                         part[u], 0, 0, 0);
-        acc[i][j] += (part[0] + part[1]) + (part[2] + part[3]);
-        // one accumulator at a time: its partial sums take 64 registers until they are added
-        asm volatile("" : "+v"(acc[i][j]));
-      }
-    };
-    multiply(0);
-    if (two) multiply(1);
-  }
+    return Parts{{__builtin_bit_cast(bf16x8, w[0]), __builtin_bit_cast(bf16x8, w[1]), __builtin_bit_cast(bf16x8, w[2])}};
+  };
 
-  // ---- the eighths as a tree: 4..7 into 0..3 through LDS, then the four tiles by all threads ----
+  f32x16 acc[2][2];
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // The products as six bf16 ones, the leading part's in sums of their own.  Tiles of at most 32 rows (two: false)
+  // leave out the second half.
+  auto multiply_parts = [&](bool two) {
+    f32x16 low[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = low[i][j] = zero;
+    for (int kt = kt0; kt < kt1; ++kt) {
+      next_k_tile(kt);
+      const Parts b[2] = {read_parts(kBM + r32), read_parts(kBM + 32 + r32)};
+      auto half = [&](int i) {
+        const Parts a = read_parts(i * 32 + r32);
+        auto mul = [&](f32x16 (&d)[2], int u, int w) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) d[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j].v[w], a.v[u], d[j], 0, 0, 0);
+        };
+        mul(low[i], 2, 0);
+        mul(acc[i], 0, 0);
+        mul(low[i], 1, 1);
+        mul(low[i], 0, 2);
+        mul(low[i], 1, 0);
+        mul(low[i], 0, 1);
+      };
+      half(0);
+      if (two) half(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] += low[i][j];
+  };
+  // The products on the fp32 matrix cores: pairs, the pairs of a k-tile as a tree.  MFMA j of chunk pair c
+  // consumes element j, i.e. the elements 8 c + j and 8 c + 4 + j of the k-tile.
+  auto multiply_f32 = [&](bool two) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = zero;
+    fetch_first();
+    for (int kt = kt0; kt < kt1; ++kt) {
+      next_k_tile(kt);
+      f32x4 a[2][2], b[2][2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          a[s][c] = read_chunk(s * 32 + r32, c);
+          b[s][c] = read_chunk(kBM + s * 32 + r32, c);
+        }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      auto half = [&](int i) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          f32x16 part[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][u >> 1][2 * (u & 1)], a[i][u >> 1][2 * (u & 1)], zero, 0, 0, 0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][u >> 1][2 * (u & 1) + 1], a[i][u >> 1][2 * (u & 1) + 1],
+                                                           part[u], 0, 0, 0);
+          acc[i][j] += (part[0] + part[1]) + (part[2] + part[3]);
+          // one accumulator at a time: its partial sums take 64 registers until they are added
+          asm volatile("" : "+v"(acc[i][j]));
+        }
+      };
+      half(0);
+      if (two) half(1);
+    }
+  };
+  auto all_finite = [&] {
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) z = fmaf(acc[i][j][v], 0.f, z);
+    return __ballot(z != 0.f) == 0;   // (a NaN is not equal to zero)
+  };
+
   // Register v of lane (r32, q): row r32 of the row half, column 8 (v / 4) + 4 q + v % 4.
-  float* const slot = smem + (wave & 3) * kRedFloats + r32 * kRedPitch + q * 4;
+  float* const red = smem + kWaves * kStageBytes / 4;
+  float* const slot = red + (wave & 3) * kRedFloats + r32 * kRedPitch + q * 4;
   auto each_quad = [&](auto&& fn) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -259,47 +376,75 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p, int 
           fn(reinterpret_cast<f32x4*>(slot + i * 32 * kRedPitch + j * 32 + vg * 8), acc[i][j], vg);
   };
   auto put = [](f32x4* d, f32x16& s, int vg) { *d = f32x4{s[vg * 4], s[vg * 4 + 1], s[vg * 4 + 2], s[vg * 4 + 3]}; };
-  __syncthreads();
-  if (wave >= 4) each_quad(put);
-  __syncthreads();
-  if (wave < 4)
-    each_quad([](f32x4* d, f32x16& s, int vg) {
-      const f32x4 o = *d;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[vg * 4 + e] += o[e];
-    });
-  __syncthreads();
-  if (wave < 4) each_quad(put);
-  __syncthreads();
 
-  const int row = threadIdx.x >> 3, c4 = (threadIdx.x & 7) * 4;
-  if (row >= rt.row_count) return;
-  auto total = [&](int col) {
-    f32x4 t[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) t[w] = *reinterpret_cast<const f32x4*>(smem + w * kRedFloats + row * kRedPitch + col);
-    return (t[0] + t[2]) + (t[1] + t[3]);
-  };
-  float* const out = (GATED ? p.h : p.y) + (size_t)(rt.row_start + row) * N;
-  auto store = [&](int n, const f32x4& v) {
-    if (n + 4 <= N) {
-      *reinterpret_cast<f32x4u*>(out + n) = v;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (n + e < N) out[n + e] = v[e];
+  Item cur = find_item(item);
+  set_addresses(cur);
+  fetch_first();
+  while (true) {
+    const bool has_next = item + slots < item_end;
+    item += slots;
+    const Item next = find_item(has_next ? item : item - slots);   // asked for before the products
+    const RowTile rt = cur.rt;
+    const int ct = cur.ct;
+    const bool two = rt.row_count > 32;
+    bool in_f32 = K > kSplitMaxK;
+    if (!in_f32) {
+      multiply_parts(two);
+      // an infinity or NaN is no sum of three parts, nor is a value that rounds up to infinity: once more in fp32
+      in_f32 = !all_finite();
     }
-  };
-  if (GATED) {
-    const f32x4 ag = total(c4), au = total(c4 + kBN / 2);
-    f32x4 o;
+    if (in_f32) multiply_f32(two);
+    if (has_next) {   // the next item's first k-tile travels during the sums of this one
+      set_addresses(next);
+      fetch_first();
+    }
+
+    // ---- the eighths as a tree: 4..7 into 0..3 through LDS, then the four tiles by all threads ----
+    lds_barrier();   // the item before has been read
+    if (wave >= 4) each_quad(put);
+    lds_barrier();
+    if (wave < 4)
+      each_quad([](f32x4* d, f32x16& s, int vg) {
+        const f32x4 o = *d;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = (ag[e] / (1.0f + expf(-ag[e]))) * au[e];
-    store(ct * kCols + c4, o);
-  } else {
-    store(ct * kCols + c4, total(c4));
-    store(ct * kCols + c4 + kBN / 2, total(c4 + kBN / 2));
+        for (int e = 0; e < 4; ++e) s[vg * 4 + e] += o[e];
+        *d = f32x4{s[vg * 4], s[vg * 4 + 1], s[vg * 4 + 2], s[vg * 4 + 3]};
+      });
+    lds_barrier();
+
+    const int row = threadIdx.x >> 3, c4 = (threadIdx.x & 7) * 4;
+    if (row < rt.row_count) {
+      auto total = [&](int col) {
+        f32x4 t[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) t[w] = *reinterpret_cast<const f32x4*>(red + w * kRedFloats + row * kRedPitch + col);
+        return (t[0] + t[2]) + (t[1] + t[3]);
+      };
+      float* const out = (GATED ? p.h : p.y) + (size_t)(rt.row_start + row) * N;
+      auto store = [&](int n, const f32x4& v) {
+        if (n + 4 <= N) {
+          *reinterpret_cast<f32x4u*>(out + n) = v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (n + e < N) out[n + e] = v[e];
+        }
+      };
+      if (GATED) {
+        const f32x4 ag = total(c4), au = total(c4 + kBN / 2);
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (ag[e] / (1.0f + expf(-ag[e]))) * au[e];
+        store(ct * kCols + c4, o);
+      } else {
+        store(ct * kCols + c4, total(c4));
+        store(ct * kCols + c4 + kBN / 2, total(c4 + kBN / 2));
+      }
+    }
+    if (!has_next) break;
+    cur = next;
   }
+#endif
 }
 
 template <bool GATED>
@@ -308,15 +453,13 @@ prism_status launch_f32_gemm(const F32Args& a, hipStream_t st) {
   // row tiles there can be: a full one per 64 assignments, and one that is not per expert with rows
   const long long row_tiles = (long long)A / kBM + std::min(a.E, A) + (long long)a.S * ceil_div(a.T, kBM);
   const long long items = row_tiles * ceil_div(GATED ? a.F : a.H, GATED ? kBN / 2 : kBN);
-  // One dimension of a grid may hold fewer than 2^32 threads: beyond kMaxGridX workgroups they stand in
-  // several rows of equal length.  (2^31 items, each for up to 64 x 32 elements of h, are beyond any memory.)
+  // (2^31 items, each for up to 64 x 32 elements of h, are beyond any memory)
   if (items >= 0x7FFF0000LL) return PRISM_ERR_UNSUPPORTED;
-  const unsigned down = (unsigned)((items + kMaxGridX - 1) / kMaxGridX);
-  const unsigned across = (unsigned)align_up((size_t)((items + down - 1) / down), kXcds);
   static LdsLimitOnce lds_limit;   // one per instantiation
   if (!raise_lds_limit(lds_limit, (const void*)ffn_f32_kernel<GATED>, kLdsBytes)) return PRISM_ERR_LAUNCH;
-  hipLaunchKernelGGL(ffn_f32_kernel<GATED>, dim3(across, down), dim3(kThreads), kLdsBytes, st, a,
-                     (int)row_tiles, (int)items);
+  // one workgroup fits a CU
+  hipLaunchKernelGGL(ffn_f32_kernel<GATED>, dim3((unsigned)std::min<long long>(kWorkgroups, align_up((size_t)items, kXcds))),
+                     dim3(kThreads), kLdsBytes, st, a);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }

@@ -57,6 +57,35 @@ def test_f32_ffn_edges(T, H, F, rows, S):
         check(y[A + s * T:A + (s + 1) * T], ffn(x, w[E + s]))
 
 
+@pytest.mark.parametrize("T,H,F", [(70, 40, 24), (33, 264, 130), (65, 2056, 40), (40, 64, 2056)])
+def test_f32_ffn_values_without_bf16_parts(T, H, F):
+    """Values that round up to infinity in bf16, infinities and NaN, on both sides of the longest contraction
+    that is multiplied in parts (2048): finite rows as in 64 bits, the others infinite or NaN in the same places."""
+    import paper_2508_12851_amd as P
+    rng = np.random.default_rng([T, H, F])
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    w = [(rng.standard_normal(s) / np.sqrt(s[1])).astype(np.float32) for s in ((F, H), (F, H), (H, F))]
+    for m in w[:2]:
+        m[:, 7] *= np.float32(1e-38)
+    x[5, 7] = 3.4e38                             # below the largest fp32 value, above the largest bf16 one
+    x[9, 1], x[T - 1, H - 1] = np.inf, -np.inf
+    x[11, 2] = np.nan
+    dev = lambda a: torch.from_numpy(a).cuda()
+    desc = P.make_desc(H, F, 1, 1, 0, "f32")
+    y = P.prism_expert_ffn(desc, dev(x), P.WeightTable([tuple(map(dev, w))]), torch.arange(T, dtype=torch.int32, device="cuda"),
+                           torch.tensor([0, T], dtype=torch.int32, device="cuda"), P.alloc_workspace(desc, T)).cpu().numpy()
+    with np.errstate(all="ignore"):
+        g, u, d = (m.astype(np.float64) for m in w)
+        z = x.astype(np.float64) @ g.T
+        ref = (z / (1.0 + np.exp(-z)) * (x.astype(np.float64) @ u.T)) @ d.T
+    odd = [9, 11, T - 1]
+    assert (np.isnan(ref[odd]) | np.isinf(ref[odd])).all()
+    np.testing.assert_array_equal(np.isnan(y), np.isnan(ref))
+    np.testing.assert_array_equal(np.isinf(y), np.isinf(ref))
+    rest = np.setdiff1d(np.arange(T), odd)       # bound: test_f32_ffn_edges
+    assert np.linalg.norm(y[rest] - ref[rest]) <= 1e-6 * np.linalg.norm(ref[rest])
+
+
 def test_f32_ffn_of_more_tiles_than_one_grid_dimension_holds():
     """16392 row tiles x 512 column tiles = 8.4 million workgroups of 512 threads, more than 2^32 threads in a row
     (h takes 69 GB).  Every row written, rows at the edges of every expert against 64-bit arithmetic."""
