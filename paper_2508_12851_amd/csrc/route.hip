@@ -189,27 +189,6 @@ __device__ __forceinline__ void finish_group(const double (&s)[NT], const float 
                        nullptr, picked);
 }
 
-// The same for a tile of 16 tokens held by one wavefront in the accumulator layout of
-// v_mfma_f64_16x16x4: register v of lane (r, q) is token 4 v + q, expert 16 n + r.
-template <int NT>
-__device__ __forceinline__ void finish_tile(const f64x4 (&acc)[NT], int tok0,
-                                            const float* __restrict__ bias, int T, int E, int k,
-                                            int bias_group_tokens, int gate_mode,
-                                            float* __restrict__ logits, int32_t* topk_idx,
-                                            float* __restrict__ topk_gate, int* s_counts) {
-  const int q = (threadIdx.x & 63) >> 4;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int t = tok0 + 4 * v + q;
-    double s[NT];
-    float b[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) s[n] = acc[n][v];
-    load_bias_group<NT>(bias, t, T, E, bias_group_tokens, b);
-    finish_group<NT>(s, b, bias != nullptr, t, T, E, k, gate_mode, logits, topk_idx, topk_gate, s_counts);
-  }
-}
-
 // NT = number of 16-expert column tiles (E <= 16 * NT).
 // PARTIAL: workgroup (tile, y) covers hidden elements [y h_span, (y + 1) h_span) only and
 // stores its fp64 tile to partial[tile][y][NT][64 lanes][4]; nothing else is written.
@@ -229,8 +208,12 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_kernel(
   const int q = lane >> 4;
   const int tok0 = blockIdx.x * kTokPerBlock;
 
-  for (int e = threadIdx.x; e < EP; e += blockDim.x) s_counts[e] = 0;
-  __syncthreads();
+  for (int e = threadIdx.x; e < EP; e += blockDim.x) s_counts[e] = 0;   // (read after the barriers below)
+
+  // wavefronts 0..3 finish tokens 4 wave + q; their bias entries are fetched now
+  const int t_fin = tok0 + 4 * (wave & 3) + q;
+  float bias_fin[NT];
+  if (!PARTIAL) load_bias_group<NT>(bias, t_fin, T, E, bias_group_tokens, bias_fin);
 
   // ---- router GEMM on the fp64 matrix cores --------------------------------
   f64x4 acc[NT];
@@ -276,43 +259,48 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_kernel(
     }
   }
 
-  // ---- sum the partial tiles: (1,3,5,7) -> (0,2,4,6), (2,6) -> (0,4), 4 -> 0 ----
+  // ---- sum the partial tiles as a tree: wavefronts 1, 3, 5, 7 into 0, 2, 4, 6, then those by wavefronts 0..3,
+  // each for the four tokens of one accumulator register (register v of lane (r, q): token 4 v + q,
+  // expert 16 n + r).  The routing of a token is a long dependent chain; one wavefront for all 16
+  // tokens took four of them one after the other (64 tokens x 8 experts of 256 elements, fp32: layer 39.8 ->
+  // 36.9 us).
+  double* const slot = s_part + (size_t)(wave >> 1) * (NT * 4 * 64) + lane;
+  if (wave & 1) {
 #pragma unroll
-  for (int step = 1; step < kWavesPerBlock; step <<= 1) {
-    const bool sender = (wave & (2 * step - 1)) == step;
-    const bool receiver = (wave & (2 * step - 1)) == 0;
-    double* slot = s_part + (size_t)(wave / (2 * step)) * (NT * 4 * 64);
-    if (sender) {
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
-      for (int n = 0; n < NT; ++n)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) slot[(n * 4 + v) * 64 + lane] = acc[n][v];
-    }
-    __syncthreads();
-    if (receiver) {
-#pragma unroll
-      for (int n = 0; n < NT; ++n)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[n][v] += slot[(n * 4 + v) * 64 + lane];
-    }
-    __syncthreads();
+      for (int v = 0; v < 4; ++v) slot[(n * 4 + v) * 64] = acc[n][v];
   }
-  if (wave != 0) return;   // wavefront 0 holds the full sums (no barrier follows)
-
-  if (PARTIAL) {
-    double* out = partial + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * (NT * 256);
+  __syncthreads();
+  if (!(wave & 1)) {
 #pragma unroll
-    for (int n = 0; n < NT; ++n) *reinterpret_cast<f64x4*>(out + n * 256 + lane * 4) = acc[n];
-    return;
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) slot[(n * 4 + v) * 64] = acc[n][v] + slot[(n * 4 + v) * 64];
   }
-
-  finish_tile<NT>(acc, tok0, bias, T, E, k, bias_group_tokens, gate_mode, logits, topk_idx,
-                  topk_gate, counts != nullptr ? s_counts : nullptr);
-  if (counts == nullptr) return;   // the caller derives the counts from the dispatch histogram
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // this wavefront's LDS atomics, then its reads
+  __syncthreads();
+  if (wave < 4) {
+    double sum[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const double* const s = s_part + (n * 4 + wave) * 64 + lane;
+      constexpr int kPair = NT * 4 * 64;
+      sum[n] = (s[0] + s[kPair]) + (s[2 * kPair] + s[3 * kPair]);
+    }
+    if (PARTIAL) {
+      double* out = partial + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * (NT * 256);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) out[n * 256 + lane * 4 + wave] = sum[n];
+    } else {
+      finish_group<NT>(sum, bias_fin, bias != nullptr, t_fin, T, E, k, gate_mode, logits, topk_idx, topk_gate,
+                       counts != nullptr ? s_counts : nullptr);
+    }
+  }
+  if (PARTIAL || counts == nullptr) return;   // the caller derives the counts from the dispatch histogram
 
   // ---- per-expert activation counts -----------------------------------------
-  for (int e = lane; e < E; e += 64) {
+  __syncthreads();
+  for (int e = threadIdx.x; e < E; e += blockDim.x) {
     const int c = s_counts[e];
     if (c != 0) {
       atomicAdd(&counts[e], c);
