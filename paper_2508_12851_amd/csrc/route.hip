@@ -366,10 +366,15 @@ __device__ __forceinline__ void read_blocks(u32x4 (&o)[N], uint32_t addr) {
 template <int NT, int TMB>
 struct StagedCfg {
   static constexpr int kBlocks = TMB + NT;                       // 1 KiB blocks per slice
-  static constexpr int kFit = (96 * 1024) / (kWavesPerBlock * kBlocks * 1024);
+  // Two workgroups share a CU where 2 slices and the partial tiles leave room: one's ring fills and adds up its
+  // tiles under the other's products (route stage, 2 x 2 tiles: 3000 tokens x 256 experts of 1024 elements 47 -> 44 us,
+  // 8192 x 200 of 2048 156 -> 142).
+  static constexpr int kReduceBytes = kWavesPerBlock * TMB * NT * 4 * 64 * 8;
+  static constexpr int kShared = 76 * 1024;
+  static constexpr bool kTwo = kReduceBytes <= kShared && 2 * kWavesPerBlock * kBlocks * 1024 <= kShared;
+  static constexpr int kFit = (kTwo ? kShared : 96 * 1024) / (kWavesPerBlock * kBlocks * 1024);
   static constexpr int kDepth = kFit < 4 ? kFit : 4;             // slices in flight per wavefront
   static constexpr int kStageBytes = kWavesPerBlock * kDepth * kBlocks * 1024;
-  static constexpr int kReduceBytes = kWavesPerBlock * TMB * NT * 4 * 64 * 8;
   static constexpr int kLdsBytes = kStageBytes > kReduceBytes ? kStageBytes : kReduceBytes;
   static_assert(kDepth >= 2, "the next slice must be in flight during the MFMAs of this one");
 };
@@ -821,9 +826,9 @@ bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, Spl
   static_assert(kSplitRouteMaxParts <= kRouteMaxHSplit && kDecodeMaxTokens * PRISM_MAX_TOPK <= kFineChunk, "decode regions");
   if (hist_bytes + part_bytes > scratch_bytes) return false;
   // The shape of a workgroup: the one with the least estimated time.  A SIMD holds two of its
-  // wavefronts, and a v_mfma_f64_16x16x4 takes 64 clocks, the conversion of an operand element
-  // about 12 more, none of which overlap; filling the ring and adding up the partial tiles takes
-  // about 3000 and 1500 per tile.  (13 sizes from 100 x 60 to 8192 x 60 and 3000 x 256 tokens x
+  // wavefronts (four where two workgroups share the CU), and a v_mfma_f64_16x16x4 takes 64 clocks, the
+  // conversion of an operand element about 12 more, none of which overlap; filling the ring and adding up the
+  // partial tiles takes about 3000 and 1500 per tile.  (With one workgroup per CU, 13 sizes from 100 x 60 to 8192 x 60 and 3000 x 256 tokens x
   // experts, all 5 shapes with 1 to 16 parts: what the estimate picks is within 6 % of the fastest
   // or at the launch floor; the worst shape takes up to twice as long.)
   const int tiles = ceil_div(T, kTokPerBlock), cols = ceil_div(d.n_experts, 16), slices = ceil_div(d.hidden, 32);
@@ -836,7 +841,10 @@ bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, Spl
       if (hist_bytes + part_bytes * hs > scratch_bytes) break;
       const long long wgs = (long long)ceil_div(tiles, tmb) * ceil_div(cols, nt) * hs;
       const long long per_wave = ceil_div(ceil_div(slices, hs), kWavesPerBlock);
-      const long long cost = (wgs + 255) / 256 * (3000 + 1500 * nt * tmb + per_wave * 2 * 8 * (64 * nt * tmb + 12 * (nt + tmb))) + 200 * hs;
+      const long long mfma = per_wave * 2 * 8 * (64 * nt * tmb + 12 * (nt + tmb)), fixed = 3000 + 1500 * nt * tmb;
+      const int per_cu = nt * tmb <= 4 && nt + tmb <= 4 ? 2 : 1;      // StagedCfg::kTwo
+      const long long full = wgs / (256 * per_cu), rest = wgs - full * 256 * per_cu;
+      const long long cost = full * (fixed + per_cu * mfma) + (rest > 0 ? fixed + (rest + 255) / 256 * mfma : 0) + 200 * hs;
       if (best < 0 || cost < best) {
         best = cost;
         plan->nt = nt; plan->tmb = tmb; plan->hs = hs;
