@@ -213,9 +213,7 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
   // Loads are buffer_load_dwordx4 ... lds with a per-lane 32-bit byte offset that
   // never changes within an item and the k offset in a scalar register, so a load
   // costs no vector ALU work; the buffer size makes an out-of-range row read zeros.
-  const int sub = lane / CPR;
-  const int lrow = wave * RPG + sub;              // + 4 RPG i (>= 32 rows: does not change the key)
-  const int c = (lane % CPR) ^ swizzle_key<BK>(lrow);   // global chunk fetched by this lane
+  // Row lrow = wave RPG + lane / CPR + 4 RPG i (>= 32 rows: does not change the key), chunk (lane % CPR) ^ key(lrow).
   const __amdgpu_buffer_rsrc_t a_rsrc =
       __builtin_amdgcn_make_buffer_rsrc((void*)p.A, 0, (int)p.a_bytes, kBufferFlags);
 
@@ -280,51 +278,55 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
           it.tok_base >= 0 && !p.a_tiled ? kOutOfRange : (uint32_t)it.row_start * 4u + (uint32_t)lane * 16u, 0, 0, 0);
     return r;
   };
-  // Byte offset of this lane's 16-byte chunk c of weight row n in k-tile 0 (the k-tile offset
-  // is added per load): row-major, or tiles of 16 rows x 32 columns (1 KiB, rows 64 bytes
-  // apart) laid out row-tile major -- a 64-wide k-tile spans two neighbouring tiles.
-  auto tiled_offset = [&](uint32_t n, uint32_t cols) {
-    return (n >> 4) * (cols >> 5) * 1024u + (n & 15u) * 64u + (uint32_t)(c >> 2) * 1024u +
-           (uint32_t)(c & 3) * 16u;
+  // Byte offset of row n of a matrix of K columns, tiles (16 rows x 32 columns, 1 KiB, row-tile major) or
+  // row-major alike: (n / 16) blocks of 32 K bytes, n % 16 rows of the pitch inside.  A lane adds its 16-byte chunk c
+  // of k-tile 0 (a 64-wide one spans two neighbouring tiles); the k-tile is added per load.  No branch per row: a
+  // workgroup has one wavefront per SIMD, and nothing else runs there while it prepares an item.
+  const uint32_t block_bytes = (uint32_t)p.K * 32u;
+  auto chunk_offset = [&](int c, int tiled) {
+    return tiled ? (uint32_t)(c >> 2) * 1024u + (uint32_t)(c & 3) * 16u : (uint32_t)c * 16u;
   };
-  auto weight_row_offset = [&](uint32_t n) {
-    return p.b_tiled ? tiled_offset(n, (uint32_t)p.K) : n * (uint32_t)p.K * 2u + (uint32_t)c * 16u;
-  };
+  const uint32_t b_pitch = p.b_tiled ? 64u : (uint32_t)p.K * 2u;
+  const uint32_t h_pitch = p.a_tiled ? 64u : p.a_pitch;   // plain GEMM: rows of h
+  // a / top_k for a < 2^30, top_k <= 8: the excess of a * ceil(2^32 / top_k) / 2^32 stays below 1 / top_k
+  const uint32_t k_magic = p.top_k > 1 ? 0xFFFFFFFFu / (uint32_t)p.top_k + 1u : 0u;
   auto make_ctx = [&](const Item& it, const Raw& raw) {
     Ctx cx;
     cx.row_start = it.row_start; cx.row_count = it.row_count; cx.nt = it.nt;
     cx.kt0 = it.kt0; cx.kt_n = it.kt_n; cx.part = it.part;
     cx.rot = ROTATE ? (int)((unsigned)(it.nt * 13 + it.g * 29) % (unsigned)KT) : 0;
     cx.b0 = raw.b0; cx.b1 = raw.b1;
+    // what depends on the lane is worked out anew per item: in registers across the k-loop it would push others out
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    const int sub = l / CPR, lrow = wave * RPG + sub;
+    const int c = (l % CPR) ^ swizzle_key<BK>(lrow);
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
       const int rr = min(lrow + 4 * RPG * i, it.row_count - 1);
-      uint32_t src;
+      uint32_t off;
       if (GATED) {
-        const int a = reinterpret_cast<const int*>(src_lds)[rr];
-        src = it.tok_base >= 0 && !p.a_tiled ? (uint32_t)(it.tok_base + rr) : (uint32_t)(a / p.top_k);
+        const uint32_t a = reinterpret_cast<const uint32_t*>(src_lds)[rr];
+        const uint32_t tok = k_magic != 0 ? __umulhi(a, k_magic) : a;
+        off = (it.tok_base >= 0 && !p.a_tiled ? (uint32_t)(it.tok_base + rr) : tok) * p.a_pitch + (uint32_t)c * 16u;
       } else {
-        src = (uint32_t)(it.row_start + rr);
+        const uint32_t row = (uint32_t)(it.row_start + rr);
+        off = (row >> 4) * block_bytes + (row & 15u) * h_pitch + chunk_offset(c, p.a_tiled);
       }
       // Rows past the end of a partly filled tile get an offset beyond the buffer: the
       // hardware then returns zeros, and all-zero operands cost the matrix cores far
       // less power than real data (the chip is power-limited in this kernel).
-      const uint32_t off = !GATED && p.a_tiled ? tiled_offset(src, (uint32_t)p.K)
-                                               : src * p.a_pitch + c * 16;
       cx.a_voff[i] = lrow + 4 * RPG * i < it.row_count ? off : kOutOfRange;
     }
+    const uint32_t b_lane = (uint32_t)sub * b_pitch + chunk_offset(c, p.b_tiled);
 #pragma unroll
     for (int i = 0; i < B_CH; ++i) {
       const int g0 = wave * RPG + 4 * RPG * i;      // first tile row of the group (scalar)
-      if (GATED) {
-        // tile rows [w WN, w WN + WN/2) are gate rows, the next WN/2 the up rows of the same f
-        const int w = g0 / WN, within = g0 % WN;
-        const int f = min(it.nt * (BN / 2) + w * (WN / 2) + (within % (WN / 2)) + sub, p.N - 1);
-        cx.b_voff[i] = weight_row_offset((uint32_t)f);
-      } else {
-        const int n = min(it.nt * BN + g0 + sub, p.N - 1);
-        cx.b_voff[i] = weight_row_offset((uint32_t)n);
-      }
+      // GATED: tile rows [w WN, w WN + WN/2) are gate rows, the next WN/2 the up rows of the same f.  (N is a
+      // multiple of 64: a group's rows all exist, or the last group stands in for it.)
+      const int n = GATED ? it.nt * (BN / 2) + g0 / WN * (WN / 2) + g0 % WN % (WN / 2) : it.nt * BN + g0;
+      const uint32_t n0 = (uint32_t)min(n, p.N - RPG);
+      cx.b_voff[i] = (n0 >> 4) * block_bytes + (n0 & 15u) * b_pitch + b_lane;
     }
     return cx;
   };
