@@ -34,6 +34,8 @@
 #ifndef PRISM_GROUPED_GEMM_H_
 #define PRISM_GROUPED_GEMM_H_
 
+#include <type_traits>
+
 #include "prism_internal.h"
 #include "schedule.h"
 
@@ -401,7 +403,10 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
   constexpr int kPart = (LPS + KK - 1) / KK;     // most loads one step issues
   int stage = 0;                       // g % STAGES
   int fill_stage = STAGES - 1;         // (g + STAGES - 1) % STAGES
-  auto k_iteration = [&](const Ctx& fill_cx, int fill_kt) {
+  // first: the first k-tile of an item, whose products start the sums (clearing the accumulators would take
+  // as long as a k-tile's products, with nothing else to issue).
+  const f32x16 kZero = {};
+  auto k_iteration = [&](const Ctx& fill_cx, int fill_kt, auto first) __attribute__((always_inline)) {
     const int next_stage = stage + 1 == STAGES ? 0 : stage + 1;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
@@ -423,7 +428,8 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
           // snake order over the grid of accumulators: every MFMA shares an operand with the one
           // before it (0.5 % on the power-limited prefill GEMMs)
           const int j = (i & 1) ? NJ - 1 - j0 : j0;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i],
+                                                              first && kk == 0 ? kZero : acc[i][j], 0, 0, 0);
         }
       // Issue order inside the step: one MFMA first (so the wait for this step's
       // operands precedes any new LDS read), then the next step's operand reads one
@@ -632,16 +638,17 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
     const Item& it_fill = has_next ? it_next : it_cur;
     const Raw raw_next = fetch_raw(it_fill);      // one more counted load, older than all that follow
 
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
     // refills still inside this item
     const int kt_n = SLICES ? cur.kt_n : KT;   // (every entry has at least STAGES - 1 k-tiles)
-    for (int kt = 0; kt + (STAGES - 1) < kt_n; ++kt) k_iteration(cur, kt + STAGES - 1);
+    if (kt_n > STAGES - 1) {
+      k_iteration(cur, STAGES - 1, std::true_type{});
+      for (int kt = 1; kt + (STAGES - 1) < kt_n; ++kt) k_iteration(cur, kt + STAGES - 1, std::false_type{});
+    } else {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = kZero;
+    }
     // The source rows of the next item were requested before those iterations; loads
     // complete in order, so they have landed once enough younger loads have been
     // waited for, which the iterations above guarantee only if there were enough.
@@ -650,7 +657,7 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_kernel(const GemmAr
     // re-fetch of this item's first k-tiles, which keeps the vmcnt bookkeeping uniform)
     const Ctx nxt = make_ctx(it_fill, raw_next);
     for (int kt = max(kt_n - (STAGES - 1), 0); kt < kt_n; ++kt)
-      k_iteration(nxt, min(kt + (STAGES - 1) - kt_n, (SLICES ? nxt.kt_n : KT) - 1));
+      k_iteration(nxt, min(kt + (STAGES - 1) - kt_n, (SLICES ? nxt.kt_n : KT) - 1), std::false_type{});
 
     epilogue(cur);
     if (!has_next) break;
