@@ -35,7 +35,8 @@ struct F32Args {
   int T, H, F, E, S, top_k;
 };
 
-constexpr int kBM = 64;                  // rows of a tile
+constexpr int kBM = 64;                  // most rows of a tile
+constexpr float kHalfTile = 0.85f;       // time of a tile of 32 rows, in tiles of 64
 constexpr int kBN = 64;                  // weight rows of a tile
 constexpr int kBK = 16;                  // contraction elements per k-tile
 constexpr int kWaves = 8;
@@ -65,23 +66,39 @@ struct RowTile {
 
 // The row tiles: those of the routed experts in expert order, then those of the shared ones.  Every
 // wavefront holds the offsets of four experts per lane and finds a tile by its number with a ballot.
+// All are 64 or all are 32 rows high, whichever takes less time by the rounds of items it makes of the launch's
+// workgroups: 887 rows of 5 experts x 16 column tiles are 272 items of 64 rows, two rounds on 256 workgroups, and
+// 496 of 32, also two (down projection of 2048 x 1024, 62 -> 52 us); 64 tokens make one round of either, and lower tiles
+// spread the work further (layer of 256 x 512: 36.9 -> 34.6 us).
 struct RowTiles {
   int off[5];      // offsets of experts 4 lane .. 4 lane + 4
   int before;      // row tiles of the experts before lane's
   int routed;      // row tiles of all routed experts
+  int shift;       // 2^shift rows per tile
 };
-__device__ __forceinline__ int tiles_of(int rows) { return (rows + kBM - 1) / kBM; }
-__device__ __forceinline__ RowTiles load_row_tiles(const F32Args& p) {
+__device__ __forceinline__ int tiles_of(int rows, int shift) { return (rows + (1 << shift) - 1) >> shift; }
+__device__ __forceinline__ RowTiles load_row_tiles(const F32Args& p, int n_col_tiles) {
   const int lane = threadIdx.x & 63;
   RowTiles r;
 #pragma unroll
   for (int j = 0; j < 5; ++j) r.off[j] = p.local_offsets[min(4 * lane + j, p.E)];
-  int tiles = 0;
+  float best = INFINITY;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) tiles += tiles_of(r.off[j + 1] - r.off[j]);
-  const int incl = wave_inclusive_scan(tiles);
-  r.before = incl - tiles;
-  r.routed = __builtin_amdgcn_readlane(incl, 63);
+  for (int shift = 6; shift >= 5; --shift) {
+    int tiles = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tiles += tiles_of(r.off[j + 1] - r.off[j], shift);
+    const int incl = wave_inclusive_scan(tiles);
+    const int routed = __builtin_amdgcn_readlane(incl, 63);
+    const float items = (float)(routed + p.S * tiles_of(p.T, shift)) * (float)n_col_tiles;
+    const float time = ceilf(items / (float)gridDim.x) * (shift == 6 ? 1.f : kHalfTile);
+    if (time < best) {
+      best = time;
+      r.before = incl - tiles;
+      r.routed = routed;
+      r.shift = shift;
+    }
+  }
   return r;
 }
 __device__ __forceinline__ RowTile row_tile(const F32Args& p, const RowTiles& r, int b) {
@@ -90,12 +107,12 @@ __device__ __forceinline__ RowTile row_tile(const F32Args& p, const RowTiles& r,
     bool mine = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int t = tiles_of(r.off[j + 1] - r.off[j]);
+      const int t = tiles_of(r.off[j + 1] - r.off[j], r.shift);
       if (rel >= 0 && rel < t) {
         mine = true;
         e = 4 * (threadIdx.x & 63) + j;
-        start = r.off[j] + rel * kBM;
-        count = min(kBM, r.off[j + 1] - start);
+        start = r.off[j] + (rel << r.shift);
+        count = min(1 << r.shift, r.off[j + 1] - start);
       }
       rel -= t;
     }
@@ -103,8 +120,8 @@ __device__ __forceinline__ RowTile row_tile(const F32Args& p, const RowTiles& r,
     return RowTile{__builtin_amdgcn_readlane(e, owner), __builtin_amdgcn_readlane(start, owner),
                    __builtin_amdgcn_readlane(count, owner), -1};
   }
-  const int per_shared = tiles_of(p.T), s = (b - r.routed) / per_shared, tok = (b - r.routed - s * per_shared) * kBM;
-  return RowTile{p.E + s, p.T * (p.top_k + s) + tok, min(kBM, p.T - tok), tok};
+  const int per_shared = tiles_of(p.T, r.shift), s = (b - r.routed) / per_shared, tok = (b - r.routed - s * per_shared) << r.shift;
+  return RowTile{p.E + s, p.T * (p.top_k + s) + tok, min(1 << r.shift, p.T - tok), tok};
 }
 
 // An fp32 value is the sum of three bf16 values: the nearest one, the nearest one to what is left, and
@@ -137,9 +154,10 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
   // Consecutive workgroups go to the 8 XCDs in turn; every XCD takes a contiguous eighth of the
   // items, row tiles running fastest, so that the row tiles of an expert read its weight rows
   // through one L2.
-  const RowTiles tiles = load_row_tiles(p);
-  const int n_row_tiles = tiles.routed + p.S * tiles_of(p.T);
-  const int n_items = n_row_tiles * ((N + kCols - 1) / kCols);
+  const int n_col_tiles = (N + kCols - 1) / kCols;
+  const RowTiles tiles = load_row_tiles(p, n_col_tiles);
+  const int n_row_tiles = tiles.routed + p.S * tiles_of(p.T, tiles.shift);
+  const int n_items = n_row_tiles * n_col_tiles;
   const int xcd = blockIdx.x % kXcds, slots = gridDim.x / kXcds;
   const int item_end = (int)((long long)n_items * (xcd + 1) / kXcds);
   int item = (int)((long long)n_items * xcd / kXcds) + blockIdx.x / kXcds;
@@ -450,15 +468,18 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
 template <bool GATED>
 prism_status launch_f32_gemm(const F32Args& a, hipStream_t st) {
   const int A = a.T * a.top_k;
-  // row tiles there can be: a full one per 64 assignments, and one that is not per expert with rows
-  const long long row_tiles = (long long)A / kBM + std::min(a.E, A) + (long long)a.S * ceil_div(a.T, kBM);
-  const long long items = row_tiles * ceil_div(GATED ? a.F : a.H, GATED ? kBN / 2 : kBN);
-  // (2^31 items, each for up to 64 x 32 elements of h, are beyond any memory)
-  if (items >= 0x7FFF0000LL) return PRISM_ERR_UNSUPPORTED;
+  // items there can be, in tiles of 2^shift rows: a full row tile per 2^shift assignments, and one that is not per
+  // expert with rows
+  auto items = [&](int shift) {
+    const long long row_tiles = ((long long)A >> shift) + std::min(a.E, A) + (long long)a.S * ceil_div(a.T, 1 << shift);
+    return row_tiles * ceil_div(GATED ? a.F : a.H, GATED ? kBN / 2 : kBN);
+  };
+  // (2^31 items of 64 rows, each for up to 64 x 32 elements of h, are beyond any memory)
+  if (items(6) >= 0x7FFF0000LL) return PRISM_ERR_UNSUPPORTED;
   static LdsLimitOnce lds_limit;   // one per instantiation
   if (!raise_lds_limit(lds_limit, (const void*)ffn_f32_kernel<GATED>, kLdsBytes)) return PRISM_ERR_LAUNCH;
   // one workgroup fits a CU
-  hipLaunchKernelGGL(ffn_f32_kernel<GATED>, dim3((unsigned)std::min<long long>(kWorkgroups, align_up((size_t)items, kXcds))),
+  hipLaunchKernelGGL(ffn_f32_kernel<GATED>, dim3((unsigned)std::min<long long>(kWorkgroups, align_up((size_t)items(5), kXcds))),
                      dim3(kThreads), kLdsBytes, st, a);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;

@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
     (160, 200, 33, [63, 0, 97], 1),
     (40, 1024, 2047, [7, 33, 0], 1),            # the longest chains; every weight row at another alignment
     (300, 264, 130, [129, 128, 43], 0),
+    (1000, 64, 2048, [500, 300, 97, 65, 33], 0),   # gate/up in tiles of 64 rows, down in tiles of 32
+    (200, 40, 4096, [100, 64, 33], 3),          # the same with shared rows
 ])
 def test_f32_ffn_edges(T, H, F, rows, S):
     import paper_2508_12851_amd as P
