@@ -174,8 +174,8 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
                              hipStream_t st, int32_t* tiles = nullptr,
                              bool* schedules_built = nullptr);
 
-// bf16 batches inside the whole layer, but for decode batches of at most 16 experts (launch_decode_front_end) and large
-// batches of at most 64 (launch_route; so do shapes whose h and y cannot hold the sums): the router as two launches.  The
+// bf16 batches inside the whole layer, but for decode batches of at most 16 experts (launch_decode_front_end) and
+// batches of 6113 to 8192 tokens of at most 64 (launch_route; so do shapes whose h and y cannot hold the sums): the router as two launches.  The
 // first spreads (token tile, experts, hidden elements) over the chip and leaves fp64 partial
 // logits, the second sums them, picks the experts and counts them per block of assignments.
 struct SplitRoutePlan {

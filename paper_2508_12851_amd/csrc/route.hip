@@ -26,7 +26,7 @@
 //     schedules of the two grouped GEMMs (decode_front_end_kernel);
 //   other bf16 batches: route_staged_kernel<SPLIT> spreads token tiles, experts and hidden elements,
 //     route_pick_kernel sums the parts, picks, and counts the picks per block of the placement.
-// prism_route on its own, fp32 layers and the largest batches take one launch (route_staged_kernel
+// prism_route on its own, fp32 layers and batches of 6113 to 8192 tokens take one launch (route_staged_kernel
 // for bf16 batches of more than 64 tokens and at most 64 experts, else route_kernel).
 #include "dispatch_device.h"
 #include "prism_internal.h"
@@ -806,10 +806,12 @@ prism_status launch_route(const prism_layer_desc& d, const void* x, const void* 
 bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, SplitRoutePlan* plan) {
   if (d.dtype != PRISM_BF16 || T <= 0 || (uint64_t)T * d.hidden * 2 >= 0xFFFF0000ull) return false;
   if (decode_front_end_applies(d, T)) return false;
-  // With 32-token workgroups for three quarters of the CUs the router in one launch is as good
-  // (8192 tokens x 60 experts: 51 us with its histogram launch of 5, split 52 + 6 us, and the
-  // layer 1 % slower).
-  if (staged_router_applies(d, T) && ceil_div(T, 2 * kTokPerBlock) >= 192) return false;
+  // One round of 32-token workgroups on at least three quarters of the CUs: the router in one launch is as good (route
+  // and dispatch stages, 60 experts of 2048 elements: 8192 tokens 60 against 61 us split, 6500 tokens 61 / 61).  Beyond, its
+  // second round starts with few (10000 tokens 101 / 75, 12288 99 / 80, 16384 101 / 99; 8 experts of 4096, 10000
+  // tokens, 63 / 50).
+  const int wgs32 = ceil_div(T, 2 * kTokPerBlock);
+  if (staged_router_applies(d, T) && wgs32 >= 192 && wgs32 <= 256) return false;
   const int A = T * d.top_k;
   // Blocks of 512 assignments up to 8192 (a block's four wavefronts then take two steps instead of
   // eight); beyond, every placing workgroup would sum more histograms than that saves (32768
