@@ -229,6 +229,14 @@ prism_status prism_combine(const prism_layer_desc* desc, const void* y, const in
  */
 prism_status prism_pack_remote(const prism_layer_desc* desc, const void* x, const int32_t* remote_src,
                                const int32_t* remote_offsets, int32_t T, void* packed, void* stream);
+
+/*
+ * Zeros in the rows that prism_expert_ffn (y, offsets = local_offsets) or prism_pack_remote (packed, offsets =
+ * remote_offsets) leave untouched, for callers that want defined values there:
+ *   rows[r] = 0  for offsets[E] <= r < n_rows;  rows [n_rows, H] layer dtype, 16-byte aligned (n_rows: T*k).
+ */
+prism_status prism_clear_rows(const prism_layer_desc* desc, const int32_t* offsets, int32_t n_rows, void* rows,
+                              void* stream);
 prism_status prism_combine_remote(const prism_layer_desc* desc, const void* y_remote,
                                   const int32_t* remote_src, const int32_t* remote_offsets,
                                   const float* topk_gate, int32_t T, void* out, void* workspace,

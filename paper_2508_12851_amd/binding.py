@@ -21,7 +21,8 @@ SYMBOLS = ("prism_status_string", "prism_workspace_bytes", "prism_route", "prism
            "prism_expert_ffn", "prism_combine", "prism_moe_layer", "prism_moe_layer_traced",
            "prism_ceiling_mfma_bf16", "prism_ceiling_hbm_read", "prism_pack_remote",
            "prism_combine_remote", "prism_debug_check_weights", "prism_pack_weights",
-           "prism_layer_permutation", "prism_moe_layer_static", "prism_ceiling_hbm_read_pattern")
+           "prism_layer_permutation", "prism_moe_layer_static", "prism_ceiling_hbm_read_pattern",
+           "prism_clear_rows")
 STAGES = ("route", "dispatch", "ffn_up", "ffn_down", "combine")
 GATE_MODES = {"renormalized": 0, "softmax_all": 1}
 WEIGHT_LAYOUTS = {"row_major": 0, "tiled": 1}
@@ -74,6 +75,7 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.prism_moe_layer_static.argtypes = lib.prism_moe_layer.argtypes[:16] + [vp]
     lib.prism_pack_remote.argtypes = [dp, vp, vp, vp, i32, vp, vp]
     lib.prism_combine_remote.argtypes = [dp, vp, vp, vp, vp, i32, vp, vp, sz, vp]
+    lib.prism_clear_rows.argtypes = [dp, vp, i32, vp, vp]
     lib.prism_pack_weights.argtypes = [vp, i32, i32, vp, vp]
     lib.prism_layer_permutation.argtypes = [dp, i32, vp, sz, vp, vp, vp, vp]
     lib.prism_debug_check_weights.argtypes = [dp, wp, vp, ctypes.POINTER(i32)]
@@ -189,8 +191,8 @@ def prism_dispatch(desc: LayerDesc, topk_idx, local_mask, workspace, stream=None
     T, E, k = topk_idx.shape[0], desc.n_experts, desc.top_k
     dev = topk_idx.device
     i32 = dict(dtype=torch.int32, device=dev)
-    out = DispatchOut(torch.full((T * k,), -1, **i32), torch.empty((E + 1,), **i32),
-                      torch.full((T * k,), -1, **i32), torch.empty((E + 1,), **i32),
+    src = torch.full((2, T * k), -1, **i32)     # one fill for both lists
+    out = DispatchOut(src[0], torch.empty((E + 1,), **i32), src[1], torch.empty((E + 1,), **i32),
                       torch.empty((2,), **i32), torch.empty((2,), dtype=torch.int64, device=dev))
     _check(load_library().prism_dispatch(ctypes.byref(desc), _ptr(topk_idx), _ptr(local_mask), T,
                                          _ptr(out.local_src), _ptr(out.local_offsets),
@@ -201,12 +203,18 @@ def prism_dispatch(desc: LayerDesc, topk_idx, local_mask, workspace, stream=None
     return out
 
 
+def _clear_rows(desc: LayerDesc, offsets, n_rows, rows, stream) -> None:
+    _check(load_library().prism_clear_rows(ctypes.byref(desc), _ptr(offsets), n_rows, _ptr(rows), _stream(stream)),
+           "prism_clear_rows")
+
+
 def prism_expert_ffn(desc: LayerDesc, x, weights: WeightTable, local_src, local_offsets, workspace,
                      y=None, stream=None) -> torch.Tensor:
     T = x.shape[0]
     rows = T * desc.top_k + desc.n_shared * T
     if y is None:
-        y = torch.zeros((rows, desc.hidden), dtype=torch_dtype(desc), device=x.device)
+        y = torch.empty((rows, desc.hidden), dtype=torch_dtype(desc), device=x.device)
+        _clear_rows(desc, local_offsets, T * desc.top_k, y, stream)
     _check(load_library().prism_expert_ffn(ctypes.byref(desc), _ptr(x), ctypes.byref(weights.struct),
                                            _ptr(local_src), _ptr(local_offsets), T, _ptr(y),
                                            _ptr(workspace), workspace.numel(), _stream(stream)),
@@ -349,7 +357,8 @@ def prism_ceiling_hbm_read_pattern(src, out, n_workgroups: int, loads_in_flight:
 def prism_pack_remote(desc: LayerDesc, x, remote_src, remote_offsets, stream=None) -> torch.Tensor:
     """Activation rows to ship, in remote-list order ([T*k, H]; rows past the remote count are zero)."""
     T = x.shape[0]
-    packed = torch.zeros((T * desc.top_k, desc.hidden), dtype=x.dtype, device=x.device)
+    packed = torch.empty((T * desc.top_k, desc.hidden), dtype=x.dtype, device=x.device)
+    _clear_rows(desc, remote_offsets, T * desc.top_k, packed, stream)
     _check(load_library().prism_pack_remote(ctypes.byref(desc), _ptr(x), _ptr(remote_src),
                                             _ptr(remote_offsets), T, _ptr(packed), _stream(stream)),
            "prism_pack_remote")

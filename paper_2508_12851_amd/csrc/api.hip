@@ -162,8 +162,17 @@ prism_status prism_combine(const prism_layer_desc* desc, const void* y, const in
   Workspace ws;
   PRISM_TRY(check_workspace(*desc, T, workspace, workspace_bytes, &ws));
   const hipStream_t st = (hipStream_t)stream;
-  PRISM_TRY(launch_build_inverse(*desc, local_src, local_offsets, T, ws.inv, st));
-  return launch_combine(*desc, y, ws.inv, topk_gate, T, out, st);
+  PRISM_TRY(launch_scatter_inverse(*desc, local_src, local_offsets, T, ws.inv, st));
+  return launch_combine(*desc, y, ws.inv, topk_gate, T, out, st, nullptr, nullptr, false, local_src, local_offsets);
+}
+
+prism_status prism_clear_rows(const prism_layer_desc* desc, const int32_t* offsets, int32_t n_rows, void* rows,
+                              void* stream) {
+  PRISM_ENTER();
+  PRISM_TRY(validate_desc(desc, 0, false));
+  PRISM_RETURN_IF(offsets == nullptr || n_rows < 0, PRISM_ERR_INVALID_ARG);
+  if (n_rows > 0) PRISM_RETURN_IF(rows == nullptr || ((uintptr_t)rows & 15u) != 0, PRISM_ERR_INVALID_ARG);
+  return launch_clear_rows(*desc, offsets, n_rows, rows, (hipStream_t)stream);
 }
 
 prism_status prism_pack_remote(const prism_layer_desc* desc, const void* x, const int32_t* remote_src,
@@ -188,8 +197,8 @@ prism_status prism_combine_remote(const prism_layer_desc* desc, const void* y_re
   Workspace ws;
   PRISM_TRY(check_workspace(*desc, T, workspace, workspace_bytes, &ws));
   const hipStream_t st = (hipStream_t)stream;
-  PRISM_TRY(launch_build_inverse(*desc, remote_src, remote_offsets, T, ws.inv, st));
-  return launch_combine(*desc, y_remote, ws.inv, topk_gate, T, out, st, nullptr, nullptr, true);
+  PRISM_TRY(launch_scatter_inverse(*desc, remote_src, remote_offsets, T, ws.inv, st));
+  return launch_combine(*desc, y_remote, ws.inv, topk_gate, T, out, st, nullptr, nullptr, true, remote_src, remote_offsets);
 }
 
 prism_status prism_pack_weights(const void* src, int32_t rows, int32_t cols, void* dst, void* stream) {

@@ -55,11 +55,16 @@ template <> struct Vec<uint16_t> {
 
 // ADD: the sum starts from the value out already holds (returned remote rows are added to
 // the local partial sum) instead of zero.
+// src given: inv was scattered over whatever it held before, and an entry counts only if the list src (of
+// offsets[E] assignments) agrees that it is the place of its assignment.  One more read per slot, of a word that the
+// whole token shares, instead of a launch that clears inv.  (A server's call of nine entry points, 1500 tokens x 6
+// picks: with two such launches, a fill of both lists at once and clear_rows_kernel in place of whole fills 480 -> 458 us.)
 template <typename TIO, bool ADD>
 __global__ __launch_bounds__(256) void combine_kernel(const TIO* __restrict__ y,
                                                       const int32_t* __restrict__ inv,
                                                       const float* __restrict__ gate, int T, int H,
-                                                      int k, int S, TIO* out) {
+                                                      int k, int S, TIO* out, const int32_t* __restrict__ src,
+                                                      const int32_t* __restrict__ n_rows) {
   constexpr int N = Vec<TIO>::N;
   const int vec_per_row = H / N;
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -73,9 +78,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const TIO* __restrict__ y,
 #pragma unroll
     for (int i = 0; i < N; ++i) acc[i] = 0.f;
   }
+  const unsigned n = src != nullptr ? (unsigned)min(max(*n_rows, 0), T * k) : 0x7FFFFFFFu;   // (no place: stored as -1)
   for (int j = 0; j < k; ++j) {
     const int row = inv[t * k + j];
-    if (row >= 0) {
+    if ((unsigned)row < n && (src == nullptr || src[row] == t * k + j)) {
       const float gt = gate[t * k + j];
       float v[N];
       Vec<TIO>::load(y + (size_t)row * H + col, v);
@@ -111,6 +117,14 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const TIO* __restrict__ 
   typedef typename Vec<TIO>::raw raw_t;
   *reinterpret_cast<raw_t*>(packed + (size_t)r * H + col) =
       *reinterpret_cast<const raw_t*>(x + (size_t)t * H + col);
+}
+
+// Zeros in the rows past the ones an assignment list fills (16-byte pieces, row_vecs per row).
+__global__ __launch_bounds__(256) void clear_rows_kernel(const int32_t* __restrict__ offsets, int E, int n_rows,
+                                                         int row_vecs, uint4* __restrict__ rows) {
+  const long long end = (long long)n_rows * row_vecs, step = (long long)gridDim.x * blockDim.x;
+  for (long long i = (long long)offsets[E] * row_vecs + (long long)blockIdx.x * blockDim.x + threadIdx.x; i < end; i += step)
+    rows[i] = uint4{0, 0, 0, 0};
 }
 
 // One 16-byte chunk (8 bf16) per thread from the row-major matrix to its place in the
@@ -206,14 +220,23 @@ __global__ __launch_bounds__(256) void combine_slices_kernel(const float* __rest
 
 }  // namespace
 
-prism_status launch_build_inverse(const prism_layer_desc& d, const int32_t* local_src,
+prism_status launch_scatter_inverse(const prism_layer_desc& d, const int32_t* local_src,
                                   const int32_t* local_offsets, int T, int32_t* inv,
                                   hipStream_t st) {
   const int A = T * d.top_k;
   if (A == 0) return PRISM_OK;
-  PRISM_TRY(launch_fill_i32(inv, A, -1, st));
   hipLaunchKernelGGL(scatter_inverse_kernel, dim3(ceil_div(A, 256)), dim3(256), 0, st, local_src,
                      local_offsets, d.n_experts, A, inv);
+  PRISM_CHECK_LAUNCH();
+  return PRISM_OK;
+}
+
+prism_status launch_clear_rows(const prism_layer_desc& d, const int32_t* offsets, int n_rows, void* rows, hipStream_t st) {
+  if (n_rows == 0) return PRISM_OK;
+  const int row_vecs = d.hidden * elem_size(d.dtype) / 16;     // (H is a multiple of 8)
+  const long long blocks = ((long long)n_rows * row_vecs + 255) / 256;
+  hipLaunchKernelGGL(clear_rows_kernel, dim3((unsigned)std::min<long long>(blocks, 2048)), dim3(256), 0, st, offsets,
+                     d.n_experts, n_rows, row_vecs, (uint4*)rows);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }
@@ -246,8 +269,10 @@ prism_status launch_pack_rows(const prism_layer_desc& d, const void* x, const in
 
 prism_status launch_combine(const prism_layer_desc& d, const void* y, const int32_t* inv,
                             const float* topk_gate, int T, void* out, hipStream_t st,
-                            const float* part, const int32_t* n_splits, bool add_to_out) {
+                            const float* part, const int32_t* n_splits, bool add_to_out, const int32_t* src,
+                            const int32_t* offsets) {
   if (T == 0) return PRISM_OK;
+  const int32_t* n_rows = src != nullptr ? offsets + d.n_experts : nullptr;
   if (add_to_out) {   // returned remote rows: no shared experts, no slices
     if (n_splits != nullptr) return PRISM_ERR_INVALID_ARG;
     const int nv = d.dtype == PRISM_F32 ? 4 : 8;
@@ -255,10 +280,10 @@ prism_status launch_combine(const prism_layer_desc& d, const void* y, const int3
     const unsigned bl = (unsigned)((th + 255) / 256);
     if (d.dtype == PRISM_F32)
       hipLaunchKernelGGL((combine_kernel<float, true>), dim3(bl), dim3(256), 0, st, (const float*)y,
-                         inv, topk_gate, T, d.hidden, d.top_k, 0, (float*)out);
+                         inv, topk_gate, T, d.hidden, d.top_k, 0, (float*)out, src, n_rows);
     else
       hipLaunchKernelGGL((combine_kernel<uint16_t, true>), dim3(bl), dim3(256), 0, st,
-                         (const uint16_t*)y, inv, topk_gate, T, d.hidden, d.top_k, 0, (uint16_t*)out);
+                         (const uint16_t*)y, inv, topk_gate, T, d.hidden, d.top_k, 0, (uint16_t*)out, src, n_rows);
     PRISM_CHECK_LAUNCH();
     return PRISM_OK;
   }
@@ -276,10 +301,10 @@ prism_status launch_combine(const prism_layer_desc& d, const void* y, const int3
   const unsigned blocks = (unsigned)((threads + 255) / 256);
   if (d.dtype == PRISM_F32)
     hipLaunchKernelGGL((combine_kernel<float, false>), dim3(blocks), dim3(256), 0, st, (const float*)y, inv,
-                       topk_gate, T, d.hidden, d.top_k, d.n_shared, (float*)out);
+                       topk_gate, T, d.hidden, d.top_k, d.n_shared, (float*)out, src, n_rows);
   else
     hipLaunchKernelGGL((combine_kernel<uint16_t, false>), dim3(blocks), dim3(256), 0, st, (const uint16_t*)y,
-                       inv, topk_gate, T, d.hidden, d.top_k, d.n_shared, (uint16_t*)out);
+                       inv, topk_gate, T, d.hidden, d.top_k, d.n_shared, (uint16_t*)out, src, n_rows);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }

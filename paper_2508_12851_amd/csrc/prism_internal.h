@@ -257,11 +257,12 @@ static inline void trace(void* const* ev, int stage, int end, hipStream_t st) {
 
 prism_status launch_fill_i32(int32_t* p, int n, int32_t v, hipStream_t st);
 
-// Builds inv from local_src/local_offsets (fill -1, then scatter).
-prism_status launch_build_inverse(const prism_layer_desc& d, const int32_t* local_src,
+// inv[a] = row of assignment a, for the assignments of the list only: the other entries keep what they held.
+prism_status launch_scatter_inverse(const prism_layer_desc& d, const int32_t* local_src,
                                   const int32_t* local_offsets, int T, int32_t* inv,
                                   hipStream_t st);
 
+// src, offsets: the list inv was scattered from (launch_scatter_inverse); NULL: inv is complete, -1 for no row.
 // add_to_out: the gate-weighted rows are added to what out holds (no shared rows, no slices).
 // n_splits (device memory) not NULL: expert outputs are taken from *n_splits fp32 slices in part
 // (bf16 layers only), each element summed over the slices in slice order and rounded to bf16 as
@@ -269,7 +270,10 @@ prism_status launch_build_inverse(const prism_layer_desc& d, const int32_t* loca
 prism_status launch_combine(const prism_layer_desc& d, const void* y, const int32_t* inv,
                             const float* topk_gate, int T, void* out, hipStream_t st,
                             const float* part = nullptr, const int32_t* n_splits = nullptr,
-                            bool add_to_out = false);
+                            bool add_to_out = false, const int32_t* src = nullptr, const int32_t* offsets = nullptr);
+
+// rows[r] = 0 for offsets[E] <= r < n_rows.
+prism_status launch_clear_rows(const prism_layer_desc& d, const int32_t* offsets, int n_rows, void* rows, hipStream_t st);
 
 // Row-major bf16 [rows, cols] -> 16 x 32 tiles (rows a multiple of 16, cols of 32).
 prism_status launch_pack_weights(const void* src, int rows, int cols, void* dst, hipStream_t st);

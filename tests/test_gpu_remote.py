@@ -93,3 +93,45 @@ def test_nothing_remote_leaves_out_untouched():
     packed = P.prism_pack_remote(desc, to_dev(inp.x), o.remote_src, o.remote_offsets)
     torch.cuda.synchronize()
     assert torch.equal(o.out, before) and not packed.any()
+
+
+@pytest.mark.parametrize("dtype,H", [("f32", 8), ("bf16", 64)])
+@pytest.mark.parametrize("fill", [0, 1, 255])
+def test_combine_on_a_workspace_that_holds_other_places(dtype, H, fill):
+    """The inverse of a list is scattered over whatever the workspace held: entries of assignments that are not in
+    the list must not count, whether they hold a possible row, one past the end or nothing sensible."""
+    T, E, k = 37, 5, 3
+    rng = np.random.default_rng([H, fill])
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    desc = P.make_desc(H, 64, E, k, 0, dtype)
+    y = torch.from_numpy(rng.standard_normal((T * k, H)).astype(np.float32)).to(td).cuda()
+    gate = torch.from_numpy(rng.random((T, k)).astype(np.float32)).cuda()
+    ws = P.alloc_workspace(desc, T)
+    ws.fill_(fill)
+    for local in (0, 1, 40, T * k):             # the later calls find the places of the earlier ones
+        src = rng.permutation(T * k)[:local].astype(np.int32)
+        lst = torch.full((T * k,), -1, dtype=torch.int32, device="cuda")
+        lst[:local] = torch.from_numpy(src).cuda()
+        off = torch.from_numpy(np.linspace(0, local, E + 1).astype(np.int32)).cuda()
+        got = P.prism_combine(desc, y, lst, off, gate, ws).double().cpu().numpy()
+        start = torch.full((T, H), 0.5, dtype=td, device="cuda")
+        added = P.prism_combine_remote(desc, y, lst, off, gate, start, ws).double().cpu().numpy()
+        ref = np.zeros((T, H))
+        for r, a in enumerate(src):
+            ref[a // k] += gate[a // k, a % k].item() * y[r].double().cpu().numpy()
+        # one rounding of the result to p significant bits, which is off by at most half a unit in the last place,
+        # 2^-p of it (p = 24, and 8 for bf16), and up to 4 of the fp32 sum, whose terms are below 8
+        for v, w in ((got, ref), (added, ref + 0.5)):
+            assert np.all(np.abs(v - w) <= 2.0 ** (-24 if dtype == "f32" else -8) * np.abs(w) + 32 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("dtype,H,n_rows,first", [("bf16", 8, 1, 0), ("bf16", 2056, 700, 3), ("f32", 24, 700, 699), ("f32", 8, 5, 5)])
+def test_clear_rows(dtype, H, n_rows, first):
+    desc = P.make_desc(H, 64, 2, 1, 0, dtype)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    rows = torch.ones((n_rows + 1, H), dtype=td, device="cuda")
+    off = torch.tensor([0, 0, first], dtype=torch.int32, device="cuda")
+    P.binding._clear_rows(desc, off, n_rows, rows, None)
+    ref = torch.ones_like(rows)
+    ref[first:n_rows] = 0
+    assert torch.equal(rows, ref)
