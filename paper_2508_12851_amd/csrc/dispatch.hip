@@ -48,12 +48,12 @@ constexpr int kSchedParts = 4;   // workgroups that share the building of one sc
 
 // Workgroups [0, n_blocks) place their block; if n_sched > 0, workgroups n_blocks + 4 s + part
 // build part `part` of schedule s (0: gate/up GEMM, 1: down GEMM) from the same histograms.
-template <bool FROM_HIST, int CHUNK>
+template <bool FROM_HIST, int CHUNK, bool WIDTHS = false>
 __global__ __launch_bounds__(kThreads) void dispatch_place_kernel(
     const int32_t* __restrict__ idx, int A, int E, const uint8_t* __restrict__ mask,
     const int32_t* __restrict__ block_hist, int n_blocks, int sub, const SplitOut o,
     int32_t* __restrict__ local_src, int32_t* __restrict__ remote_src, int32_t* __restrict__ inv,
-    int S, int T, const gg::SchedParams p0, const gg::SchedParams p1) {
+    int S, int T, const gg::sched_params_t<WIDTHS> p0, const gg::sched_params_t<WIDTHS> p1) {
   if ((int)blockIdx.x < n_blocks) {
     dispatch_place_block<FROM_HIST, CHUNK>(idx, A, E, mask, block_hist, n_blocks, sub, blockIdx.x, o,
                                            local_src, remote_src, inv);
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kThreads) void dispatch_place_kernel(
     lds_barrier();
     if (threadIdx.x < kWave) split_offsets(s_total, s_mask, E, o, s_start, false, s_local_off);
     lds_barrier();
-    const gg::SchedParams p[1] = {j / kSchedParts == 0 ? p0 : p1};
-    gg::build_schedules_block<1>(s_local_off, E, S, T, A, p, j % kSchedParts, kSchedParts);
+    const gg::sched_params_t<WIDTHS> p[1] = {j / kSchedParts == 0 ? p0 : p1};
+    gg::build_schedules_block<1, WIDTHS>(s_local_off, E, S, T, A, p, j % kSchedParts, kSchedParts);
   }
 }
 
@@ -89,7 +89,7 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
   const SplitOut o{local_offsets, remote_offsets, n_local_remote, remote_bytes, counts,
                    (unsigned long long*)counts_accum, d.hidden * elem_size(d.dtype)};
   if (schedules_built != nullptr) *schedules_built = false;
-  gg::SchedParams p0{}, p1{};
+  gg::WidthParams p0{}, p1{};
   if (A <= kDispatchChunk) {   // one workgroup histograms and places (T = 0: writes the empty split)
     hipLaunchKernelGGL((dispatch_place_kernel<false, kDispatchChunk>), dim3(1), dim3(kThreads), 0, st, topk_idx,
                        A, E, mask, (const int32_t*)nullptr, 1, 1, o, local_src, remote_src, inv, 0, T, p0, p1);
@@ -107,9 +107,12 @@ prism_status launch_dispatch(const prism_layer_desc& d, const int32_t* topk_idx,
   hipLaunchKernelGGL(dispatch_hist_kernel, dim3(n_blocks), dim3(kThreads), 0, st, topk_idx, A, E, sub,
                      block_hist);
   PRISM_CHECK_LAUNCH();
-  hipLaunchKernelGGL((dispatch_place_kernel<true, kDispatchChunk>), dim3(n_blocks + n_sched), dim3(kThreads),
-                     0, st, topk_idx, A, E, mask, block_hist, n_blocks, sub, o, local_src, remote_src, inv,
-                     d.n_shared, T, p0, p1);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(n_blocks + n_sched), dim3(kThreads), 0, st, topk_idx, A, E, mask, block_hist, n_blocks,
+                       sub, o, local_src, remote_src, inv, d.n_shared, T, p0, p1);
+  };
+  if (p0.wide_ntiles > 0) launch(dispatch_place_kernel<true, kDispatchChunk, true>);
+  else launch(dispatch_place_kernel<true, kDispatchChunk>);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }
@@ -122,17 +125,21 @@ prism_status launch_place_counted(const prism_layer_desc& d, const int32_t* topk
   const int A = T * d.top_k;
   const SplitOut o{local_offsets, remote_offsets, n_local_remote, remote_bytes, counts,
                    (unsigned long long*)counts_accum, d.hidden * elem_size(d.dtype)};
-  gg::SchedParams p0, p1;
+  gg::WidthParams p0, p1;
   gg::ffn_sched_params(d, T, tiles, &p0, &p1);
   const dim3 grid(plan.n_blocks + 2 * kSchedParts);
-  if (plan.chunk == kFineChunk)
-    hipLaunchKernelGGL((dispatch_place_kernel<true, kFineChunk>), grid, dim3(kThreads), 0, st, topk_idx, A,
-                       d.n_experts, mask, plan.block_hist, plan.n_blocks, plan.sub, o, local_src, remote_src,
-                       inv, d.n_shared, T, p0, p1);
-  else
-    hipLaunchKernelGGL((dispatch_place_kernel<true, kDispatchChunk>), grid, dim3(kThreads), 0, st, topk_idx, A,
-                       d.n_experts, mask, plan.block_hist, plan.n_blocks, plan.sub, o, local_src, remote_src,
-                       inv, d.n_shared, T, p0, p1);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, topk_idx, A, d.n_experts, mask, plan.block_hist, plan.n_blocks,
+                       plan.sub, o, local_src, remote_src, inv, d.n_shared, T, p0, p1);
+  };
+  const bool fine = plan.chunk == kFineChunk;
+  if (p0.wide_ntiles > 0) {
+    if (fine) launch(dispatch_place_kernel<true, kFineChunk, true>);
+    else launch(dispatch_place_kernel<true, kDispatchChunk, true>);
+  } else {
+    if (fine) launch(dispatch_place_kernel<true, kFineChunk>);
+    else launch(dispatch_place_kernel<true, kDispatchChunk>);
+  }
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
 }

@@ -35,8 +35,12 @@ template <int BM_, int BN_, int BK_, int STAGES_> struct TileCfg {
 // to the times of a 32-token batch of the 4096 x 14336 layer run with 2 to 8 splits.
 constexpr float kSplitRoundBytes = 14 * 8192.f;
 
+// Wide tiles of a path with two widths (schedule.h, "Two widths"): ring of their own, fewest items.
+constexpr int kWideStages = 3;
+constexpr int kWideItemsUp = 150, kWideItemsDown = 40;
+
 // What the schedule builders need to know about a path's two GEMMs (C1: gate/up, C2: down).
-template <typename C1, typename C2, bool SPLIT_DOWN, bool ROTATE>
+template <typename C1, typename C2, bool SPLIT_DOWN, bool ROTATE, bool WIDTHS>
 FfnShapes shapes_of(const prism_layer_desc& d, int T) {
   FfnShapes f{};
   f.bm1 = C1::BM;
@@ -54,6 +58,14 @@ FfnShapes shapes_of(const prism_layer_desc& d, int T) {
     f.split_round_kt2 = kSplitRoundBytes / kt_bytes;
     // one more split: every row written once more as fp32 and read once more, shared by all workgroups
     f.split_row_kt2 = (float)d.hidden * 8.f / (float)(gg::kXcds * f.split_wgs2) / kt_bytes;
+  }
+  if (WIDTHS) {
+    static_assert(!WIDTHS || (SPLIT_DOWN && ROTATE && kWideStages <= C1::STAGES && kWideStages <= C2::STAGES),
+                  "the wide tiles' ring is no longer than the slices that the narrow ones allow");
+    f.wide_nt1 = ceil_div(d.ffn, C1::BN);
+    f.wide_nt2 = ceil_div(d.hidden, 2 * C2::BN);
+    f.wide_items1 = kWideItemsUp;
+    f.wide_items2 = kWideItemsDown;
   }
   return f;
 }
@@ -160,7 +172,7 @@ __global__ __launch_bounds__(256) void pack_tokens_kernel(const uint4* __restric
   for (int j = 0; j < 8; ++j)
     if (tile0 + j < tiles) dst[(tile0 + j) * 64] = v[j];
 }
-template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B, bool ROTATE>
+template <typename C1, typename C2, bool SPLIT_DOWN, bool STREAM_B, bool ROTATE, bool WIDTHS>
 prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_expert_weights& w,
                           const int32_t* local_src, const int32_t* local_offsets, int T, void* y,
                           void* h, bool h_tiled, void* x_rows, int32_t* tiles, float* part, float* slice_part, hipStream_t st,
@@ -175,11 +187,11 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   int32_t* sched2 = tiles + tile_table_ints(d, T);
   // The schedules (built here, or by the caller's dispatch) follow ffn_schedule_shapes(), which
   // must describe the kernels this instantiation launches.
-  const FfnShapes f = shapes_of<C1, C2, SPLIT_DOWN, ROTATE>(d, T);
+  const FfnShapes f = shapes_of<C1, C2, SPLIT_DOWN, ROTATE, WIDTHS>(d, T);
   const FfnShapes told = ffn_schedule_shapes(d, T);
   if (f.bm1 != told.bm1 || f.nt1 != told.nt1 || f.bm2 != told.bm2 || f.nt2 != told.nt2 ||
       f.interleave != told.interleave || f.slice_kt2 != told.slice_kt2 || f.split_kt2 != told.split_kt2 ||
-      f.split_wgs2 != told.split_wgs2)
+      f.split_wgs2 != told.split_wgs2 || f.wide_nt1 != told.wide_nt1 || f.wide_nt2 != told.wide_nt2)
     return PRISM_ERR_LAUNCH;
   const int nt1 = f.nt1, nt2 = f.nt2;
   // the down projection's last round of items may be cut along the contraction (prefill only)
@@ -220,8 +232,13 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
     g1.a_kstep = 1024;
   }
   trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
-  PRISM_TRY((gg::launch_gemm<C1::BM, C1::BN, 2, 2, C1::BK, C1::STAGES, true, false, ROTATE, STREAM_B>(
-      g1, gg::sched_capacity(d, T, C1::BM, nt1), st)));
+  if constexpr (WIDTHS) {
+    static_assert(STREAM_B && ROTATE, "as the kernel's narrow tiles");
+    PRISM_TRY((gg::launch_gemm_widths<C1::BM, C1::BN, C1::BK, C1::STAGES, kWideStages, true, false>(g1, st)));
+  } else {
+    PRISM_TRY((gg::launch_gemm<C1::BM, C1::BN, 2, 2, C1::BK, C1::STAGES, true, false, ROTATE, STREAM_B>(
+        g1, gg::sched_capacity(d, T, C1::BM, nt1), st)));
+  }
   trace(stage_events, PRISM_STAGE_FFN_UP, 1, st);
 
   GemmArgs g2{};
@@ -240,8 +257,12 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
   // SPLIT_DOWN: the number of contraction slices is in the schedule's header (schedule.h, "Splits")
   const int32_t* n_splits = sched2 + 2;
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 0, st);
-  PRISM_TRY((gg::launch_gemm<C2::BM, C2::BN, 2, 2, C2::BK, C2::STAGES, false, SPLIT_DOWN, ROTATE, STREAM_B>(
-      g2, gg::sched_capacity(d, T, C2::BM, nt2), st)));
+  if constexpr (WIDTHS) {
+    PRISM_TRY((gg::launch_gemm_widths<C2::BM, C2::BN, C2::BK, C2::STAGES, kWideStages, false, SPLIT_DOWN>(g2, st)));
+  } else {
+    PRISM_TRY((gg::launch_gemm<C2::BM, C2::BN, 2, 2, C2::BK, C2::STAGES, false, SPLIT_DOWN, ROTATE, STREAM_B>(
+        g2, gg::sched_capacity(d, T, C2::BM, nt2), st)));
+  }
   if constexpr (kCanSlice) {
     if (slice_kt > 0)   // the cut last round: one slice entry per workgroup, fp32 partial tiles
       PRISM_TRY((gg::launch_gemm<C2::BM, C2::BN, 2, 2, C2::BK, C2::STAGES, false, false, false, false, true>(
@@ -266,11 +287,12 @@ prism_status run_bf16_ffn(const prism_layer_desc& d, const void* x, const prism_
 
 // One tile path of the bf16 FFN: tile shapes of the two GEMMs, whether the down projection is
 // split along its contraction, whether the weight loads are marked non-temporal, whether the items
-// are dealt to the XCDs one by one with rotated contractions (grouped_gemm.h, ROTATE).
-template <typename C1_, typename C2_, bool SPLIT_DOWN_, bool STREAM_B_, bool ROTATE_> struct Path {
+// are dealt to the XCDs one by one with rotated contractions (grouped_gemm.h, ROTATE), whether the
+// schedule may choose tiles twice as wide instead.
+template <typename C1_, typename C2_, bool SPLIT_DOWN_, bool STREAM_B_, bool ROTATE_, bool WIDTHS_ = false> struct Path {
   using C1 = C1_;
   using C2 = C2_;
-  static constexpr bool kSplitDown = SPLIT_DOWN_, kStreamB = STREAM_B_, kRotate = ROTATE_;
+  static constexpr bool kSplitDown = SPLIT_DOWN_, kStreamB = STREAM_B_, kRotate = ROTATE_, kWidths = WIDTHS_;
 };
 
 // Calls fn(Path<...>{}) with the path that serves a bf16 batch of T tokens of layer d (ffn_paths.h).
@@ -283,7 +305,7 @@ auto select_path(const prism_layer_desc& d, int T, Fn&& fn) {
     case FfnPath::kDecodeTiled: return fn(Path<TileCfg<64, 128, 32, 8>, TileCfg<64, 128, 32, 8>, true, true, true>{});
     case FfnPath::kDecode: return fn(Path<Decode, Decode, true, true, true>{});
     case FfnPath::kDecodeShort: return fn(Path<TileCfg<64, 128, 32, 3>, TileCfg<64, 128, 32, 3>, true, true, true>{});
-    case FfnPath::kStream: return fn(Path<Square, Square, true, true, true>{});
+    case FfnPath::kStream: return fn(Path<Square, Square, true, true, true, true>{});
     case FfnPath::kSplitSquare: return fn(Path<Square, Square, true, false, false>{});
     case FfnPath::kSplitWide: return fn(Path<Wide, Wide, true, false, false>{});
     case FfnPath::kFewRows64: return fn(Path<Decode, Decode, false, true, false>{});
@@ -316,7 +338,7 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
   if (align_up(rows, 16) * d.ffn * 2 >= kMaxOperandBytes) h_tiled = false;   // (the buffer holds the plain rows too)
   return select_path(d, T, [&](auto path) {
     using P = decltype(path);
-    return run_bf16_ffn<typename P::C1, typename P::C2, P::kSplitDown, P::kStreamB, P::kRotate>(
+    return run_bf16_ffn<typename P::C1, typename P::C2, P::kSplitDown, P::kStreamB, P::kRotate, P::kWidths>(
         d, x, w, local_src, local_offsets, T, y, h, h_tiled, x_rows, tiles, part, slice_part, st, stage_events, deferred_splits,
         schedules_built);
   });
@@ -325,7 +347,7 @@ prism_status launch_expert_ffn(const prism_layer_desc& d, const void* x,
 FfnShapes ffn_schedule_shapes(const prism_layer_desc& d, int T) {
   return select_path(d, T, [&](auto path) {
     using P = decltype(path);
-    return shapes_of<typename P::C1, typename P::C2, P::kSplitDown, P::kRotate>(d, T);
+    return shapes_of<typename P::C1, typename P::C2, P::kSplitDown, P::kRotate, P::kWidths>(d, T);
   });
 }
 

@@ -67,7 +67,7 @@ enum class FfnPath {
   kDecodeTiled,    // 64 x 128 tiles, 32-wide k-tiles; contraction of the down projection split
   kDecode,         // 64 x 128, 64-wide k-tiles; split
   kDecodeShort,    // the same with a short ring, for short contractions
-  kStream,         // 128 x 128, weights non-temporal, items dealt to the XCDs one by one; split
+  kStream,         // 128 x 128, weights non-temporal, items dealt to the XCDs one by one, or 128 x 256 in lists (the device chooses); split
   kSplitSquare,    // 128 x 128; split
   kSplitWide,      // 128 x 256; split
   kFewRows64,      // 64 x 128, weights non-temporal
@@ -101,9 +101,9 @@ static inline FfnPath ffn_path(const prism_layer_desc& d, int T) {
   // contraction as for decode batches.  64-wide k-tiles take whole 128-byte lines of the
   // activations (and of row-major weights), which 32-wide ones ask the L2 for twice.
   // Up to 256 tokens an expert has one or two row tiles: 128 x 128, dealt item by item and
-  // non-temporal.  128 x 256 tiles halve the number of items, and the host does not know how many
-  // experts are hosted: with one or two of 8, a layer has fewer wide tiles than the machine has
-  // workgroups.  Layer, weights from HBM, 128 x 128 against 128 x 256: 4096 x 14336, 66 tokens, 1 hosted
+  // non-temporal, unless some expert has two and 128 x 256 tiles make items enough, which only the
+  // device knows (schedule.h, "Two widths"): with one or two of 8 hosted, a layer has fewer wide tiles
+  // than the machine has workgroups.  Layer, weights from HBM, 128 x 128 against 128 x 256: 4096 x 14336, 66 tokens, 1 hosted
   // 94 / 128 us; 200 tokens, 1 hosted, evenly spread picks 104 / 143 (the other way with 5 hosted, 412 /
   // 376); 3072 x 8192, 96 tokens, 2 hosted 83 / 101; 2048 x 8192, 66 tokens, 5 hosted 116 / 132, and 131 if
   // dealt in rectangles with temporal loads.  16 shapes, 1 to 8 hosted, against the better of those two for

@@ -246,6 +246,9 @@ struct FfnShapes {
   int split_wgs2;           // workgroups per XCD of the launch
   float split_round_kt2;    // fixed cost of a round of items, in k-tiles of one workgroup
   float split_row_kt2;      // cost of one more fp32 copy of a row, in k-tiles of one workgroup
+  // Tiles twice as wide that the schedule builder may choose instead (schedule.h, "Two widths"); 0: none.
+  int wide_nt1, wide_nt2;         // their column tiles
+  int wide_items1, wide_items2;   // fewest items they are taken from
 };
 FfnShapes ffn_schedule_shapes(const prism_layer_desc& d, int T);
 

@@ -910,8 +910,8 @@ prism_status launch_decode_front_end(const prism_layer_desc& d, const void* x, c
   const int n_hsplit = ceil_div(d.hidden, route_h_span(d.hidden));
   const dispatch_dev::SplitOut o{local_offsets, remote_offsets, n_local_remote, remote_bytes, counts,
                                  (unsigned long long*)counts_accum, d.hidden * elem_size(d.dtype)};
-  gg::SchedParams p0, p1;
-  gg::ffn_sched_params(d, T, tiles, &p0, &p1);
+  gg::WidthParams p0, p1;
+  gg::ffn_sched_params(d, T, tiles, &p0, &p1);   // (decode tiles have one width)
   trace(stage_events, PRISM_STAGE_DISPATCH, 0, st);
   hipLaunchKernelGGL(decode_front_end_kernel, dim3(1), dim3(kFrontThreads), 0, st, route_part, n_hsplit, bias, T, E,
                      d.top_k, d.n_shared, d.bias_group_tokens, d.gate_mode, topk_idx, topk_gate, mask, o,

@@ -3,6 +3,8 @@
 #ifndef PRISM_SCHEDULE_H_
 #define PRISM_SCHEDULE_H_
 
+#include <type_traits>
+
 #include "prism_internal.h"
 
 namespace prism {
@@ -19,6 +21,7 @@ constexpr int kReduceInts = 8;       // ints per entry of the list of sliced ite
 
 // Schedule memory (int32):
 //   [0] n_mtiles  [1] capacity of one XCD list (entries)  [2] contraction splits (see "Splits")
+//   [3] 1: the tiles are twice as wide (see "Two widths")
 //   [4 + x] items in the list of XCD x
 //   [20 + x] slice entries of XCD x (they occupy the last kSliceSlots places of its list)
 //   then, from int kSchedHeader on, for schedules that deal their items to the XCDs one by
@@ -56,6 +59,18 @@ constexpr int kReduceInts = 8;       // ints per entry of the list of sliced ite
 // workgroups of a round share the memory bandwidth, so that a thin last round costs less than a
 // full one, was fitted to the same measurements and chose worse: it leaves the 20 items per XCD
 // of five hosted experts whole, 109 us against 96 us with three splits.)
+//
+// Two widths.  A launch may offer tiles of BM x BN dealt to the XCDs one by one and tiles of BM x 2 BN in
+// lists (below), and which are better depends on how many experts are hosted and how popular they are.  While every
+// group has one row tile, its weights stream once whatever the tile, and the narrow, non-temporal one streams
+// faster.  A group with more row tiles reads its weights once per row tile: next to each other in
+// an XCD's list the later ones find the weight tile in the L2, and twice the width halves how often activations
+// are read -- if the wide tiles still make items for most of the machine (wide_items).
+// 504 batches of 66 to 256 tokens of six layers, 1024 x 7168 to 4096 x 14336, 1 to all experts hosted, even and
+// skewed picks, time in wide tiles over time in narrow ones.  Gate/up, some group with more than one row tile: fewer than
+// 150 wide items 1.02-1.36, 150 to 300 0.82 on average, beyond 0.90, at most 1.07; down projection (split): fewer than
+// 40 wide items 1.03, from there 0.86.  All groups with one row tile: 1.09 and 1.04.  (4096 x 14336, 200 tokens, 6
+// experts hosted: gate/up 290 -> 274 us, down and combine 183 -> 141, layer 512 -> 455; 4 hosted, 256 tokens 457 -> 372.)
 //
 // Work order.  A group's row tiles are split into equal parts of at most kRectRows.  All
 // items -- groups in order, then row parts, then the column tiles of a row part, the row tiles
@@ -95,6 +110,14 @@ struct SchedParams {
   float split_round_kt;   // fixed cost of a round, in k-tiles of one workgroup
   float split_row_kt;     // cost of one more fp32 copy of one row, in k-tiles of one workgroup
 };
+
+// The same with two widths to choose from ("Two widths" above).  A type and builders of their own: with a choice
+// to look at, the launches of a few microseconds that have none would be 0.6 us longer.
+struct WidthParams : SchedParams {
+  int wide_ntiles;   // column tiles of the wide tiles; 0: no choice
+  int wide_items;    // fewest items they are taken from
+};
+template <bool WIDTHS> using sched_params_t = std::conditional_t<WIDTHS, WidthParams, SchedParams>;
 
 // Where the list of sliced items starts (ints from the start of the schedule).
 __host__ __device__ inline size_t sched_reduce_offset(int capacity) {
@@ -141,13 +164,14 @@ __device__ __forceinline__ Slicing slicing_of(int n, int longest, int slice_kt) 
 // this workgroup (with a barrier in between), hence no __restrict__ on it.
 // Several workgroups can share the work: workgroup `part` of `n_parts` writes every
 // n_parts-th group of blockDim.x items, part 0 also the header.
-template <int NS>
+template <int NS, bool WIDTHS = false>
 __device__ __forceinline__ void build_schedules_block(const int32_t* local_offsets, int E, int S,
                                                       int T, int A_total,
-                                                      const SchedParams (&p)[NS], int part = 0,
+                                                      const sched_params_t<WIDTHS> (&p)[NS], int part = 0,
                                                       int n_parts = 1) {
   __shared__ int s_rows[kMaxGroups], s_row0[kMaxGroups];
   __shared__ int s_start[NS][kMaxGroups + 1];            // first row tile of group g
+  __shared__ int s_wide[NS];                             // see "Two widths"
   __shared__ unsigned s_routed[NS][kXcds + 1], s_all[NS][kXcds + 1];   // see "Work order": items before XCD x's
   const int G = E + S;
   // p[s] for a thread-dependent s, without indexing the parameter array at run time
@@ -172,8 +196,8 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
   const int lane = threadIdx.x & 63;
   if ((int)(threadIdx.x >> 6) < NS) {
     const int s = threadIdx.x >> 6;
-    const SchedParams ps = pick(s);
-    int run = 0, routed_tiles = 0;
+    const sched_params_t<WIDTHS> ps = pick(s);
+    int run = 0, routed_tiles = 0, taken = 0;   // (taken: groups with rows)
     for (int g0 = 0; g0 < G; g0 += 64) {
       const int g = g0 + lane;
       const int rows = g < G ? s_rows[g] : 0;
@@ -182,14 +206,25 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
       if (g < G) s_start[s][g] = run + incl - tiles;
       if (E - g0 >= 1 && E - g0 <= 64) routed_tiles = run + __builtin_amdgcn_readlane(incl, E - g0 - 1);
       run += __builtin_amdgcn_readlane(incl, 63);
+      if (WIDTHS) taken += __popcll(__ballot(tiles > 0));
     }
+    bool wide = false;
+    int n_ntiles = ps.n_ntiles;
+    if constexpr (WIDTHS)
+      if (run > taken && run * ps.wide_ntiles >= ps.wide_items) {
+        wide = true;
+        n_ntiles = ps.wide_ntiles;
+      }
     const int rows_total = s_row0[E - 1] + s_rows[E - 1] + S * T;   // all rows of all groups
-    if (lane == 0) s_start[s][G] = run;
-    const unsigned total = (unsigned)run * (unsigned)ps.n_ntiles;
+    if (lane == 0) {
+      s_start[s][G] = run;
+      if (WIDTHS) s_wide[s] = wide;
+    }
+    const unsigned total = (unsigned)run * (unsigned)n_ntiles;
     const unsigned per_xcd = (total + kXcds - 1) / kXcds;
     // items dealt to the XCDs before XCD x: routed ones, and all of them (fewer than 8 shared items
     // are counted as routed ones, so that no XCD's share of either is negative)
-    unsigned routed_items = (unsigned)routed_tiles * (unsigned)ps.n_ntiles;
+    unsigned routed_items = (unsigned)routed_tiles * (unsigned)n_ntiles;
     if (total - routed_items < kXcds) routed_items = total;
     auto eighths = [&](unsigned items, int x) { return (unsigned)((unsigned long long)items * (unsigned)x / kXcds); };
     if (lane <= kXcds) {
@@ -200,11 +235,12 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
       if (lane == 0) {
         ps.sched[0] = run;
         ps.sched[1] = ps.capacity;
+        if (WIDTHS) ps.sched[3] = wide;
       }
       if (lane < kXcds) {
         const unsigned x = lane;
         unsigned count;
-        if (ps.interleave)   // items x, x + 8, ...
+        if (ps.interleave && !wide)   // items x, x + 8, ...
           count = total > x ? (total - x + kXcds - 1) / kXcds : 0;
         else
           count = eighths(total, lane + 1) - eighths(total, lane);
@@ -218,8 +254,9 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
       float cost = INFINITY;
       if (ps.split_kt > 0 && sp <= min(ps.split_max, 8) && slots >= 1 && ps.split_kt / sp >= ps.split_min_kt) {
         const int rounds = ((int)per_xcd + slots - 1) / slots;   // per_xcd: the longest XCD list
-        cost = (float)rounds * ((float)((ps.split_kt + sp - 1) / sp) + ps.split_round_kt) +
-               (float)sp * (float)rows_total * ps.split_row_kt;
+        const float unit = wide ? 0.5f : 1.f;                    // (a k-tile of twice the width takes twice as long)
+        cost = (float)rounds * ((float)((ps.split_kt + sp - 1) / sp) + unit * ps.split_round_kt) +
+               (float)sp * (float)rows_total * unit * ps.split_row_kt;
       }
       static_assert(kDecodeSplits <= 8, "the candidates sit in lanes 0..7");
       int best = sp;
@@ -238,8 +275,12 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
   lds_barrier();
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    const int BM = p[s].BM, n_ntiles = p[s].n_ntiles, capacity = p[s].capacity;
-    const bool interleave = p[s].interleave != 0;
+    const bool wide = WIDTHS && s_wide[s] != 0;
+    int n_ntiles = p[s].n_ntiles;
+    if constexpr (WIDTHS)
+      if (wide) n_ntiles = p[s].wide_ntiles;
+    const int BM = p[s].BM, capacity = p[s].capacity;
+    const bool interleave = p[s].interleave != 0 && !wide;
     const int n_mtiles = s_start[s][G];
     auto group_of_tile = [&](int i) {   // largest g with s_start[g] <= i (skips empty groups)
       int lo = 0, hi = G;               // invariant: s_start[lo] <= i < s_start[hi]
@@ -338,14 +379,14 @@ static inline int sched_capacity(const prism_layer_desc& d, int T, int BM, int n
 
 // Parameters of the two schedules of launch_expert_ffn for a bf16 batch of T tokens, which live
 // side by side in `tiles` (2 x tile_table_ints): what every kernel that builds them is given.
-static inline void ffn_sched_params(const prism_layer_desc& d, int T, int32_t* tiles, SchedParams* p0,
-                                    SchedParams* p1) {
+static inline void ffn_sched_params(const prism_layer_desc& d, int T, int32_t* tiles, WidthParams* p0,
+                                    WidthParams* p1) {
   const FfnShapes f = ffn_schedule_shapes(d, T);
-  *p0 = SchedParams{f.bm1, f.nt1, sched_capacity(d, T, f.bm1, f.nt1), tiles, f.interleave ? 1 : 0,
-                    0, 0, 0, 0, 0, 0.f, 0.f};
-  *p1 = SchedParams{f.bm2, f.nt2, sched_capacity(d, T, f.bm2, f.nt2), tiles + tile_table_ints(d, T),
+  *p0 = WidthParams{{f.bm1, f.nt1, sched_capacity(d, T, f.bm1, f.nt1), tiles, f.interleave ? 1 : 0,
+                    0, 0, 0, 0, 0, 0.f, 0.f}, f.wide_nt1, f.wide_items1};
+  *p1 = WidthParams{{f.bm2, f.nt2, sched_capacity(d, T, f.bm2, f.nt2), tiles + tile_table_ints(d, T),
                     f.interleave ? 1 : 0, f.slice_kt2, f.split_kt2, max_splits(d, T), f.split_min_kt2,
-                    f.split_wgs2, f.split_round_kt2, f.split_row_kt2};
+                    f.split_wgs2, f.split_round_kt2, f.split_row_kt2}, f.wide_nt2, f.wide_items2};
 }
 
 }  // namespace gg

@@ -135,3 +135,43 @@ def test_layer_parity_on_a_random_streaming_shape(i):
     err = check_layer(cfg, o, ref, per_row=i in PER_ROW_STREAMING_CASES)
     print(f"streaming case {i}: out err {err:.3g}, n_local {ref.dispatch.n_local}, n_remote {ref.dispatch.n_remote}")
 
+
+
+@pytest.mark.parametrize("tiled", [False, True])
+@pytest.mark.parametrize("T,k,H,F,rows", [
+    (128, 1, 256, 9600, (128, 0)),               # one row tile per expert: narrow tiles in both
+    (129, 1, 256, 9600, (129, 0)),               # 150 wide items of gate/up: wide
+    (129, 1, 256, 9536, (0, 129)),               # 149 of them (one column tile half full): narrow
+    (130, 2, 2560, 1024, (130, 129)),            # 40 wide items of the down projection: wide
+    (130, 2, 2368, 1088, (130, 129, 1)),         # 50, the last column tile a quarter full, a third expert with one row
+    (130, 2, 2304, 1024, (130, 129)),            # 36: narrow
+    (256, 3, 2624, 9664, (256, 129, 100, 0, 1))])  # both wide, ragged in every size
+def test_expert_ffn_at_the_lines_between_tile_widths(T, k, H, F, rows, tiled):
+    """Batches of 65 to 256 tokens of wide layers: the device chooses between two widths of the tiles, for each of the
+    two GEMMs, by the row tiles and the items it counts.  Against plain fp32 products, with the bar of the other
+    tests; rows past the list must stay as they were."""
+    import torch
+    import paper_2508_12851_amd as P
+    from gpu_util import TOL, rel_err, to_f32
+    rng = np.random.default_rng([T, H, F])
+    E, n = len(rows), sum(rows)
+    gen = torch.Generator(device="cuda").manual_seed(T + H + F)
+    draw = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)
+    x = draw(T, H)
+    experts = [(draw(F, H) * H ** -0.5, draw(F, H) * H ** -0.5, draw(H, F) * F ** -0.5) for _ in rows]
+    src = torch.full((T * k,), -1, dtype=torch.int32, device="cuda")
+    src[:n] = torch.from_numpy(rng.integers(0, T * k, n).astype(np.int32)).cuda()
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)).cuda()
+    desc = P.make_desc(H, F, E, k, 0, "bf16", weight_layout="tiled" if tiled else "row_major")
+    wt = P.WeightTable([tuple(P.prism_pack_weights(w) if tiled else w for w in ws) for ws in experts])
+    y = torch.full((T * k, H), 7.0, dtype=torch.bfloat16, device="cuda")
+    P.prism_expert_ffn(desc, x, wt, src, off, P.alloc_workspace(desc, T), y=y)
+    torch.cuda.synchronize()
+    ref, r0 = [], 0
+    for (wg, wu, wd), m in zip(experts, rows):
+        xr = x[(src[r0:r0 + m] // k).long()].float()
+        h = (torch.nn.functional.silu(xr @ wg.float().t()) * (xr @ wu.float().t())).to(torch.bfloat16).float()
+        ref.append(h @ wd.float().t())
+        r0 += m
+    assert rel_err(to_f32(y)[:n], torch.cat(ref).cpu().numpy()) <= TOL["bf16"]
+    assert bool((y[n:] == 7.0).all())
