@@ -19,8 +19,8 @@
 // have accumulators of their own (16 terms per rounding, chains of K / 128), the other five products, 2^-8 and
 // below, share a second set, and the eighths are added as a tree.  Relative 2-norm of the FFN's error against
 // 64 bits, N(0, 1) tokens, H x F: 256 x 512 1.27e-7 (in fp32 1.50e-7), 1024 x 2048 1.72e-7 (1.78e-7), 2048 x 1024
-// 1.79e-7 (1.86e-7), 4096 x 512 2.18e-7 (2.10e-7): contractions beyond 2048 stay in fp32, and so does a
-// wavefront's eighth whose sums are not finite, because an infinity has no parts.
+// 1.79e-7 (1.86e-7), 4096 x 512 2.18e-7 (2.10e-7): contractions beyond 2048 stay in fp32 (LONG).  What has no parts, infinities and
+// very small values, is looked at again (see "Small values").
 #include "prism_internal.h"
 
 namespace prism {
@@ -48,14 +48,26 @@ constexpr int kRowBytes = kBK * 4;
 constexpr int kStageBytes = (kBM + kBN) * kRowBytes;         // one wavefront's k-tile
 constexpr int kRedPitch = kBN + 4;                           // floats; rows start in different banks
 constexpr int kRedFloats = kBM * kRedPitch;                  // one wavefront's partial tile
-constexpr int kLdsBytes = kWaves * kStageBytes + kWaves / 2 * kRedFloats * 4;   // k-tiles, partial tiles
-static_assert(kLdsBytes <= 160 * 1024, "LDS per workgroup");
+constexpr int kTileBytes = kWaves * kRedFloats * 4;
+constexpr int kMarkWords = 32;           // one bit per item of a workgroup, from the start again after 1024
+constexpr int kLdsBytes = kTileBytes + (kMarkWords + 1) * 4 + (PRISM_MAX_EXPERTS + 1) * 4;   // (+ one word: any mark)
+static_assert(kRedFloats * 4 >= kStageBytes && kLdsBytes <= 160 * 1024, "a partial tile replaces its wavefront's k-tile");
+// Which sums of products of parts are good (see "Small values"): of operands up to kPlainMax those from kPlainMin on, otherwise those
+// beyond kLossPerOperand (A + B) + kLossFloor.
+constexpr float kPlainMax = 0x1p30f, kPlainMin = 0x1p-60f;
+constexpr float kLossPerOperand = 0x1p-99f, kLossFloor = 0x1p-116f;
 
 // Rows of fp32 matrices start at any multiple of 4 bytes (F need not be a multiple of 4).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 // Pointers that come out of a table in memory: said to be global memory, which the compiler cannot know.
 typedef const __attribute__((address_space(1))) float* global_ptr;
 typedef const __attribute__((address_space(1))) f32x4u* global_ptr4;
+
+// Entry i, the same in all lanes, of a table of weight pointers, which no kernel writes: a scalar load.
+__device__ __forceinline__ global_ptr table_entry(const void* const* table, int i) {
+  typedef const __attribute__((address_space(4))) uint64_t* const_table;
+  return (global_ptr)((const_table)(uint64_t)table)[__builtin_amdgcn_readfirstlane(i)];
+}
 
 struct RowTile {
   int g;           // expert (g < E), shared expert E + s, or -1: nothing here
@@ -64,24 +76,22 @@ struct RowTile {
   int tok_base;    // shared experts: token of the first row; routed ones: -1
 };
 
-// The row tiles: those of the routed experts in expert order, then those of the shared ones.  Every
-// wavefront holds the offsets of four experts per lane and finds a tile by its number with a ballot.
+// The row tiles: those of the routed experts in expert order, then those of the shared ones.  A lane
+// stands for four experts, and a wavefront finds a tile by its number with a ballot.
 // All are 64 or all are 32 rows high, whichever takes less time by the rounds of items it makes of the launch's
-// workgroups: 887 rows of 5 experts x 16 column tiles are 272 items of 64 rows, two rounds on 256 workgroups, and
+// workgroups (half_tile: time of a lower one): 887 rows of 5 experts x 16 column tiles are 272 items of 64 rows, two rounds on 256 workgroups, and
 // 496 of 32, also two (down projection of 2048 x 1024, 62 -> 52 us); 64 tokens make one round of either, and lower tiles
 // spread the work further (layer of 256 x 512: 36.9 -> 34.6 us).
 struct RowTiles {
-  int off[5];      // offsets of experts 4 lane .. 4 lane + 4
+  const int* off;  // LDS: offsets of experts 4 lane .. 4 lane + 4
   int before;      // row tiles of the experts before lane's
   int routed;      // row tiles of all routed experts
   int shift;       // 2^shift rows per tile
 };
 __device__ __forceinline__ int tiles_of(int rows, int shift) { return (rows + (1 << shift) - 1) >> shift; }
-__device__ __forceinline__ RowTiles load_row_tiles(const F32Args& p, int n_col_tiles) {
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ RowTiles load_row_tiles(const F32Args& p, int n_col_tiles, float half_tile, int tid, const int* s_off) {
   RowTiles r;
-#pragma unroll
-  for (int j = 0; j < 5; ++j) r.off[j] = p.local_offsets[min(4 * lane + j, p.E)];
+  r.off = s_off + 4 * (tid & 63);
   float best = INFINITY;
 #pragma unroll
   for (int shift = 6; shift >= 5; --shift) {
@@ -91,7 +101,7 @@ __device__ __forceinline__ RowTiles load_row_tiles(const F32Args& p, int n_col_t
     const int incl = wave_inclusive_scan(tiles);
     const int routed = __builtin_amdgcn_readlane(incl, 63);
     const float items = (float)(routed + p.S * tiles_of(p.T, shift)) * (float)n_col_tiles;
-    const float time = ceilf(items / (float)gridDim.x) * (shift == 6 ? 1.f : kHalfTile);
+    const float time = ceilf(items / (float)gridDim.x) * (shift == 6 ? 1.f : half_tile);
     if (time < best) {
       best = time;
       r.before = incl - tiles;
@@ -101,7 +111,7 @@ __device__ __forceinline__ RowTiles load_row_tiles(const F32Args& p, int n_col_t
   }
   return r;
 }
-__device__ __forceinline__ RowTile row_tile(const F32Args& p, const RowTiles& r, int b) {
+__device__ __forceinline__ RowTile row_tile(const F32Args& p, const RowTiles& r, int tid, int b) {
   if (b < r.routed) {
     int rel = b - r.before, e = 0, start = 0, count = 0;
     bool mine = false;
@@ -110,7 +120,7 @@ __device__ __forceinline__ RowTile row_tile(const F32Args& p, const RowTiles& r,
       const int t = tiles_of(r.off[j + 1] - r.off[j], r.shift);
       if (rel >= 0 && rel < t) {
         mine = true;
-        e = 4 * (threadIdx.x & 63) + j;
+        e = 4 * (tid & 63) + j;
         start = r.off[j] + (rel << r.shift);
         count = min(1 << r.shift, r.off[j + 1] - start);
       }
@@ -145,17 +155,20 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t minus_lo, 
   }
 }
 
-template <bool GATED>
-__global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the bf16 dot product exists in device code only
-  extern __shared__ __align__(16) float smem[];
+// A workgroup's walk over its items.  LONG: products in fp32.  AGAIN: only the marked items, with a closer look at their
+// sums (see "Small values").  That is a walk of its own, with registers of its own: inside the first one its code made the
+// smallest FFN 20.1 us instead of 18.2, and 4 us of the larger ones.
+template <bool GATED, bool LONG, bool AGAIN>
+__device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, const int tid) {
+  uint32_t* const marks = reinterpret_cast<uint32_t*>(smem) + kTileBytes / 4;
   const int K = GATED ? p.H : p.F, N = GATED ? p.F : p.H;
   constexpr int kCols = GATED ? kBN / 2 : kBN;      // output columns of the tile
   // Consecutive workgroups go to the 8 XCDs in turn; every XCD takes a contiguous eighth of the
   // items, row tiles running fastest, so that the row tiles of an expert read its weight rows
   // through one L2.
   const int n_col_tiles = (N + kCols - 1) / kCols;
-  const RowTiles tiles = load_row_tiles(p, n_col_tiles);
+  const RowTiles tiles = load_row_tiles(p, n_col_tiles, kHalfTile, tid, reinterpret_cast<int*>(marks) + kMarkWords + 1);
   const int n_row_tiles = tiles.routed + p.S * tiles_of(p.T, tiles.shift);
   const int n_items = n_row_tiles * n_col_tiles;
   const int xcd = blockIdx.x % kXcds, slots = gridDim.x / kXcds;
@@ -163,13 +176,13 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
   int item = (int)((long long)n_items * xcd / kXcds) + blockIdx.x / kXcds;
   if (item >= item_end) return;
 
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r32 = lane & 31, q = lane >> 5;
 
   // ---- global -> LDS assignment: lane l brings chunk l % 4 (4 elements) of rows l / 4 + 16 i ----
   const int lrow = lane >> 2, chunk = lane & 3;
-  const float* a_ptr[4];
+  uint32_t a_row[4];      // rows of x or h
   uint32_t b_off[4];      // elements (H and F are at most 16384)
   global_ptr b_lo, b_hi;  // weight rows 0 .. 31 and 32 .. 63
   // What an item needs from memory before its first operand can be fetched.
@@ -177,17 +190,16 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
     RowTile rt;
     int ct;
     int src[4];                  // GATED, routed: entries of local_src of this lane's rows
-    const void* lo;
-    const void* hi;
+    global_ptr lo, hi;           // weight rows 0 .. 31 and 32 .. 63
   };
   auto find_item = [&](int it) {
     Item n;
     n.ct = it / n_row_tiles;
-    n.rt = row_tile(p, tiles, it - n.ct * n_row_tiles);
+    n.rt = row_tile(p, tiles, tid, it - n.ct * n_row_tiles);
     const bool routed = n.rt.g < p.E;
     const int gi = routed ? n.rt.g : n.rt.g - p.E;
-    n.lo = GATED ? (routed ? p.wg[gi] : p.swg[gi]) : (routed ? p.wd[gi] : p.swd[gi]);
-    n.hi = GATED ? (routed ? p.wu[gi] : p.swu[gi]) : n.lo;
+    n.lo = table_entry(GATED ? (routed ? p.wg : p.swg) : (routed ? p.wd : p.swd), gi);
+    n.hi = GATED ? table_entry(routed ? p.wu : p.swu, gi) : n.lo;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       n.src[i] = GATED && routed ? p.local_src[n.rt.row_start + min(lrow + 16 * i, n.rt.row_count - 1)] : 0;
@@ -199,26 +211,28 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
       const int br = lrow + 16 * i;
       const int rr = min(br, n.rt.row_count - 1);   // rows past the end repeat the last one
       if (GATED)
-        a_ptr[i] = p.x + (size_t)(n.rt.g < p.E ? n.src[i] / p.top_k : n.rt.tok_base + rr) * K;
+        a_row[i] = n.rt.g < p.E ? n.src[i] / p.top_k : n.rt.tok_base + rr;
       else
-        a_ptr[i] = p.h + (size_t)(n.rt.row_start + rr) * K;
+        a_row[i] = n.rt.row_start + rr;
       b_off[i] = (uint32_t)min(n.ct * kCols + br % kCols, N - 1) * (uint32_t)K;
     }
-    b_lo = (global_ptr)n.lo;
-    b_hi = (global_ptr)n.hi;
+    b_lo = n.lo;
+    b_hi = n.hi;
   };
 
   // this wavefront's k-tiles
   const int n_kt = (K + kBK - 1) / kBK;
   const int kt0 = (int)((long long)n_kt * wave / kWaves), kt1 = (int)((long long)n_kt * (wave + 1) / kWaves);
   f32x4 fa[4], fb[4];
+  float largest;          // !LONG: magnitude of the elements this lane brought
+  const float* const a_base = GATED ? p.x : p.h;
   // Element k = kt kBK + 4 chunk and the three after it, of every row this lane brings.  At the end
   // of the rows the last 4 elements come instead (cut_tail puts them right).
   auto fetch = [&](int kt) {
     const uint32_t k = (uint32_t)min(kt * kBK + chunk * 4, K - 4);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      fa[i] = *reinterpret_cast<const f32x4u*>(a_ptr[i] + k);
+      fa[i] = *reinterpret_cast<const f32x4u*>(a_base + ((uint64_t)a_row[i] * (uint32_t)K + k));
       fb[i] = *(global_ptr4)((i < 2 ? b_lo : b_hi) + (b_off[i] + k));
     }
   };
@@ -231,7 +245,7 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          fa[i][e] = a_ptr[i][min(e, K - 1)];
+          fa[i][e] = a_base[(uint64_t)a_row[i] * (uint32_t)K + min(e, K - 1)];
           fb[i][e] = ((i < 2 ? b_lo : b_hi) + b_off[i])[min(e, K - 1)];
         }
     }
@@ -259,12 +273,22 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
 
   // 64-byte LDS rows; chunk c of row r sits in slot c ^ ((r >> 2) & 3), so that the 16-byte reads
   // of 16 consecutive rows fall into 16 different slots of the 256-byte bank window.
-  uint8_t* const stage = reinterpret_cast<uint8_t*>(smem) + wave * kStageBytes;
+  uint8_t* const stage = reinterpret_cast<uint8_t*>(smem + wave * kRedFloats);   // (its partial tile replaces its k-tile)
   const int wr = lrow * kRowBytes + (chunk ^ ((lrow >> 2) & 3)) * 16;
   const int key = (r32 >> 2) & 3;
+  // m: the largest magnitude so far
+  auto grow = [](float& m, const f32x4& v) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|\n\tv_max3_f32 %0, %0, |%3|, |%4|" : "+&v"(m) : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+  };
   // puts the k-tile that was fetched into LDS and asks for the next one
-  auto next_k_tile = [&](int kt) {
+  auto next_k_tile = [&](int kt, bool with_max) {
     if (kt * kBK + kBK > K) cut_tail(kt);
+    if (with_max)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        grow(largest, fa[i]);
+        grow(largest, fb[i]);
+      }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       *reinterpret_cast<f32x4*>(stage + wr + i * 16 * kRowBytes) = fa[i];
@@ -298,16 +322,16 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
 
   f32x16 acc[2][2];
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  // The products as six bf16 ones, the leading part's in sums of their own.  Tiles of at most 32 rows (two: false)
-  // leave out the second half.
+  // The products as six bf16 ones, the leading part's in sums of their own.  Tiles of at most 32 rows (two: false) leave out the second half.
   auto multiply_parts = [&](bool two) {
     f32x16 low[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = low[i][j] = zero;
+    largest = 0.f;
     for (int kt = kt0; kt < kt1; ++kt) {
-      next_k_tile(kt);
+      next_k_tile(kt, true);
       const Parts b[2] = {read_parts(kBM + r32), read_parts(kBM + 32 + r32)};
       auto half = [&](int i) {
         const Parts a = read_parts(i * 32 + r32);
@@ -331,112 +355,147 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] += low[i][j];
   };
-  // The products on the fp32 matrix cores: pairs, the pairs of a k-tile as a tree.  MFMA j of chunk pair c
-  // consumes element j, i.e. the elements 8 c + j and 8 c + 4 + j of the k-tile.
+  // acc += the products of a k-tile on the fp32 matrix cores: pairs, the pairs of a k-tile as a tree.  MFMA j of chunk
+  // pair c consumes element j, i.e. the elements 8 c + j and 8 c + 4 + j of the k-tile.
+  auto add_products = [&](const f32x4 (&a)[2], const f32x4 (&b)[2], f32x16& sum) {
+    f32x16 part[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[u >> 1][2 * (u & 1)], a[u >> 1][2 * (u & 1)], zero, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[u >> 1][2 * (u & 1) + 1], a[u >> 1][2 * (u & 1) + 1], part[u], 0, 0, 0);
+    sum += (part[0] + part[1]) + (part[2] + part[3]);
+    // one accumulator at a time: its partial sums take 64 registers until they are added
+    asm volatile("" : "+v"(sum));
+  };
+  auto read_row = [&](int row, f32x4 (&v)[2]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) v[c] = read_chunk(row, c);
+  };
   auto multiply_f32 = [&](bool two) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = zero;
-    fetch_first();
     for (int kt = kt0; kt < kt1; ++kt) {
-      next_k_tile(kt);
+      next_k_tile(kt, false);
       f32x4 a[2][2], b[2][2];
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          a[s][c] = read_chunk(s * 32 + r32, c);
-          b[s][c] = read_chunk(kBM + s * 32 + r32, c);
-        }
+      for (int s = 0; s < 2; ++s) {
+        read_row(s * 32 + r32, a[s]);
+        read_row(kBM + s * 32 + r32, b[s]);
+      }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       auto half = [&](int i) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          f32x16 part[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][u >> 1][2 * (u & 1)], a[i][u >> 1][2 * (u & 1)], zero, 0, 0, 0);
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            part[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][u >> 1][2 * (u & 1) + 1], a[i][u >> 1][2 * (u & 1) + 1],
-                                                           part[u], 0, 0, 0);
-          acc[i][j] += (part[0] + part[1]) + (part[2] + part[3]);
-          // one accumulator at a time: its partial sums take 64 registers until they are added
-          asm volatile("" : "+v"(acc[i][j]));
-        }
+        for (int j = 0; j < 2; ++j) add_products(a[i], b[j], acc[i][j]);
       };
       half(0);
       if (two) half(1);
     }
   };
-  auto all_finite = [&] {
-    float z = 0.f;
+  // Small values: the three parts of an element miss at most 2^-134 (the smallest bf16 value is 2^-133), nothing of one from
+  // 2^-110 on.  A wavefront's sum of at most 2^9 products of a row whose largest element is A with a weight row whose largest is B
+  // is off by at most 2^-125 (A + B) for that, and by 2^-142 for products below the smallest fp32 value.  A sum of more
+  // than 2^26 times as much keeps what fp32 products would; the others, and those that are not finite, are taken from fp32
+  // products.  Each sum is judged by its own value and operands, so that a result depends on nothing else in the tile.
+  auto redo_sums = [&](bool two) {
+    float a_max[4] = {0.f, 0.f, 0.f, 0.f}, b_max[4] = {0.f, 0.f, 0.f, 0.f};   // rows lrow + 16 i
+    fetch_first();
+    for (int kt = kt0; kt < kt1; ++kt) {
+      if (kt * kBK + kBK > K) cut_tail(kt);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        grow(a_max[i], fa[i]);
+        grow(b_max[i], fb[i]);
+      }
+      if (kt + 1 < kt1) fetch(kt + 1);
+    }
+    float ra[2], rb[2];   // rows s 32 + r32
+    auto of_rows = [&](float (&m)[4], float (&o)[2]) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {   // a row is brought by four lanes
+        m[i] = fmaxf(m[i], __shfl_xor(m[i], 1));
+        m[i] = fmaxf(m[i], __shfl_xor(m[i], 2));
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const float lo = __shfl(m[2 * s], (r32 & 15) * 4), hi = __shfl(m[2 * s + 1], (r32 & 15) * 4);
+        o[s] = r32 < 16 ? lo : hi;
+      }
+    };
+    of_rows(a_max, ra);
+    of_rows(b_max, rb);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j) {
+        uint32_t bad = 0;
+        if (i == 0 || two)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) z = fmaf(acc[i][j][v], 0.f, z);
-    return __ballot(z != 0.f) == 0;   // (a NaN is not equal to zero)
+          for (int v = 0; v < 16; ++v) {
+            const float x = fabsf(acc[i][j][v]), c = __shfl(rb[j], 8 * (v / 4) + 4 * q + v % 4);
+            // (a zero row gives zeros either way)
+            const bool lost = x <= kLossPerOperand * (ra[i] + c) + kLossFloor && ra[i] > 0.f && c > 0.f;
+            bad |= (uint32_t)(lost || !(x < INFINITY)) << v;
+          }
+        if (__ballot(bad != 0) == 0) continue;
+        f32x16 sum = zero;
+        fetch_first();
+        for (int kt = kt0; kt < kt1; ++kt) {
+          next_k_tile(kt, false);
+          f32x4 a[2], b[2];
+          read_row(i * 32 + r32, a);
+          read_row(kBM + j * 32 + r32, b);
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          add_products(a, b, sum);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = (bad >> v) & 1 ? sum[v] : acc[i][j][v];
+      }
+  };
+  // Whether no sum of this wavefront can need that: one comparison for all (a NaN stays one either way).
+  auto all_plain = [&](bool two) {
+    float small = INFINITY;
+    auto shrink = [&](const f32x16& s) {
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(small) : "v"(s[v]), "v"(s[v + 1]));
+    };
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      shrink(acc[0][j]);
+      if (two) shrink(acc[1][j]);
+    }
+    return __ballot(!(largest <= kPlainMax && small >= kPlainMin)) == 0;
   };
 
+  // ---- the eighths: through LDS, where they take the k-tiles' place, and added by all threads ----
   // Register v of lane (r32, q): row r32 of the row half, column 8 (v / 4) + 4 q + v % 4.
-  float* const red = smem + kWaves * kStageBytes / 4;
-  float* const slot = red + (wave & 3) * kRedFloats + r32 * kRedPitch + q * 4;
-  auto each_quad = [&](auto&& fn) {
+  auto add_and_store = [&](const RowTile& rt, int ct) {
+    // !LONG: what depends on the lane is worked out anew, in registers across the products it would push others out
+    int t = tid;
+    if (!LONG) asm volatile("" : "+v"(t));
+    float* const slot = smem + wave * kRedFloats + (t & 31) * kRedPitch + ((t >> 5) & 1) * 4;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int vg = 0; vg < 4; ++vg)
-          fn(reinterpret_cast<f32x4*>(slot + i * 32 * kRedPitch + j * 32 + vg * 8), acc[i][j], vg);
-  };
-  auto put = [](f32x4* d, f32x16& s, int vg) { *d = f32x4{s[vg * 4], s[vg * 4 + 1], s[vg * 4 + 2], s[vg * 4 + 3]}; };
-
-  Item cur = find_item(item);
-  set_addresses(cur);
-  fetch_first();
-  while (true) {
-    const bool has_next = item + slots < item_end;
-    item += slots;
-    const Item next = find_item(has_next ? item : item - slots);   // asked for before the products
-    const RowTile rt = cur.rt;
-    const int ct = cur.ct;
-    const bool two = rt.row_count > 32;
-    bool in_f32 = K > kSplitMaxK;
-    if (!in_f32) {
-      multiply_parts(two);
-      // an infinity or NaN is no sum of three parts, nor is a value that rounds up to infinity: once more in fp32
-      in_f32 = !all_finite();
-    }
-    if (in_f32) multiply_f32(two);
-    if (has_next) {   // the next item's first k-tile travels during the sums of this one
-      set_addresses(next);
-      fetch_first();
-    }
-
-    // ---- the eighths as a tree: 4..7 into 0..3 through LDS, then the four tiles by all threads ----
-    lds_barrier();   // the item before has been read
-    if (wave >= 4) each_quad(put);
+          *reinterpret_cast<f32x4*>(slot + i * 32 * kRedPitch + j * 32 + vg * 8) =
+              f32x4{acc[i][j][vg * 4], acc[i][j][vg * 4 + 1], acc[i][j][vg * 4 + 2], acc[i][j][vg * 4 + 3]};
     lds_barrier();
-    if (wave < 4)
-      each_quad([](f32x4* d, f32x16& s, int vg) {
-        const f32x4 o = *d;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[vg * 4 + e] += o[e];
-        *d = f32x4{s[vg * 4], s[vg * 4 + 1], s[vg * 4 + 2], s[vg * 4 + 3]};
-      });
-    lds_barrier();
-
-    const int row = threadIdx.x >> 3, c4 = (threadIdx.x & 7) * 4;
+    const int row = t >> 3, c4 = (t & 7) * 4;
     if (row < rt.row_count) {
       auto total = [&](int col) {
-        f32x4 t[4];
+        f32x4 s[kWaves], o;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) t[w] = *reinterpret_cast<const f32x4*>(red + w * kRedFloats + row * kRedPitch + col);
-        return (t[0] + t[2]) + (t[1] + t[3]);
+        for (int w = 0; w < kWaves; ++w) s[w] = *reinterpret_cast<const f32x4*>(smem + w * kRedFloats + row * kRedPitch + col);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          o[e] = ((s[0][e] + s[4][e]) + (s[2][e] + s[6][e])) + ((s[1][e] + s[5][e]) + (s[3][e] + s[7][e]));
+        return o;
       };
       float* const out = (GATED ? p.h : p.y) + (size_t)(rt.row_start + row) * N;
       auto store = [&](int n, const f32x4& v) {
@@ -459,13 +518,72 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
         store(ct * kCols + c4 + kBN / 2, total(c4 + kBN / 2));
       }
     }
+    lds_barrier();   // before the next k-tiles
+  };
+
+  int number = 0;   // of the item in this workgroup
+  if (AGAIN) {
+    for (; item < item_end; item += slots, ++number) {
+      if (!((marks[number / 32 % kMarkWords] >> number % 32) & 1)) continue;
+      const Item it = find_item(item);
+      set_addresses(it);
+      fetch_first();
+      const bool two = it.rt.row_count > 32;
+      multiply_parts(two);
+      if (kt0 < kt1) redo_sums(two);
+      add_and_store(it.rt, it.ct);
+    }
+    return;
+  }
+  Item cur = find_item(item);
+  set_addresses(cur);
+  fetch_first();
+  while (true) {
+    const bool has_next = item + slots < item_end;
+    item += slots;
+    const Item next = find_item(has_next ? item : item - slots);   // asked for before the products
+    const RowTile rt = cur.rt;
+    const int ct = cur.ct;
+    const bool two = rt.row_count > 32;
+    if (LONG) {
+      multiply_f32(two);
+    } else {
+      multiply_parts(two);
+      if (kt0 < kt1 && !all_plain(two)) {
+        atomicOr(&marks[number / 32 % kMarkWords], 1u << number % 32);
+        marks[kMarkWords] = 1;
+      }
+    }
+    if (has_next) {   // the next item's first k-tile travels during the sums of this one
+      set_addresses(next);
+      fetch_first();
+    }
+    add_and_store(rt, ct);
     if (!has_next) break;
     cur = next;
+    ++number;
+  }
+}
+#endif
+
+template <bool GATED, bool LONG>
+__global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __align__(16) float smem[];
+  int* const marks = reinterpret_cast<int*>(smem) + kTileBytes / 4;
+  for (int i = threadIdx.x; i <= kMarkWords + 1 + PRISM_MAX_EXPERTS; i += kThreads)   // marks, offsets
+    marks[i] = i <= kMarkWords ? 0 : p.local_offsets[min(i - kMarkWords - 1, p.E)];
+  __syncthreads();
+  walk_items<GATED, LONG, false>(p, smem, threadIdx.x);
+  if (!LONG && marks[kMarkWords] != 0) {   // (written before the last barrier)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    walk_items<GATED, LONG, true>(p, smem, tid);
   }
 #endif
 }
 
-template <bool GATED>
+template <bool GATED, bool LONG>
 prism_status launch_f32_gemm(const F32Args& a, hipStream_t st) {
   const int A = a.T * a.top_k;
   // items there can be, in tiles of 2^shift rows: a full row tile per 2^shift assignments, and one that is not per
@@ -477,9 +595,9 @@ prism_status launch_f32_gemm(const F32Args& a, hipStream_t st) {
   // (2^31 items of 64 rows, each for up to 64 x 32 elements of h, are beyond any memory)
   if (items(6) >= 0x7FFF0000LL) return PRISM_ERR_UNSUPPORTED;
   static LdsLimitOnce lds_limit;   // one per instantiation
-  if (!raise_lds_limit(lds_limit, (const void*)ffn_f32_kernel<GATED>, kLdsBytes)) return PRISM_ERR_LAUNCH;
+  if (!raise_lds_limit(lds_limit, (const void*)ffn_f32_kernel<GATED, LONG>, kLdsBytes)) return PRISM_ERR_LAUNCH;
   // one workgroup fits a CU
-  hipLaunchKernelGGL(ffn_f32_kernel<GATED>, dim3((unsigned)std::min<long long>(kWorkgroups, align_up((size_t)items(5), kXcds))),
+  hipLaunchKernelGGL((ffn_f32_kernel<GATED, LONG>), dim3((unsigned)std::min<long long>(kWorkgroups, align_up((size_t)items(5), kXcds))),
                      dim3(kThreads), kLdsBytes, st, a);
   PRISM_CHECK_LAUNCH();
   return PRISM_OK;
@@ -496,10 +614,10 @@ prism_status launch_expert_ffn_f32(const prism_layer_desc& d, const void* x, con
                   w.shared_w_down, local_src, local_offsets, (float*)h, (float*)y,
                   T, d.hidden, d.ffn, d.n_experts, d.n_shared, d.top_k};
   trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
-  PRISM_TRY(launch_f32_gemm<true>(a, st));
+  PRISM_TRY((d.hidden > kSplitMaxK ? launch_f32_gemm<true, true> : launch_f32_gemm<true, false>)(a, st));
   trace(stage_events, PRISM_STAGE_FFN_UP, 1, st);
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 0, st);
-  PRISM_TRY(launch_f32_gemm<false>(a, st));
+  PRISM_TRY((d.ffn > kSplitMaxK ? launch_f32_gemm<false, true> : launch_f32_gemm<false, false>)(a, st));
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 1, st);
   return PRISM_OK;
 }

@@ -117,3 +117,72 @@ def test_f32_ffn_of_more_tiles_than_one_grid_dimension_holds():
         got = y[e * T:(e + 1) * T][picks].double()
         # 4 + 2 + F / 128 + 3 roundings of 2^-24, independent: sqrt(137) * 6e-8 = 7e-7 of a sum's norm; three sums
         assert float((got - ref).norm() / ref.norm()) <= 2e-6
+
+
+def run_one_expert(x, wg, wu, wd):
+    """prism_expert_ffn of one expert that takes every row of x once; numpy in, numpy out."""
+    import paper_2508_12851_amd as P
+    T, (F, H) = len(x), wg.shape
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    desc = P.make_desc(H, F, 1, 1, 0, "f32")
+    y = P.prism_expert_ffn(desc, dev(x), P.WeightTable([(dev(wg), dev(wu), dev(wd))]),
+                           torch.arange(T, dtype=torch.int32, device="cuda"),
+                           torch.tensor([0, T], dtype=torch.int32, device="cuda"), P.alloc_workspace(desc, T))
+    return y.cpu().numpy()
+
+
+def normal_operands(T, H, F, seed=0):
+    rng = np.random.default_rng([T, H, F, seed])
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    return [x] + [(rng.standard_normal(s) / np.sqrt(s[1])).astype(np.float32) for s in ((F, H), (F, H), (H, F))]
+
+
+@pytest.mark.parametrize("T,H,F", [(33, 8, 8), (70, 264, 130), (40, 2048, 40), (300, 40, 2048)])
+@pytest.mark.parametrize("ex,eg,eu,ed", [
+    (118, -118, -118, 0),                        # weights of which bf16 parts keep about 13 bits, ordinary sums
+    (-118, 118, 118, 0),                         # the same of the tokens
+    (122, -125, -125, 0),                        # weights next to the smallest normal fp32 value, and below
+    (0, 0, 0, -118),                             # small weights of the down projection: all results are small
+    (-40, 40, -50, 100),                         # small sums of one matrix, large weights after them
+])
+def test_f32_ffn_small_operands(T, H, F, ex, eg, eu, ed):
+    """Operands whose bf16 parts fall below the smallest bf16 value: as good as any others (bound: test_f32_ffn_edges;
+    scaled by powers of two, so that the operands are the same ones but for what falls below the smallest fp32 value,
+    which the reference sees too)."""
+    ops = [np.ldexp(m, e).astype(np.float32) for m, e in zip(normal_operands(T, H, F), (ex, eg, eu, ed))]
+    y = run_one_expert(*ops)
+    x, g, u, d = (m.astype(np.float64) for m in ops)
+    z = x @ g.T
+    ref = (z / (1.0 + np.exp(-z)) * (x @ u.T)) @ d.T
+    assert np.linalg.norm(y - ref) <= 1e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("T,H,F", [(33, 64, 40), (70, 264, 130), (300, 1024, 72)])
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4e38, 1e-36, 0.0])
+def test_f32_ffn_rows_do_not_depend_on_their_neighbours(T, H, F, value):
+    """A token or an output column of which the products of parts are not enough must not change a bit of the others."""
+    x, wg, wu, wd = normal_operands(T, H, F)
+    plain = run_one_expert(x, wg, wu, wd)
+    odd = x.copy()
+    odd[5, :] = value                            # one whole row ...
+    odd[T - 1, H // 2] = value                   # ... one element of another
+    rest = np.setdiff1d(np.arange(T), [5, T - 1])
+    with np.errstate(all="ignore"):
+        np.testing.assert_array_equal(run_one_expert(odd, wg, wu, wd)[rest], plain[rest])
+        odd = wd.copy()
+        odd[3, :] = value
+        odd[H - 1, F // 2] = value
+        rest = np.setdiff1d(np.arange(H), [3, H - 1])
+        np.testing.assert_array_equal(run_one_expert(x, wg, wu, odd)[:, rest], plain[:, rest])
+
+
+def test_f32_ffn_marks_more_than_1024_items_of_a_workgroup():
+    """Small rows in the first and last tiles of 271392 items, 1060 per workgroup: only their rows are redone."""
+    T, H, F = 66 * 1024, 8, 8200                 # 1056 row tiles of 64 rows x 257 column tiles of h
+    x, wg, wu, wd = normal_operands(T, H, F)
+    plain = run_one_expert(x, wg, wu, wd)
+    odd = x.copy()
+    odd[[0, T - 1]] = np.float32(1e-36)
+    odd[7] = np.inf
+    rest = np.setdiff1d(np.arange(T), [0, 7, T - 1])
+    np.testing.assert_array_equal(run_one_expert(odd, wg, wu, wd)[rest], plain[rest])
