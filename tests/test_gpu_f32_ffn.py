@@ -186,3 +186,19 @@ def test_f32_ffn_marks_more_than_1024_items_of_a_workgroup():
     odd[7] = np.inf
     rest = np.setdiff1d(np.arange(T), [0, 7, T - 1])
     np.testing.assert_array_equal(run_one_expert(odd, wg, wu, wd)[rest], plain[rest])
+
+
+def test_f32_ffn_single_products():
+    """Contractions of one term: a million products of full fp32 values, each rounded once.  Tokens and the gate are
+    powers of two (silu(32) = 32 in fp32), so h = 32 W_up exactly, and a row of W_down has one element."""
+    T = H = F = 1024
+    rng = np.random.default_rng(11)
+    x = np.eye(T, H, dtype=np.float32)
+    wu = rng.standard_normal((F, H)).astype(np.float32)
+    pick, wd = rng.integers(0, F, H), np.zeros((H, F), np.float32)
+    wd[np.arange(H), pick] = rng.standard_normal(H)
+    y = run_one_expert(x, np.full((F, H), 32, np.float32), wu, wd).astype(np.float64)
+    ref = 32.0 * wu[pick, :].T.astype(np.float64) * wd[np.arange(H), pick].astype(np.float64)[None, :]
+    # one rounding to fp32, 2^-24; the seven smaller products of parts (at most 2^-8 of the product each, two
+    # roundings of 2^-24 apiece) add less than 14 * 2^-32, the ninth, left out, 2^-34
+    assert np.all(np.abs(y - ref) <= 2.0 ** -24 * (1 + 2.0 ** -4) * np.abs(ref))
