@@ -33,7 +33,7 @@
 //
 // FFN of fp32 products as one launch of a workgroup per item -> here, us: 500 tokens, 1024 x 2048, 5 of 8 experts hosted 157 -> 121
 // (six products, and leading sums kept in the matrix cores: 102); 256 x 512, 64 tokens 18.2 -> 18.3; LONG, 2056 x 2056, 200
-// tokens 154 -> 151, 4096 x 4096, 4 / 500 tokens 169 / 784 -> 173 / 715.
+// tokens 154 -> 137, 4096 x 4096, 4 / 500 tokens 169 / 784 -> 173 / 715.
 #include "prism_internal.h"
 
 namespace prism {
@@ -49,7 +49,9 @@ struct F32Args {
 };
 
 constexpr int kBM = 64;                  // most rows of a tile
-constexpr float kHalfTile = 0.85f;       // time of a tile of 32 rows, in tiles of 64
+// Time of a tile of 32 rows, in tiles of 64.  In parts, whose conversions of weights stay: 0.6 / 0.85 FFN of 500 tokens, 1024 x
+// 2048, 127 / 118 us.  In fp32, where half the MFMAs go: 2056 x 2056, 200 tokens 137 / 151, 500 tokens 232 / 243.
+constexpr float kHalfTile = 0.85f, kHalfTileF32 = 0.6f;
 constexpr int kBN = 64;                  // weight rows of a tile
 constexpr int kBK = 16;                  // contraction elements per k-tile
 constexpr int kWaves = 8;
@@ -181,7 +183,7 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
   // items, row tiles running fastest, so that the row tiles of an expert read its weight rows
   // through one L2.
   const int n_col_tiles = (N + kCols - 1) / kCols;
-  const RowTiles tiles = load_row_tiles(p, n_col_tiles, kHalfTile, tid, reinterpret_cast<int*>(marks) + kMarkWords + 1);
+  const RowTiles tiles = load_row_tiles(p, n_col_tiles, LONG ? kHalfTileF32 : kHalfTile, tid, reinterpret_cast<int*>(marks) + kMarkWords + 1);
   const int n_row_tiles = tiles.routed + p.S * tiles_of(p.T, tiles.shift);
   const int n_items = n_row_tiles * n_col_tiles;
   const int xcd = blockIdx.x % kXcds, slots = gridDim.x / kXcds;

@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (300, 264, 130, [129, 128, 43], 0),
     (1000, 64, 2048, [500, 300, 97, 65, 33], 0),   # gate/up in tiles of 64 rows, down in tiles of 32
     (200, 40, 4096, [100, 64, 33], 3),          # the same with shared rows
+    (1100, 2056, 320, [600, 65, 33, 400], 0),   # fp32 products: gate/up in tiles of 64 rows (200 items), ...
+    (1100, 2056, 512, [600, 65, 33, 400], 0),   # ... and of 32 (320 items of 64 rows are two rounds, 592 of 32 three)
 ])
 def test_f32_ffn_edges(T, H, F, rows, S):
     import paper_2508_12851_amd as P
