@@ -233,7 +233,8 @@ prism_status prism_pack_remote(const prism_layer_desc* desc, const void* x, cons
 /*
  * Zeros in the rows that prism_expert_ffn (y, offsets = local_offsets) or prism_pack_remote (packed, offsets =
  * remote_offsets) leave untouched, for callers that want defined values there:
- *   rows[r] = 0  for offsets[E] <= r < n_rows;  rows [n_rows, H] layer dtype, 16-byte aligned (n_rows: T*k).
+ *   rows[r] = 0  for r < offsets[0] and for offsets[E] <= r < n_rows;  rows [n_rows, H] layer dtype, 16-byte aligned
+ *   (n_rows: T*k; offsets[0] is 0 in the lists of prism_dispatch, and may be more in a caller's own).
  */
 prism_status prism_clear_rows(const prism_layer_desc* desc, const int32_t* offsets, int32_t n_rows, void* rows,
                               void* stream);

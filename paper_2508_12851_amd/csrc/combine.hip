@@ -119,12 +119,15 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const TIO* __restrict__ 
       *reinterpret_cast<const raw_t*>(x + (size_t)t * H + col);
 }
 
-// Zeros in the rows past the ones an assignment list fills (16-byte pieces, row_vecs per row).
+// Zeros in the rows that no segment of an assignment list covers: before offsets[0] and from offsets[E] on (16-byte
+// pieces, row_vecs per row).
 __global__ __launch_bounds__(256) void clear_rows_kernel(const int32_t* __restrict__ offsets, int E, int n_rows,
                                                          int row_vecs, uint4* __restrict__ rows) {
-  const long long end = (long long)n_rows * row_vecs, step = (long long)gridDim.x * blockDim.x;
-  for (long long i = (long long)offsets[E] * row_vecs + (long long)blockIdx.x * blockDim.x + threadIdx.x; i < end; i += step)
-    rows[i] = uint4{0, 0, 0, 0};
+  const int first = min(max(offsets[0], 0), n_rows), last = min(max(offsets[E], first), n_rows);
+  const long long head = (long long)first * row_vecs, covered = (long long)(last - first) * row_vecs;
+  const long long end = (long long)n_rows * row_vecs - covered, step = (long long)gridDim.x * blockDim.x;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < end; i += step)
+    rows[i < head ? i : i + covered] = uint4{0, 0, 0, 0};
 }
 
 // One 16-byte chunk (8 bf16) per thread from the row-major matrix to its place in the

@@ -275,7 +275,7 @@ prism_status launch_combine(const prism_layer_desc& d, const void* y, const int3
                             const float* part = nullptr, const int32_t* n_splits = nullptr,
                             bool add_to_out = false, const int32_t* src = nullptr, const int32_t* offsets = nullptr);
 
-// rows[r] = 0 for offsets[E] <= r < n_rows.
+// rows[r] = 0 for r < offsets[0] and offsets[E] <= r < n_rows.
 prism_status launch_clear_rows(const prism_layer_desc& d, const int32_t* offsets, int n_rows, void* rows, hipStream_t st);
 
 // Row-major bf16 [rows, cols] -> 16 x 32 tiles (rows a multiple of 16, cols of 32).

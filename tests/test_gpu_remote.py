@@ -135,3 +135,37 @@ def test_clear_rows(dtype, H, n_rows, first):
     ref = torch.ones_like(rows)
     ref[first:n_rows] = 0
     assert torch.equal(rows, ref)
+
+
+@pytest.mark.parametrize("dtype,T", [("f32", 70), ("bf16", 700)])
+def test_expert_ffn_of_a_list_that_starts_later(dtype, T):
+    """A caller's own list whose first segment starts at row 9: the rows before it are zeros, as those after the last."""
+    H, F, E = 128, 192, 3
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    draw = lambda *s: (torch.randn(s, generator=gen, device="cuda") * s[1] ** -0.5).to(td)
+    x, w = draw(T, H) * H ** 0.5, [(draw(F, H), draw(F, H), draw(H, F)) for _ in range(E)]
+    off = [9, 9 + T // 3, 9 + T // 3, T - 7]
+    src = torch.randperm(T, generator=gen, device="cuda").to(torch.int32)
+    desc = P.make_desc(H, F, E, 1, 0, dtype)
+    ws = P.alloc_workspace(desc, T)
+    torch.full((T, H), 7.0, dtype=td, device="cuda")      # freed at once: what the allocator hands out next
+    y = P.prism_expert_ffn(desc, x, P.WeightTable(w), src, torch.tensor(off, dtype=torch.int32, device="cuda"), ws)
+    assert not y[:9].any() and not y[T - 7:].any()
+    for e in range(E):
+        xr = x[src[off[e]:off[e + 1]].long()].float()
+        g, u, d = (m.float() for m in w[e])
+        h = (torch.nn.functional.silu(xr @ g.t()) * (xr @ u.t())).to(td).float()
+        if len(xr):
+            assert rel_err(to_f32(y[off[e]:off[e + 1]]), (h @ d.t()).cpu().numpy()) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("first,last", [(0, 0), (3, 3), (2, 5), (0, 11), (11, 11)])
+def test_clear_rows_before_and_after_the_list(first, last):
+    desc = P.make_desc(24, 64, 2, 1, 0, "f32")
+    rows = torch.ones((12, 24), device="cuda")
+    P.binding._clear_rows(desc, torch.tensor([first, first, last], dtype=torch.int32, device="cuda"), 11, rows, None)
+    ref = torch.ones_like(rows)
+    ref[:first] = 0
+    ref[last:11] = 0
+    assert torch.equal(rows, ref)
