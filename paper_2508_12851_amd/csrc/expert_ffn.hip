@@ -37,7 +37,7 @@ constexpr float kSplitRoundBytes = 14 * 8192.f;
 
 // Wide tiles of a path with two widths (schedule.h, "Two widths"): ring of their own, fewest items.
 constexpr int kWideStages = 3;
-constexpr int kWideItemsUp = 150, kWideItemsDown = 40;
+constexpr int kWideItemsUp = 150, kWideItemsDown = 48;
 
 // What the schedule builders need to know about a path's two GEMMs (C1: gate/up, C2: down).
 template <typename C1, typename C2, bool SPLIT_DOWN, bool ROTATE, bool WIDTHS>

@@ -17,6 +17,7 @@ constexpr int kItemInts = 8;         // ints per work item
 constexpr int kMaxSlices = 16;       // contraction slices of one sliced item, at most
 constexpr int kMinSliceKt = 8;       // k-tiles of one slice, at least
 constexpr int kSliceSlots = 32;      // workgroups per XCD that sliced lists are cut for
+constexpr int kCus = 256;            // workgroups in one round of items that do not share a CU
 constexpr int kReduceInts = 8;       // ints per entry of the list of sliced items
 
 // Schedule memory (int32):
@@ -66,11 +67,15 @@ constexpr int kReduceInts = 8;       // ints per entry of the list of sliced ite
 // faster.  A group with more row tiles reads its weights once per row tile: next to each other in
 // an XCD's list the later ones find the weight tile in the L2, and twice the width halves how often activations
 // are read -- if the wide tiles still make items for most of the machine (wide_items).
-// 504 batches of 66 to 256 tokens of six layers, 1024 x 7168 to 4096 x 14336, 1 to all experts hosted, even and
-// skewed picks, time in wide tiles over time in narrow ones.  Gate/up, some group with more than one row tile: fewer than
-// 150 wide items 1.02-1.36, 150 to 300 0.82 on average, beyond 0.90, at most 1.07; down projection (split): fewer than
-// 40 wide items 1.03, from there 0.86.  All groups with one row tile: 1.09 and 1.04.  (4096 x 14336, 200 tokens, 6
-// experts hosted: gate/up 290 -> 274 us, down and combine 183 -> 141, layer 512 -> 455; 4 hosted, 256 tokens 457 -> 372.)
+// Without a split the rounds of items count as well (a workgroup per CU): the wide tiles are taken if twice their
+// rounds, times the share of row tiles that are the first of their group, are fewer than the narrow ones' rounds.
+// 900 batches of 66 to 256 tokens of seven shapes, 1024 x 7168 to 4096 x 14336, 0 to 4 shared experts (a group of two row
+// tiles each from 129 tokens on), 1 to all experts hosted, even and skewed picks, every pass with other weights (1.5 GB until
+// they return), wide over narrow where some group has more than one row tile (420 of them).  Gate/up: fewer than 150 wide
+// items 1.08-1.46; from there 0.90 on average, up to 1.10 where the rounds say no, 1.04 where they say yes.  Down
+// projection and combine: fewer than 32 wide items 1.15-1.41, to 40 1.07, to 48 0.98 and up to 1.08, beyond 0.89, at most 1.04.  Layer
+// by this rule: 0.93 on average, 0.86 for 4096 x 14336, at most 1.035 (2 of 420 above 1.02).  All groups with one row tile: gate/up
+// 1.09, down 1.04.  (4096 x 14336, 200 tokens, 6 experts hosted: gate/up 295 -> 279 us, down and combine 183 -> 140.)
 //
 // Work order.  A group's row tiles are split into equal parts of at most kRectRows.  All
 // items -- groups in order, then row parts, then the column tiles of a row part, the row tiles
@@ -210,11 +215,13 @@ __device__ __forceinline__ void build_schedules_block(const int32_t* local_offse
     }
     bool wide = false;
     int n_ntiles = ps.n_ntiles;
-    if constexpr (WIDTHS)
-      if (run > taken && run * ps.wide_ntiles >= ps.wide_items) {
-        wide = true;
-        n_ntiles = ps.wide_ntiles;
-      }
+    if constexpr (WIDTHS) {
+      const int items = run * ps.wide_ntiles;
+      auto rounds = [](int n) { return (n + kCus - 1) / kCus; };
+      wide = run > taken && items >= ps.wide_items &&
+             (ps.split_kt > 0 || 2 * rounds(items) * taken < rounds(run * ps.n_ntiles) * run);
+      if (wide) n_ntiles = ps.wide_ntiles;
+    }
     const int rows_total = s_row0[E - 1] + s_rows[E - 1] + S * T;   // all rows of all groups
     if (lane == 0) {
       s_start[s][G] = run;

@@ -137,16 +137,37 @@ def test_layer_parity_on_a_random_streaming_shape(i):
 
 
 
+def width_of_schedule(ws, row_tiles, narrow, wide):
+    """1 or 0: the wide or narrow tiles of a schedule of `row_tiles` x `narrow` / `wide` column tiles that a call left in
+    its workspace (int 0 row tiles, int 3 the choice, ints 4 to 11 the items of the eight lists)."""
+    import torch
+    i = ws.view(torch.int32)
+    i = i[:i.numel() - 64]
+    found = set()
+    for at in torch.nonzero(i == row_tiles).flatten().tolist():
+        head = ws.view(torch.int32)[at:at + 12].tolist()
+        for w, cols in ((0, narrow), (1, wide)):
+            if head[3] == w and sum(head[4:]) == row_tiles * cols and max(head[4:]) - min(head[4:]) <= 1 and head[1] >= max(head[4:]):
+                found.add(w)
+    assert len(found) == 1, found
+    return found.pop()
+
+
 @pytest.mark.parametrize("tiled", [False, True])
-@pytest.mark.parametrize("T,k,H,F,rows", [
-    (128, 1, 256, 9600, (128, 0)),               # one row tile per expert: narrow tiles in both
-    (129, 1, 256, 9600, (129, 0)),               # 150 wide items of gate/up: wide
-    (129, 1, 256, 9536, (0, 129)),               # 149 of them (one column tile half full): narrow
-    (130, 2, 2560, 1024, (130, 129)),            # 40 wide items of the down projection: wide
-    (130, 2, 2368, 1088, (130, 129, 1)),         # 50, the last column tile a quarter full, a third expert with one row
-    (130, 2, 2304, 1024, (130, 129)),            # 36: narrow
-    (256, 3, 2624, 9664, (256, 129, 100, 0, 1))])  # both wide, ragged in every size
-def test_expert_ffn_at_the_lines_between_tile_widths(T, k, H, F, rows, tiled):
+@pytest.mark.parametrize("T,k,H,F,rows,up,down", [
+    (128, 1, 256, 9600, (128, 0), 0, 0),               # one row tile per expert: narrow tiles in both
+    (129, 1, 256, 9600, (129, 0), 1, 0),               # 150 wide items of gate/up: wide
+    (129, 1, 256, 9536, (0, 129), 1, 0),               # the same, the last column tile half full
+    (129, 1, 256, 9472, (0, 129), 0, 0),               # 148 of them: narrow
+    (150, 1, 256, 3584, (129, 3, 3, 3, 3, 3, 3, 3), 1, 0),   # 252: one round of items, two of the narrow ones, 8 of 9 row tiles first
+    (150, 1, 256, 4096, (129, 3, 3, 3, 3, 3, 3, 3), 0, 0),   # 288: two, three
+    (130, 2, 3072, 1024, (130, 129), 0, 1),            # 48 wide items of the down projection: wide
+    (130, 2, 2816, 1024, (130, 129), 0, 0),            # 44: narrow
+    (130, 2, 2560, 1024, (130, 129), 0, 0),            # 40
+    (130, 2, 2368, 1088, (130, 129, 1), 0, 1),         # 50, the last column tile a quarter full, a third expert with one row
+    (130, 2, 2304, 1024, (130, 129), 0, 0),            # 36: narrow
+    (256, 3, 2624, 9664, (256, 129, 100, 0, 1), 1, 1)])   # both wide, ragged in every size
+def test_expert_ffn_at_the_lines_between_tile_widths(T, k, H, F, rows, up, down, tiled):
     """Batches of 65 to 256 tokens of wide layers: the device chooses between two widths of the tiles, for each of the
     two GEMMs, by the row tiles and the items it counts.  Against plain fp32 products, with the bar of the other
     tests; rows past the list must stay as they were."""
@@ -165,8 +186,12 @@ def test_expert_ffn_at_the_lines_between_tile_widths(T, k, H, F, rows, tiled):
     desc = P.make_desc(H, F, E, k, 0, "bf16", weight_layout="tiled" if tiled else "row_major")
     wt = P.WeightTable([tuple(P.prism_pack_weights(w) if tiled else w for w in ws) for ws in experts])
     y = torch.full((T * k, H), 7.0, dtype=torch.bfloat16, device="cuda")
-    P.prism_expert_ffn(desc, x, wt, src, off, P.alloc_workspace(desc, T), y=y)
+    ws = P.alloc_workspace(desc, T).zero_()
+    P.prism_expert_ffn(desc, x, wt, src, off, ws, y=y)
     torch.cuda.synchronize()
+    row_tiles = sum(-(-m // 128) for m in rows)
+    assert width_of_schedule(ws, row_tiles, -(-F // 64), -(-F // 128)) == up
+    assert width_of_schedule(ws, row_tiles, -(-H // 128), -(-H // 256)) == down
     ref, r0 = [], 0
     for (wg, wu, wd), m in zip(experts, rows):
         xr = x[(src[r0:r0 + m] // k).long()].float()
