@@ -210,10 +210,11 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_kernel(
 
   for (int e = threadIdx.x; e < EP; e += blockDim.x) s_counts[e] = 0;   // (read after the barriers below)
 
-  // wavefronts 0..3 finish tokens 4 wave + q; their bias entries are fetched now
-  const int t_fin = tok0 + 4 * (wave & 3) + q;
+  // wavefronts 0..3 finish tokens 4 wave + q; their bias entries are fetched now, but not where the sums of up to 256
+  // experts and the operands take all registers
+  constexpr bool kBiasNow = !PARTIAL && NT <= 8;
   float bias_fin[NT];
-  if (!PARTIAL) load_bias_group<NT>(bias, t_fin, T, E, bias_group_tokens, bias_fin);
+  if (kBiasNow) load_bias_group<NT>(bias, tok0 + 4 * (wave & 3) + q, T, E, bias_group_tokens, bias_fin);
 
   // ---- router GEMM on the fp64 matrix cores --------------------------------
   f64x4 acc[NT];
@@ -223,8 +224,10 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_kernel(
   const int t_load = min(tok0 + r, T - 1);
   const TIn* xrow = x + (size_t)t_load * H;
   const TIn* wrow[NT];
+  int r_load = r;
+  if (!kBiasNow && sizeof(TIn) == 2) asm volatile("" : "+v"(r_load));   // (nor the expert numbers, which the end needs again)
 #pragma unroll
-  for (int n = 0; n < NT; ++n) wrow[n] = w_router + (size_t)min(n * 16 + r, E - 1) * H;
+  for (int n = 0; n < NT; ++n) wrow[n] = w_router + (size_t)min(n * 16 + r_load, E - 1) * H;
 
   // Wavefront w takes the 32-element slices w, w + 8, w + 16, ... of the hidden dimension,
   // U slices per trip so that their loads are all in flight before the first MFMA waits.
@@ -264,33 +267,37 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_kernel(
   // expert 16 n + r).  The routing of a token is a long dependent chain; one wavefront for all 16
   // tokens took four of them one after the other (64 tokens x 8 experts of 256 elements, fp32: layer 39.8 ->
   // 36.9 us).
-  double* const slot = s_part + (size_t)(wave >> 1) * (NT * 4 * 64) + lane;
-  if (wave & 1) {
+  int tid = threadIdx.x;
+  if (!kBiasNow) asm volatile("" : "+v"(tid));   // (what depends on it is not kept across the loop)
+  const int wave_fin = tid >> 6, lane_fin = tid & 63, t_fin = tok0 + 4 * (wave_fin & 3) + (lane_fin >> 4);
+  if (!PARTIAL && !kBiasNow) load_bias_group<NT>(bias, t_fin, T, E, bias_group_tokens, bias_fin);
+  double* const slot = s_part + (size_t)(wave_fin >> 1) * (NT * 4 * 64) + lane_fin;
+  if (wave_fin & 1) {
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
       for (int v = 0; v < 4; ++v) slot[(n * 4 + v) * 64] = acc[n][v];
   }
   __syncthreads();
-  if (!(wave & 1)) {
+  if (!(wave_fin & 1)) {
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
       for (int v = 0; v < 4; ++v) slot[(n * 4 + v) * 64] = acc[n][v] + slot[(n * 4 + v) * 64];
   }
   __syncthreads();
-  if (wave < 4) {
+  if (wave_fin < 4) {
     double sum[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
-      const double* const s = s_part + (n * 4 + wave) * 64 + lane;
+      const double* const s = s_part + (n * 4 + wave_fin) * 64 + lane_fin;
       constexpr int kPair = NT * 4 * 64;
       sum[n] = (s[0] + s[kPair]) + (s[2 * kPair] + s[3 * kPair]);
     }
     if (PARTIAL) {
       double* out = partial + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * (NT * 256);
 #pragma unroll
-      for (int n = 0; n < NT; ++n) out[n * 256 + lane * 4 + wave] = sum[n];
+      for (int n = 0; n < NT; ++n) out[n * 256 + lane_fin * 4 + wave_fin] = sum[n];
     } else {
       finish_group<NT>(sum, bias_fin, bias != nullptr, t_fin, T, E, k, gate_mode, logits, topk_idx, topk_gate,
                        counts != nullptr ? s_counts : nullptr);
