@@ -37,21 +37,18 @@ def test_split_router_in_layer(T, H, E, k, gates):
     check_layer(cfg, o, oracle_layer(inp, mask, renormalize=gates == "renormalized"))
 
 
-@pytest.mark.parametrize("T,E,k", [(6112, 60, 2), (6113, 60, 2), (8192, 60, 4), (8193, 60, 4), (10001, 8, 2)])
+@pytest.mark.parametrize("T,E,k", [(6112, 60, 4), (6113, 60, 4), (8192, 60, 4), (8193, 60, 4), (10001, 8, 2)])
 def test_router_of_large_batches(T, E, k):
-    """Both sides of the lines between the router in one launch (6113 to 8192 tokens) and the spread one: picks, gates and the
-    split.  (No output rows: with F = 64 and half a million of them the largest rounding error is past the bar of 2e-2.)"""
-    from gpu_util import oracle_layer, run_layer, weight_table
+    """Both sides of the lines between the router in one launch (6113 to 8192 tokens) and the spread one, the whole layer."""
+    from gpu_util import check_layer, oracle_layer, run_layer, weight_table
     from prism_inputs import make_config, make_inputs
-    cfg = make_config("cfg4_finegrained", T=T, H=64, F=64, E=E, k=k, S=0, bias_group_tokens=100)
+    H, F = 64, 256
+    # the spread router borrows the FFN's h and y for the histograms of blocks of at least 512 picks and one part of the
+    # logits (experts in tiles of 16, up to a power of two of them); a layer that lacks the room takes the other one
+    experts = 16 * next(n for n in (1, 2, 4, 8, 16) if 16 * n >= E)
+    assert T * k * (H + F) * 2 >= -(-T * k // 512) * E * 4 + 256 + T * experts * 8
+    cfg = make_config("cfg4_finegrained", T=T, H=H, F=F, E=E, k=k, S=0, bias_group_tokens=100)
     mask = (np.random.default_rng([T, E]).random(E) < 0.5).astype(np.uint8)
     inp = make_inputs(cfg)
     o = run_layer(cfg, inp, mask, weight_table(inp, mask))
-    ref = oracle_layer(inp, mask)
-    assert np.array_equal(o.topk_idx.cpu().numpy(), ref.route.topk_idx)
-    assert np.array_equal(o.counts.cpu().numpy(), ref.route.counts)
-    assert np.max(np.abs(o.topk_gate.cpu().numpy() - ref.route.topk_gate)) <= 1e-6
-    nl, nr = (int(v) for v in o.n_local_remote.cpu())
-    assert (nl, nr) == (ref.dispatch.n_local, ref.dispatch.n_remote)
-    assert np.array_equal(o.remote_src.cpu().numpy()[:nr], ref.dispatch.remote_src)
-    assert np.array_equal(o.remote_offsets.cpu().numpy(), ref.dispatch.remote_offsets)
+    check_layer(cfg, o, oracle_layer(inp, mask))
