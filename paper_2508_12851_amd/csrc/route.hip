@@ -375,7 +375,9 @@ struct StagedCfg {
   static constexpr int kBlocks = TMB + NT;                       // 1 KiB blocks per slice
   // Two workgroups share a CU where 2 slices and the partial tiles leave room: one's ring fills and adds up its
   // tiles under the other's products (route stage, 2 x 2 tiles: 3000 tokens x 256 experts of 1024 elements 47 -> 44 us,
-  // 8192 x 200 of 2048 156 -> 142).
+  // 8192 x 200 of 2048 156 -> 142).  Three blocks then have a ring of 3 slices instead of 4, four of 2 instead of 3, also where a
+  // CU has one workgroup: no slower (router in one launch, 16 experts of 2048, 1000 / 8192 tokens 11.2 / 18.5 us
+  // before and after, 30 experts 16.6 / 27.7 -> 16.3 / 27.6).
   static constexpr int kReduceBytes = kWavesPerBlock * TMB * NT * 4 * 64 * 8;
   static constexpr int kShared = 76 * 1024;
   static constexpr bool kTwo = kReduceBytes <= kShared && 2 * kWavesPerBlock * kBlocks * 1024 <= kShared;
@@ -816,7 +818,9 @@ bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, Spl
   // One round of 32-token workgroups on at least three quarters of the CUs: the router in one launch is as good (route
   // and dispatch stages, 60 experts of 2048 elements: 8192 tokens 60 against 61 us split, 6500 tokens 61 / 61).  Beyond, its
   // second round starts with few (10000 tokens 101 / 75, 12288 99 / 80, 16384 101 / 99; 8 experts of 4096, 10000
-  // tokens, 63 / 50).
+  // tokens, 63 / 50), and the spread one stays ahead (in one launch / split, 16385, 24576, 32768, 65536 tokens: 60 experts of 2048
+  // 139 / 116, 143 / 139, 182 / 176, 341 / 324; 64 of 4096 240 / 194, 246 / 246, 322 / 319, 619 / 614; 8 of 4096 90 / 75, 94 / 90,
+  // 119 / 112, 218 / 199).
   const int wgs32 = ceil_div(T, 2 * kTokPerBlock);
   if (staged_router_applies(d, T) && wgs32 >= 192 && wgs32 <= 256) return false;
   const int A = T * d.top_k;
@@ -837,9 +841,9 @@ bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, Spl
   // The shape of a workgroup: the one with the least estimated time.  A SIMD holds two of its
   // wavefronts (four where two workgroups share the CU), and a v_mfma_f64_16x16x4 takes 64 clocks, the
   // conversion of an operand element about 12 more, none of which overlap; filling the ring and adding up the
-  // partial tiles takes about 3000 and 1500 per tile.  (With one workgroup per CU, 13 sizes from 100 x 60 to 8192 x 60 and 3000 x 256 tokens x
-  // experts, all 5 shapes with 1 to 16 parts: what the estimate picks is within 6 % of the fastest
-  // or at the launch floor; the worst shape takes up to twice as long.)
+  // partial tiles takes about 3000 and 1500 per tile.  (130 sizes from 66 to 16384 tokens x 8 to 256 experts, all 5 shapes
+  // with 1 to 16 parts: what the estimate picks takes 1.0 % longer than the fastest on average, and at most 8 %, 0.9 us, up
+  // to 333 tokens, where it takes 8 parts and 4 would do; the worst shape takes up to twice as long.)
   const int tiles = ceil_div(T, kTokPerBlock), cols = ceil_div(d.n_experts, 16), slices = ceil_div(d.hidden, 32);
   const int shapes[5][2] = {{4, 2}, {2, 2}, {4, 1}, {2, 1}, {1, 1}};
   long long best = -1;
