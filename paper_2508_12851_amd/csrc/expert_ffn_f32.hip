@@ -31,8 +31,9 @@
 // Longer contractions would add up more low products and stay in fp32 (LONG).  What has no parts, infinities and very small
 // values, is looked at again (see "Small values").
 //
-// FFN of fp32 products as one launch of a workgroup per item -> here, us: 500 tokens, 1024 x 2048, 5 of 8 experts hosted 157 -> 121
-// (six products, and leading sums kept in the matrix cores: 102); 256 x 512, 64 tokens 18.2 -> 18.3; LONG, 2056 x 2056, 200
+// FFN of fp32 products as one launch of a workgroup per item -> here, us: 500 tokens, 1024 x 2048, 5 of 8 experts hosted 160 -> 124
+// (six products, and leading sums kept in the matrix cores: 102), every tenth token zero 160 -> 138; 256 x 512, 64 tokens
+// 18.2 -> 18.4; LONG, 2056 x 2056, 200
 // tokens 154 -> 137, 4096 x 4096, 4 / 500 tokens 169 / 784 -> 173 / 715.
 #include "prism_internal.h"
 
@@ -64,13 +65,18 @@ constexpr int kStageBytes = (kBM + kBN) * kRowBytes;         // one wavefront's 
 constexpr int kRedPitch = kBN + 4;                           // floats; rows start in different banks
 constexpr int kRedFloats = kBM * kRedPitch;                  // one wavefront's partial tile
 constexpr int kTileBytes = kWaves * kRedFloats * 4;
-constexpr int kMarkWords = 32;           // one bit per item of a workgroup, from the start again after 1024
-constexpr int kLdsBytes = kTileBytes + (kMarkWords + 1) * 4 + (PRISM_MAX_EXPERTS + 1) * 4;   // (+ one word: any mark)
+// Marks: two bits per item of a workgroup (from the start again after 512): its sums need a closer look, or do if some
+// operand is very small.  Two words more: any mark, and whether the second walk has seen such an operand.
+constexpr int kMarkWords = 32;
+constexpr uint32_t kLook = 1, kLookIfSmall = 2;
+constexpr int kControlWords = kMarkWords + 2;
+constexpr int kLdsBytes = kTileBytes + kControlWords * 4 + (PRISM_MAX_EXPERTS + 1) * 4;
 static_assert(kRedFloats * 4 >= kStageBytes && kLdsBytes <= 160 * 1024, "a partial tile replaces its wavefront's k-tile");
 // Which sums of products of parts are good (see "Small values"): of operands up to kPlainMax those from kPlainMin on, otherwise those
 // beyond kLossPerOperand (A + B) + kLossFloor.
 constexpr float kPlainMax = 0x1p30f, kPlainMin = 0x1p-60f;
 constexpr float kLossPerOperand = 0x1p-99f, kLossFloor = 0x1p-116f;
+constexpr float kExactFrom = 0x1p-110f;  // elements that are the sum of their parts, zeros aside
 
 // Rows of fp32 matrices start at any multiple of 4 bytes (F need not be a multiple of 4).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -183,7 +189,7 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
   // items, row tiles running fastest, so that the row tiles of an expert read its weight rows
   // through one L2.
   const int n_col_tiles = (N + kCols - 1) / kCols;
-  const RowTiles tiles = load_row_tiles(p, n_col_tiles, LONG ? kHalfTileF32 : kHalfTile, tid, reinterpret_cast<int*>(marks) + kMarkWords + 1);
+  const RowTiles tiles = load_row_tiles(p, n_col_tiles, LONG ? kHalfTileF32 : kHalfTile, tid, reinterpret_cast<int*>(marks) + kControlWords);
   const int n_row_tiles = tiles.routed + p.S * tiles_of(p.T, tiles.shift);
   const int n_items = n_row_tiles * n_col_tiles;
   const int xcd = blockIdx.x % kXcds, slots = gridDim.x / kXcds;
@@ -253,7 +259,7 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
   };
   auto fetch_first = [&] {
     if (kt0 >= kt1) return;
-    if (K >= 4) {
+    if (!LONG || K >= 4) {
       fetch(kt0);
     } else {   // rows of 1 to 3 elements
 #pragma unroll
@@ -477,21 +483,68 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
         for (int v = 0; v < 16; ++v) acc[i][j][v] = (bad >> v) & 1 ? sum[v] : acc[i][j][v];
       }
   };
-  // Whether no sum of this wavefront can need that: one comparison for all (a NaN stays one either way).
-  auto all_plain = [&](bool two) {
+  // The smallest magnitude but zero, as twice its bits less one (a zero gives the largest number).
+  auto shrink_nonzero = [](uint32_t& m, const float (&v)[2]) {
+    m = min(m, min(2 * __builtin_bit_cast(uint32_t, v[0]) - 1, 2 * __builtin_bit_cast(uint32_t, v[1]) - 1));
+  };
+  auto below = [](uint32_t m, float limit) { return m < 2 * __builtin_bit_cast(uint32_t, limit) - 1; };
+  // Whether some sum of this wavefront needs a closer look.  Mostly one comparison for all says no (a NaN stays one either
+  // way); zeros are left to add_and_store.
+  auto look = [&](bool two) {
     float small = INFINITY;
-    auto shrink = [&](const f32x16& s) {
+    auto each = [&](auto&& fn) {
 #pragma unroll
-      for (int v = 0; v < 16; v += 2) asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(small) : "v"(s[v]), "v"(s[v + 1]));
+      for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) fn(acc[0][j][v], acc[0][j][v + 1]);
+        if (two)
+#pragma unroll
+          for (int v = 0; v < 16; v += 2) fn(acc[1][j][v], acc[1][j][v + 1]);
+      }
     };
+    each([&](float x, float y) { asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(small) : "v"(x), "v"(y)); });
+    if (__builtin_expect(__ballot(!(largest <= kPlainMax && small >= kPlainMin)) == 0, 1)) return false;
+    uint32_t nonzero = ~0u;
+    each([&](float x, float y) { shrink_nonzero(nonzero, {x, y}); });
+    return __ballot(!(largest <= kPlainMax) || below(nonzero, kPlainMin)) != 0;
+  };
+  // Whether an element of this wavefront's k-tiles is below kExactFrom and not zero.
+  auto any_small_element = [&] {
+    uint32_t nonzero = ~0u;
+    for (int kt = kt0; kt < kt1; ++kt) {   // (the first one has been fetched)
+      if (kt * kBK + kBK > K) cut_tail(kt);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      shrink(acc[0][j]);
-      if (two) shrink(acc[1][j]);
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          shrink_nonzero(nonzero, {fa[i][e], fa[i][e + 1]});
+          shrink_nonzero(nonzero, {fb[i][e], fb[i][e + 1]});
+        }
+      if (kt + 1 < kt1) fetch(kt + 1);
     }
-    return __ballot(!(largest <= kPlainMax && small >= kPlainMin)) == 0;
+    return __ballot(below(nonzero, kExactFrom)) != 0;
   };
 
+  int number = 0;   // of the item in this workgroup
+  auto mark_word = [&] { return &marks[number / 16 % kMarkWords]; };
+  auto mark = [&](uint32_t what) {
+    atomicOr(mark_word(), what << (number % 16 * 2));
+    marks[kMarkWords] = 1;
+  };
+  // Whether row `row` (the same in all lanes) of an item's activations has an element that is not zero.
+  auto nonzero_row = [&](const RowTile& rt, int row) {
+    const int r = rt.row_start + row;
+    const int a = !GATED ? r : rt.g < p.E ? p.local_src[r] / p.top_k : rt.tok_base + row;
+    const float* const x = a_base + (uint64_t)(uint32_t)a * (uint32_t)K;
+    bool nonzero = false;
+    for (int k0 = 0; k0 < K && !nonzero; k0 += 1024)
+#pragma unroll
+      for (int k = k0; k < k0 + 1024; k += 256) {   // (what is past the end comes again)
+        const f32x4 v = *reinterpret_cast<const f32x4u*>(x + min(k + lane * 4, K - 4));
+        nonzero |= __ballot(v[0] != 0.f || v[1] != 0.f || v[2] != 0.f || v[3] != 0.f) != 0;
+      }
+    return nonzero;
+  };
   // ---- the eighths: through LDS, where they take the k-tiles' place, and added by all threads ----
   // Register v of lane (r32, q): row r32 of the row half, column 8 (v / 4) + 4 q + v % 4.
   auto add_and_store = [&](const RowTile& rt, int ct) {
@@ -509,6 +562,7 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
               f32x4{acc[i][j][vg * 4], acc[i][j][vg * 4 + 1], acc[i][j][vg * 4 + 2], acc[i][j][vg * 4 + 3]};
     lds_barrier();
     const int row = t >> 3, c4 = (t & 7) * 4;
+    float small = INFINITY;   // smallest magnitude of this lane's totals
     if (row < rt.row_count) {
       auto total = [&](int col) {
         f32x4 s[kWaves], o;
@@ -520,6 +574,12 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
                          ((double)(s[1][e] + s[5][e]) + (double)(s[3][e] + s[7][e])));
         return o;
       };
+      const f32x4 t0 = total(c4), t1 = total(c4 + kBN / 2);
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(small) : "v"(t0[e]), "v"(t0[e + 1]));
+        asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(small) : "v"(t1[e]), "v"(t1[e + 1]));
+      }
       float* const out = (GATED ? p.h : p.y) + (size_t)(rt.row_start + row) * N;
       auto store = [&](int n, const f32x4& v) {
         if (n + 4 <= N) {
@@ -531,26 +591,46 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
         }
       };
       if (GATED) {
-        const f32x4 ag = total(c4), au = total(c4 + kBN / 2);
         f32x4 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (ag[e] / (1.0f + expf(-ag[e]))) * au[e];
+        for (int e = 0; e < 4; ++e) o[e] = (t0[e] / (1.0f + expf(-t0[e]))) * t1[e];
         store(ct * kCols + c4, o);
       } else {
-        store(ct * kCols + c4, total(c4));
-        store(ct * kCols + c4 + kBN / 2, total(c4 + kBN / 2));
+        store(ct * kCols + c4, t0);
+        store(ct * kCols + c4 + kBN / 2, t1);
       }
+    }
+    // A total of zero: of a zero row (padding), or to be looked at if it can be the sum of terms that all vanished.  (A
+    // wavefront's zero in a total that is not does no harm: with the operands that look() lets pass it is off by 2^-94.)
+    if (!LONG && !AGAIN) {
+      unsigned long long zeros = __ballot(small == 0.f);
+      if (__builtin_expect(zeros != 0, 0))
+        do {
+          const int first = __ffsll(zeros) - 1 & ~7;   // of the 8 lanes of a row
+          if (nonzero_row(rt, wave * 8 + first / 8)) mark(kLookIfSmall);
+          zeros &= ~(255ull << first);
+        } while (zeros != 0);
     }
     lds_barrier();   // before the next k-tiles
   };
 
-  int number = 0;   // of the item in this workgroup
   if (AGAIN) {
+    uint32_t* const small_seen = &marks[kMarkWords + 1];
     for (; item < item_end; item += slots, ++number) {
-      if (!((marks[number / 32 % kMarkWords] >> number % 32) & 1)) continue;
+      const uint32_t what = *mark_word() >> (number % 16 * 2) & 3;
+      if (what == 0) continue;
       const Item it = find_item(item);
       set_addresses(it);
       fetch_first();
+      if (!(what & kLook)) {
+        if (any_small_element()) *small_seen = 1;
+        lds_barrier();
+        const bool seen = *small_seen != 0;
+        lds_barrier();
+        if (!seen) continue;
+        *small_seen = 0;
+        fetch_first();
+      }
       const bool two = it.rt.row_count > 32;
       multiply_parts(two);
       if (kt0 < kt1) redo_sums(two);
@@ -572,10 +652,7 @@ __device__ __forceinline__ void walk_items(const F32Args& p, float* const smem, 
       multiply_f32(two);
     } else {
       multiply_parts(two);
-      if (kt0 < kt1 && !all_plain(two)) {
-        atomicOr(&marks[number / 32 % kMarkWords], 1u << number % 32);
-        marks[kMarkWords] = 1;
-      }
+      if (__builtin_expect(kt0 < kt1 && look(two), 0)) mark(kLook);
     }
     if (has_next) {   // the next item's first k-tile travels during the sums of this one
       set_addresses(next);
@@ -594,8 +671,8 @@ __global__ __launch_bounds__(kThreads) void ffn_f32_kernel(const F32Args p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __align__(16) float smem[];
   int* const marks = reinterpret_cast<int*>(smem) + kTileBytes / 4;
-  for (int i = threadIdx.x; i <= kMarkWords + 1 + PRISM_MAX_EXPERTS; i += kThreads)   // marks, offsets
-    marks[i] = i <= kMarkWords ? 0 : p.local_offsets[min(i - kMarkWords - 1, p.E)];
+  for (int i = threadIdx.x; i <= kControlWords + PRISM_MAX_EXPERTS; i += kThreads)
+    marks[i] = i < kControlWords ? 0 : p.local_offsets[min(i - kControlWords, p.E)];
   __syncthreads();
   walk_items<GATED, LONG, false>(p, smem, threadIdx.x);
   if (!LONG && marks[kMarkWords] != 0) {   // (written before the last barrier)
@@ -636,11 +713,12 @@ prism_status launch_expert_ffn_f32(const prism_layer_desc& d, const void* x, con
   const F32Args a{(const float*)x, w.w_gate, w.w_up, w.w_down, w.shared_w_gate, w.shared_w_up,
                   w.shared_w_down, local_src, local_offsets, (float*)h, (float*)y,
                   T, d.hidden, d.ffn, d.n_experts, d.n_shared, d.top_k};
+  auto in_parts = [](int K) { return K >= 4 && K <= kSplitMaxK; };   // (LONG has the code for rows shorter than a load)
   trace(stage_events, PRISM_STAGE_FFN_UP, 0, st);
-  PRISM_TRY((d.hidden > kSplitMaxK ? launch_f32_gemm<true, true> : launch_f32_gemm<true, false>)(a, st));
+  PRISM_TRY((in_parts(d.hidden) ? launch_f32_gemm<true, false> : launch_f32_gemm<true, true>)(a, st));
   trace(stage_events, PRISM_STAGE_FFN_UP, 1, st);
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 0, st);
-  PRISM_TRY((d.ffn > kSplitMaxK ? launch_f32_gemm<false, true> : launch_f32_gemm<false, false>)(a, st));
+  PRISM_TRY((in_parts(d.ffn) ? launch_f32_gemm<false, false> : launch_f32_gemm<false, true>)(a, st));
   trace(stage_events, PRISM_STAGE_FFN_DOWN, 1, st);
   return PRISM_OK;
 }

@@ -178,7 +178,7 @@ def test_f32_ffn_rows_do_not_depend_on_their_neighbours(T, H, F, value):
         np.testing.assert_array_equal(run_one_expert(x, wg, wu, odd)[:, rest], plain[:, rest])
 
 
-def test_f32_ffn_marks_more_than_1024_items_of_a_workgroup():
+def test_f32_ffn_marks_more_items_than_a_workgroup_has_marks():
     """Small rows in the first and last tiles of 271392 items, 1060 per workgroup: only their rows are redone."""
     T, H, F = 66 * 1024, 8, 8200                 # 1056 row tiles of 64 rows x 257 column tiles of h
     x, wg, wu, wd = normal_operands(T, H, F)
@@ -204,3 +204,31 @@ def test_f32_ffn_single_products():
     # one rounding to fp32, 2^-24; the seven smaller products of parts (at most 2^-8 of the product each, two
     # roundings of 2^-24 apiece) add less than 14 * 2^-32, the ninth, left out, 2^-34
     assert np.all(np.abs(y - ref) <= 2.0 ** -24 * (1 + 2.0 ** -4) * np.abs(ref))
+
+
+def test_f32_ffn_down_projection_of_subnormal_weights():
+    """Weights so small that their bf16 parts are all zero: the sums come out as zeros and are looked at again."""
+    T, H, F = 40, 72, 136
+    x, wg, wu, wd = normal_operands(T, H, F)
+    wd = np.ldexp(wd * np.float32(np.sqrt(F)), -139).astype(np.float32)
+    y = run_one_expert(x, wg, wu, wd).astype(np.float64)
+    g, u, d = (m.astype(np.float64) for m in (wg, wu, wd))
+    z = x.astype(np.float64) @ g.T
+    ref = (z / (1.0 + np.exp(-z)) * (x.astype(np.float64) @ u.T)) @ d.T
+    # results are multiples of 2^-149, each of the F products is rounded to one, half of it at most
+    assert np.abs(ref).max() > 2.0 ** -138 and np.all(np.abs(y - ref) <= F * 2.0 ** -150)
+
+
+@pytest.mark.parametrize("T,H,F", [(33, 64, 40), (300, 1024, 72), (200, 72, 1024)])
+def test_f32_ffn_sparse_rows(T, H, F):
+    """Rows with few elements or none: most sums of a wavefront are zeros.  Bound: test_f32_ffn_edges."""
+    x, wg, wu, wd = normal_operands(T, H, F)
+    rng = np.random.default_rng(T)
+    x[rng.random((T, H)) < 0.97] = 0
+    x[::7] = 0
+    wd[rng.random((H, F)) < 0.97] = 0
+    y = run_one_expert(x, wg * 4, wu * 4, wd * 4)
+    g, u, d = (4 * m.astype(np.float64) for m in (wg, wu, wd))
+    z = x.astype(np.float64) @ g.T
+    ref = (z / (1.0 + np.exp(-z)) * (x.astype(np.float64) @ u.T)) @ d.T
+    assert np.linalg.norm(y - ref) <= 1e-6 * np.linalg.norm(ref) and not y[::7].any()
