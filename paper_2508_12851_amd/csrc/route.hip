@@ -841,7 +841,7 @@ bool plan_split_route(const prism_layer_desc& d, int T, const Workspace& ws, Spl
   // The shape of a workgroup: the one with the least estimated time.  A SIMD holds two of its
   // wavefronts (four where two workgroups share the CU), and a v_mfma_f64_16x16x4 takes 64 clocks, the
   // conversion of an operand element about 12 more, none of which overlap; filling the ring and adding up the
-  // partial tiles takes about 3000 and 1500 per tile.  (130 sizes from 66 to 16384 tokens x 8 to 256 experts, all 5 shapes
+  // partial tiles takes about 3000 and 1500 per tile.  (140 sizes from 66 to 16384 tokens x 8 to 256 experts, all 5 shapes
   // with 1 to 16 parts: what the estimate picks takes 1.0 % longer than the fastest on average, and at most 8 %, 0.9 us, up
   // to 333 tokens, where it takes 8 parts and 4 would do; the worst shape takes up to twice as long.)
   const int tiles = ceil_div(T, kTokPerBlock), cols = ceil_div(d.n_experts, 16), slices = ceil_div(d.hidden, 32);
